@@ -469,39 +469,97 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
 bool nucleus_on(const duo_call* call) { return call->top_p > 0.f && call->top_p < 1.f && call->temperature > 0.f; }
 
 // After the statistics: the nucleus of every judging row (sa.nuc is where the other kernels will look for it).
-void enqueue_nucleus(const SampleArgs& sa, float top_p, const Workspace& ws, hipStream_t s) {
+// row_stats: the rows' merged statistics, or nullptr (see SpreadBuf).
+void enqueue_nucleus(const SampleArgs& sa, float top_p, const Workspace& ws, const double* row_stats, hipStream_t s) {
     if (!sa.nuc) return;
+    const int rows = 1 + sa.n * sa.k;
+    NucBuf b{nullptr, nullptr, 0, 0, 0, row_stats};
     prof(DUO_PROF_SAMPLE, s);
-    if (sa.V <= 32 * SAMPLE_THREADS)
-        DUO_LAUNCH(sample_nucleus_kernel<32>, dim3(1 + sa.n * sa.k), dim3(SAMPLE_THREADS), s, sa, (double)top_p, ws.p_rows, ws.nuc);
-    else
-        DUO_LAUNCH(sample_nucleus_kernel<0>, dim3(1 + sa.n * sa.k), dim3(SAMPLE_THREADS), s, sa, (double)top_p, ws.p_rows, ws.nuc);
+    if (sa.V < NUC_SMALL_VOCAB) {
+        DUO_LAUNCH(nucleus_cut_kernel<true>, dim3(rows), dim3(SAMPLE_THREADS), s, sa, (double)top_p, b, ws.nuc);
+        return;
+    }
+    // slices of at least 4096 ids, at most 16 per row: masses and bins of a row take 16 KiB per slice + 2 bytes per id, which
+    // is at most 4V + 2V of the row's 8V bytes of scratch
+    b.G = std::min(16, sa.V / 4096);
+    b.slice = (sa.V + b.G - 1) / b.G;
+    b.bin_stride = (sa.V + 7) / 8 * 8;
+    static_assert(NUC_SMALL_VOCAB >= 8192 && NUC_BINS * sizeof(u64) <= 4096 * 4, "masses and bins fit the rows' scratch");
+    b.hist = reinterpret_cast<u64*>(ws.p_rows);
+    b.bins = reinterpret_cast<uint16_t*>(b.hist + (size_t)rows * b.G * NUC_BINS);
+    DUO_LAUNCH(nucleus_hist_kernel, dim3(rows, b.G), dim3(512), s, sa, b);
+    prof(DUO_PROF_SAMPLE, s);
+    DUO_LAUNCH(nucleus_cut_kernel<false>, dim3(rows), dim3(SAMPLE_THREADS), s, sa, (double)top_p, b, ws.nuc);
 }
 
-// have_stats: the forward pass that produced the logits left their softmax statistics (and the root row's) already
+// Statistics of the judging rows in front of the sampling kernels.  have_stats: the forward pass that produced the logits
+// left them already (one part per 32 vocabulary entries and row, and the root row's); they are merged once where many
+// workgroups will read them (merge), and the merged ones' address is returned.  The parts of caller-supplied logits are few: the kernels that need a
+// row merge it themselves (a launch less: 4.4 us), nullptr is returned.
+// status_ready: the call's status word has been initialised by an earlier kernel.
+double* enqueue_statistics(const SampleArgs& sa, hipStream_t s, bool have_stats, bool status_ready, bool merge) {
+    prof(DUO_PROF_SAMPLE, s);
+    if (!have_stats) {
+        const dim3 grid(sa.R + sa.n * sa.k + (sa.R ? 0 : 1), STATS_SPLIT);
+        if (sa.V <= 1024 * STATS_SPLIT) DUO_LAUNCH(sample_stats_kernel<256>, grid, dim3(256), s, sa, status_ready ? 0 : 1);
+        else DUO_LAUNCH(sample_stats_kernel<SAMPLE_THREADS>, grid, dim3(SAMPLE_THREADS), s, sa, status_ready ? 0 : 1);
+        return nullptr;
+    }
+    if (!merge) return nullptr;
+    static_assert(2 * (DUO_MAX_ROWS + 2) <= 256 && SPREAD_MIN_VOCAB >= 256, "the merged statistics are the first 256 doubles of p_run");
+    // (letting every slice merge the statistics of its sequence's rows itself saves this launch and costs more:
+    // 2 x 11.6 against 3 x 6.9 us at 9 rows of 1000 parts)
+    DUO_LAUNCH(sample_row_stats_kernel, dim3(sa.R + sa.n * sa.k + 1), dim3(256), s, sa, sa.p_run);
+    return sa.p_run;
+}
+
+// The sequential first-token rule (both forms) for vocabularies of SEQ_MIN_VOCAB entries and more.  Whole calls on caller-supplied
+// logits, one workgroup against many launches (n sequences of k tokens, 32000 entries): 1 x 8 47.5 -> 23 us, 3 x 11 54 -> 32 us, 8 x 4 51 -> 34 us;
+// 128256 entries: 170 -> 29, 312 -> 60, 365 -> 80 us; 12288 entries: 27 -> 22, 27 -> 28, 27 -> 28 us, where the line is drawn.
+void enqueue_sequential(const SampleArgs& sa, const SeqArgs& d, double* row_stats, hipStream_t s) {
+    const int G = std::min(SPREAD_MAX_SLICES, sa.V / 2048);
+    const int chunk = ((sa.V + 16 * G - 1) / (16 * G) + 63) / 64 * 64;
+    static_assert(256 + SEQ_STAGES + (SEQ_STAGES + 1) * 4 <= 512, "totals and records lie between the merged statistics and the sums");
+    static_assert(512 + 2 * 16 * SPREAD_MAX_SLICES * 3 <= SEQ_MIN_VOCAB, "the records fit p_run");
+    SeqBuf b{row_stats, sa.p_run + 256, reinterpret_cast<int32_t*>(sa.p_run + 256 + SEQ_STAGES), sa.p_run + 512,
+             reinterpret_cast<int32_t*>(sa.p_run + 512 + (size_t)2 * 16 * G * 2), G, chunk,
+             std::max(3, std::min(SEQ_STAGES, sa.V / 8192))};
+    const int launches = std::max(1, std::min(d.s, b.stages));
+    for (int i = 0; i < launches; ++i) {
+        prof(DUO_PROF_SAMPLE, s);
+        if (sa.nuc) DUO_LAUNCH(seq_stage_kernel<true>, dim3(G), dim3(SAMPLE_THREADS), s, sa, d, b, i);
+        else DUO_LAUNCH(seq_stage_kernel<false>, dim3(G), dim3(SAMPLE_THREADS), s, sa, d, b, i);
+    }
+    const int32_t* rec = b.rec + (launches - 1) * 8;
+    if (d.s > b.stages) {
+        prof(DUO_PROF_SAMPLE, s);
+        if (sa.nuc) DUO_LAUNCH(seq_tail_kernel<true>, dim3(1), dim3(SAMPLE_THREADS), s, sa, d, b);
+        else DUO_LAUNCH(seq_tail_kernel<false>, dim3(1), dim3(SAMPLE_THREADS), s, sa, d, b);
+        rec = b.rec + b.stages * 8;
+    }
+    prof(DUO_PROF_SAMPLE, s);
+    if (sa.nuc) DUO_LAUNCH(seq_locate_kernel<true>, dim3(1), dim3(64), s, sa, d, b, rec, launches);
+    else DUO_LAUNCH(seq_locate_kernel<false>, dim3(1), dim3(64), s, sa, d, b, rec, launches);
+}
+
 void enqueue_sampling(const SampleArgs& sa, float top_p, const Workspace& ws, int mode, u16* kc, u16* vc,
                       const duo_model_config* c, int32_t* prefix_len, hipStream_t s, bool have_stats = false) {
-    if (!have_stats) {
-        prof(DUO_PROF_SAMPLE, s);
-        DUO_LAUNCH(sample_stats_kernel, dim3(sa.R + sa.n * sa.k + (sa.R ? 0 : 1), STATS_SPLIT), dim3(256), s, sa);
-    }
-    enqueue_nucleus(sa, top_p, ws, s);
-    prof(DUO_PROF_SAMPLE, s);
+    // the one-workgroup rules merge the parts themselves
+    const bool merged = sa.V >= (mode == DUO_SELECT_INDEPENDENT_LONGEST ? SPREAD_MIN_VOCAB : SEQ_MIN_VOCAB);
+    double* row_stats = enqueue_statistics(sa, s, have_stats, have_stats, merged);
+    enqueue_nucleus(sa, top_p, ws, row_stats, s);
     if (mode == DUO_SELECT_INDEPENDENT_LONGEST) {
         // one sequence: nothing to choose and nothing to move, the finish kernel writes the commit itself
         const bool self_commit = sa.n == 1;
+        prof(DUO_PROF_SAMPLE, s);
         if (sa.V >= SPREAD_MIN_VOCAB) {
-            // large vocabulary: row statistics, slice sums and the search as three small kernels over many compute units
+            // large vocabulary: row statistics, slice sums and the search as small kernels over many compute units
             int G = sa.V / 4096;
             G = std::min(G, std::min(SPREAD_MAX_SLICES, SPREAD_MAX_GROUPS / sa.n));
             G = std::max(G, 1);
             const int chunk = ((sa.V + 16 * G - 1) / (16 * G) + 63) / 64 * 64;
-            static_assert(2 * (DUO_MAX_ROWS + 2) <= 256 && 256 + SPREAD_MAX_GROUPS * 16 * 3 <= SPREAD_MIN_VOCAB, "the records fit p_run");
-            SpreadBuf sb{sa.p_run, sa.p_run + 256, reinterpret_cast<int32_t*>(sa.p_run + 256 + (size_t)sa.n * 16 * G * 2), G, chunk};
-            // (letting every slice merge the statistics of its sequence's rows itself saves this launch and costs more:
-            // 2 x 11.6 against 3 x 6.9 us at 9 rows of 1000 parts)
-            DUO_LAUNCH(sample_row_stats_kernel, dim3(sa.R + sa.n * sa.k + 1), dim3(256), s, sa, sb);
-            prof(DUO_PROF_SAMPLE, s);
+            static_assert(256 + SPREAD_MAX_GROUPS * 16 * 3 <= SPREAD_MIN_VOCAB, "the records fit p_run");
+            SpreadBuf sb{row_stats, sa.p_run + 256, reinterpret_cast<int32_t*>(sa.p_run + 256 + (size_t)sa.n * 16 * G * 2), G, chunk};
             if (sa.nuc) DUO_LAUNCH(sample_spread_kernel<true>, dim3(sa.n, G), dim3(SAMPLE_THREADS), s, sa, sb);
             else DUO_LAUNCH(sample_spread_kernel<false>, dim3(sa.n, G), dim3(SAMPLE_THREADS), s, sa, sb);
             prof(DUO_PROF_SAMPLE, s);
@@ -510,7 +568,11 @@ void enqueue_sampling(const SampleArgs& sa, float top_p, const Workspace& ws, in
         } else if (sa.nuc) DUO_LAUNCH(sample_finish_kernel<true>, dim3(sa.n), dim3(SAMPLE_THREADS), s, sa, self_commit ? 1 : 0, prefix_len);
         else DUO_LAUNCH(sample_finish_kernel<false>, dim3(sa.n), dim3(SAMPLE_THREADS), s, sa, self_commit ? 1 : 0, prefix_len);
         if (self_commit) return;
+    } else if (sa.V >= SEQ_MIN_VOCAB) {
+        enqueue_sequential(sa, SeqArgs{sa.tokens, sa.k, sa.q, (size_t)sa.k * sa.V, sa.u, sa.k + 1, sa.n, 0, prefix_len}, row_stats, s);
+        if (!kc) return;  // nothing to move, and the commit record is written
     } else {
+        prof(DUO_PROF_SAMPLE, s);
         if (sa.nuc) DUO_LAUNCH(sample_paper_kernel<true>, dim3(1), dim3(SAMPLE_THREADS), s, sa);
         else DUO_LAUNCH(sample_paper_kernel<false>, dim3(1), dim3(SAMPLE_THREADS), s, sa);
     }
@@ -591,7 +653,6 @@ int spec_sample_on_scratch(const float* logits, const float* root_logits, int vo
     ws.acc = reinterpret_cast<int32_t*>(b + NOALLOC_STATS_BYTES + NOALLOC_PRUN_BYTES);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     (void)hipGetLastError();
-    DUO_LAUNCH(fill_i32_kernel, dim3(1), dim3(64), s, out->status, 1, 0);
     SampleArgs sa{logits, vocab, root_logits, vocab, call->n, call->k, R, call->host_prefix_len, (double)call->temperature,
                   draft_tokens, draft_probs, uniforms, ws.stats_rows, ws.stats_parts, ws.stats_root, STATS_SPLIT, ws.acc, ws.p_run, out->accept_len, out->next_token,
                   out->commit, out->status, nullptr};
@@ -692,7 +753,6 @@ int duo_spec_sample(const float* logits, const float* root_logits, int vocab, co
     carve_sampler(static_cast<char*>(workspace), off, vocab, ws);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     (void)hipGetLastError();
-    DUO_LAUNCH(fill_i32_kernel, dim3(1), dim3(64), s, out->status, 1, 0);
     SampleArgs sa{logits, vocab, root_logits, vocab, call->n, call->k, R, call->host_prefix_len, (double)call->temperature,
                   draft_tokens, draft_probs, uniforms, ws.stats_rows, ws.stats_parts, ws.stats_root, STATS_SPLIT, ws.acc, ws.p_run, out->accept_len, out->next_token,
                   out->commit, out->status,
@@ -719,12 +779,13 @@ static int check_deferred(const duo_call* call, int vocab, const int32_t* first_
 }
 
 static void enqueue_deferred_sampling(const SampleArgs& sa, float top_p, const Workspace& ws, const DeferredArgs& da,
-                                      hipStream_t s, bool have_stats = false) {
-    if (!have_stats) {
-        prof(DUO_PROF_SAMPLE, s);
-        DUO_LAUNCH(sample_stats_kernel, dim3(sa.R + sa.k + (sa.R ? 0 : 1), STATS_SPLIT), dim3(256), s, sa);
+                                      hipStream_t s, bool have_stats = false, bool status_ready = false) {
+    double* row_stats = enqueue_statistics(sa, s, have_stats, status_ready, sa.V >= SEQ_MIN_VOCAB);
+    enqueue_nucleus(sa, top_p, ws, row_stats, s);
+    if (sa.V >= SEQ_MIN_VOCAB) {
+        enqueue_sequential(sa, SeqArgs{da.first_tokens, 1, da.first_probs, (size_t)sa.V, da.uniforms_first, 1, da.s, 1, da.prefix_len}, row_stats, s);
+        return;
     }
-    enqueue_nucleus(sa, top_p, ws, s);
     prof(DUO_PROF_SAMPLE, s);
     if (sa.nuc) DUO_LAUNCH(sample_deferred_kernel<true>, dim3(1), dim3(SAMPLE_THREADS), s, sa, da);
     else DUO_LAUNCH(sample_deferred_kernel<false>, dim3(1), dim3(SAMPLE_THREADS), s, sa, da);
@@ -767,7 +828,7 @@ int duo_verify_deferred(const duo_model_config* cfg, const duo_weights* w, duo_k
                   out->accept_len, out->next_token, out->commit, out->status,
                   nucleus_on(call) ? ws.nuc : nullptr};
     enqueue_deferred_sampling(sa, call->top_p, ws, DeferredArgs{first_tokens, first_probs, uniforms_first, s_new, cache->prefix_len}, s,
-                              M > 0);  // a pass that scored rows left their statistics and the root logits'
+                              M > 0, true);  // a pass that scored rows left their statistics and the root logits'
     return hip_ok(hipGetLastError(), "duo_verify_deferred launch");
 }
 
@@ -789,7 +850,6 @@ int duo_deferred_sample(const float* logits, const float* root_logits, int vocab
     carve_sampler(static_cast<char*>(workspace), off, vocab, ws);
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     (void)hipGetLastError();
-    DUO_LAUNCH(fill_i32_kernel, dim3(1), dim3(64), s, out->status, 1, 0);
     SampleArgs sa{logits, vocab, root_logits, vocab, 1, call->k, R, call->host_prefix_len, (double)call->temperature,
                   unverified_tokens, unverified_probs, uniforms, ws.stats_rows, ws.stats_parts, ws.stats_root, STATS_SPLIT, ws.acc, ws.p_run, out->accept_len, out->next_token,
                   out->commit, out->status,

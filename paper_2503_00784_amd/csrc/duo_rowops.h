@@ -268,11 +268,6 @@ __global__ void status_init_kernel(int32_t* status, const int32_t* prefix_len, i
     if (blockIdx.x == 0 && threadIdx.x == 0) *status = (prefix_len && *prefix_len != host_P) ? 2 : 0;
 }
 
-__global__ void fill_i32_kernel(int32_t* p, int n, int32_t v) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
 // Row m of a paired operand buffer (hi at row m, lo at row pair_rows + m; `tiles` row tiles per K step) as an operand
 // of its own for a one-row product: one tile per K step, hi in row 0, lo in row 8, all other rows zero.
 // grid = K/32 workgroups of one wave.

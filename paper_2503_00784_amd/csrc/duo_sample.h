@@ -5,16 +5,17 @@
 // the volumes are tiny next to the weight stream (two passes over a few vocabulary rows).
 //   sample_stats_kernel   max and normaliser of softmax(logits / T) for every row of logits, the vocabulary cut into
 //                         slices for parallelism (caller-supplied logits only: in the verify step the LM head's
-//                         epilogue leaves these statistics, one part per 32-column tile, see EpiLogitsStats)
-//   sample_finish_kernel  one workgroup per sequence: accept flags, leading accepts, then the
-//                         correction token from norm(max(0, p - q)) or the bonus token from p
-//   sample_row_stats_kernel, sample_spread_kernel, sample_locate_kernel
-//                         the same rule for vocabularies of SPREAD_MIN_VOCAB entries and more, spread over many
-//                         workgroups (see there)
-//   sample_paper_kernel   the sequential first-token rule over the n sequences, with the
-//                         running distribution replaced by its residual after each rejection
-//   sample_deferred_kernel  Alg. 2 as listed: verify the unverified suffix, then judge only the first
-//                         tokens of the new sequences
+//                         epilogue leaves these statistics, one part per 32-column tile, see EpiLogitsStats, and
+//                         sample_row_stats_kernel merges them)
+//   sample_spread_kernel, sample_locate_kernel
+//                         independent sequences, vocabularies of SPREAD_MIN_VOCAB entries and more: accept flags, leading
+//                         accepts, then the correction token from norm(max(0, p - q)) or the bonus token from p
+//   seq_stage_kernel, seq_tail_kernel, seq_locate_kernel
+//                         the sequential first-token rule over the candidate sequences, with the running distribution
+//                         replaced by its residual after each rejection: the call's own sequences, or (Alg. 2 as listed)
+//                         new sequences behind a verified suffix; the same vocabularies
+//   sample_finish_kernel, sample_paper_kernel, sample_deferred_kernel
+//                         the same rules for small vocabularies, one workgroup per sequence or per call
 //   commit_kernel         picks the sequence to keep, moves its accepted K/V next to the prefix
 //
 // T = 0 is the greedy limit of the same rule: softmax(logits / T) tends to the one-hot distribution at the
@@ -23,8 +24,8 @@
 // same one-hot unless q already puts all its mass there).  The statistics then hold the arg max instead of the
 // normaliser; everything else runs unchanged on the one-hot p.
 //
-// Nucleus (top-p) restriction of the target distributions: sample_nucleus_kernel finds, per judging row, the
-// set of most probable tokens whose mass reaches top_p (equal probabilities by ascending id) as a threshold on
+// Nucleus (top-p) restriction of the target distributions: nucleus_hist_kernel and nucleus_cut_kernel find, per judging
+// row, the set of most probable tokens whose mass reaches top_p (equal probabilities by ascending id) as a threshold on
 // the logit plus the last admitted id among the logits equal to it, and the kept mass; the kernels above then
 // evaluate p'(v) = p(v) / kept mass inside the set and 0 outside.  Without it (nuc == nullptr) nothing changes.
 #pragma once
@@ -156,24 +157,71 @@ __device__ __forceinline__ void slice_stats(const float* __restrict__ row, int v
 
 // grid (R + n*k + (R ? 0 : 1), STATS_SPLIT): slice sl of row r of `logits`, the last row index being root_logits when
 // there is no root row.  Used when the logits come from the caller; the verify step's LM head leaves the same
-// statistics itself (EpiLogitsStats in duo_gemm.h) and the pass's first kernel those of root_logits.
-__global__ __launch_bounds__(256) void sample_stats_kernel(SampleArgs a) {
+// statistics itself (EpiLogitsStats in duo_gemm.h) and the pass's first kernel those of root_logits.  As the first kernel
+// of a sampling-only call it also sets the status word (set_status): its first workgroup checks the draft tokens.
+// A thread holds its share of the slice in registers between the maximum and the sum (up to 16 values, i.e. a vocabulary of
+// 131072 with 1024 threads; longer slices are read twice): one trip to memory, and 16 waves per slice for the
+// double-precision exponentials the kernel is bound by (128256 entries, 65 rows: with four waves that read the slice
+// twice 46 us).  At most 64 registers, so that two workgroups of 1024 fit a compute unit: 65 rows are 520 workgroups, three
+// rounds of one per compute unit otherwise.  Slices of up to 1024 entries are left to four waves, whose block sums are shorter.
+template <int TH>
+__global__ __launch_bounds__(TH, 8) void sample_stats_kernel(SampleArgs a, int set_status) {
     __shared__ double sm[16];
-    const int r = blockIdx.x, sl = blockIdx.y, rows = a.R + a.n * a.k;
+    const int r = blockIdx.x, sl = blockIdx.y, rows = a.R + a.n * a.k, tid = threadIdx.x;
     const float* row = r < rows ? a.logits + (size_t)r * a.ld : a.root_logits;
     const int len = (a.V + STATS_SPLIT - 1) / STATS_SPLIT;
-    const int v0 = sl * len, v1 = min(a.V, v0 + len);
-    double zmax, Z;
-    slice_stats(row, v0, v1, a.T, sm, zmax, Z);
-    if (threadIdx.x == 0) {
+    const int v0 = min(a.V, sl * len), v1 = min(a.V, v0 + len);
+    constexpr int PER = 16;
+    const bool in_regs = len <= PER * TH;
+    float x[PER];
+    float lm = -INFINITY;
+    if (in_regs) {
+#pragma unroll
+        for (int e = 0; e < PER; ++e) {  // beyond the slice: its first value again (a slice may be empty: any value of the row)
+            const int v = v0 + tid + e * TH;
+            x[e] = row[v < v1 ? v : 0];
+        }
+#pragma unroll
+        for (int e = 0; e < PER; ++e) lm = v0 + tid + e * TH < v1 ? fmaxf(lm, x[e]) : lm;
+    } else {
+        for (int v = v0 + tid; v < v1; v += TH) lm = fmaxf(lm, row[v]);
+    }
+    if (set_status && r == 0 && sl == 0) {
+        const int raw = tid < a.n * a.k ? a.tokens[tid] : 0;  // n * k is at most DUO_MAX_ROWS
+        const int bad = __syncthreads_or(raw < 0 || raw >= a.V);
+        if (tid == 0 && a.status) *a.status = bad ? 1 : 0;
+    }
+    double zmax = block_max_d((double)lm, sm), Z;
+    if (a.greedy()) {  // Z: the lowest id of the slice that holds the slice's largest logit
+        int first = 0x7fffffff;
+        if (in_regs) {
+#pragma unroll
+            for (int e = PER - 1; e >= 0; --e)
+                if (v0 + tid + e * TH < v1 && (double)x[e] == zmax) first = v0 + tid + e * TH;
+        } else {
+            for (int v = v0 + tid; v < v1; v += TH)
+                if ((double)row[v] == zmax) first = min(first, v);
+        }
+        Z = -block_max_d(-(double)first, sm);
+    } else {
+        const double iT = 1.0 / a.T;  // a reciprocal instead of a division per entry: an ulp, as in TokenWeights
+        zmax *= iT;
+        double s = 0.0;
+        if (in_regs) {
+#pragma unroll
+            for (int e = 0; e < PER; ++e) {
+                if (e * TH >= len) break;  // workgroup-uniform
+                if (v0 + tid + e * TH < v1) s += exp((double)x[e] * iT - zmax);
+            }
+        } else {
+            for (int v = v0 + tid; v < v1; v += TH) s += exp((double)row[v] * iT - zmax);
+        }
+        Z = block_sum_d(s, sm);
+    }
+    if (tid == 0) {
         double* st = (r < rows ? a.stats_rows + ((size_t)r * a.parts + sl) * 2 : a.stats_root + sl * 2);
         st[0] = zmax;
         st[1] = Z;
-        const int t = r - a.R;  // the draft token this row belongs to
-        if (sl == 0 && t >= 0 && t < a.n * a.k) {
-            const int raw = a.tokens[t];
-            if ((raw < 0 || raw >= a.V) && a.status) atomicOr(a.status, 1);
-        }
     }
 }
 
@@ -183,31 +231,38 @@ struct SeqStats {
     double (*t)[2];
 };
 
-// Merge of the partial statistics of judging rows (i, j0 .. j1) into st.t[j]: one wave per row, lanes stride over the
-// parts, fixed butterflies (deterministic).  All threads of the workgroup call it; ends with a barrier.
+// Merge of the partial statistics of one judging row (jr as judge_index returns it) by one wave: lanes stride over the
+// parts, fixed butterflies (deterministic); every lane gets the result.
+__device__ __forceinline__ void wave_row_stats(const SampleArgs& a, int jr, double& zmax, double& Z) {
+    const int lane = threadIdx.x & 63;
+    const double* pt = jr < 0 ? a.stats_root : a.stats_rows + (size_t)jr * a.parts * 2;
+    const int np = jr < 0 ? a.root_parts : a.parts;
+    double mx = -INFINITY;
+#pragma unroll 4
+    for (int p = lane; p < np; p += 64) mx = fmax(mx, pt[2 * p]);
+    mx = wave_max(mx);
+    if (a.greedy()) {  // the lowest id among the parts that hold the largest logit (parts are in id order)
+        double first = 4.0e9;
+        for (int p = lane; p < np; p += 64)
+            if (pt[2 * p] == mx) first = fmin(first, pt[2 * p + 1]);
+        Z = -wave_max(-first);
+    } else {
+        double sum = 0.0;
+#pragma unroll 4
+        for (int p = lane; p < np; p += 64)
+            if (pt[2 * p + 1] > 0.0) sum += pt[2 * p + 1] * exp(pt[2 * p] - mx);
+        Z = wave_sum(sum);
+    }
+    zmax = mx;
+}
+
+// The same for judging rows (i, j0 .. j1) into st.t[j], one wave per row.  All threads of the workgroup call it; ends
+// with a barrier.
 __device__ __forceinline__ void load_seq_stats(const SampleArgs& a, int i, int j0, int j1, const SeqStats& st) {
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, nw = blockDim.x >> 6;
     for (int j = j0 + wave; j <= j1; j += nw) {
-        const int jr = a.judge_index(i, j);
-        const double* pt = jr < 0 ? a.stats_root : a.stats_rows + (size_t)jr * a.parts * 2;
-        const int np = jr < 0 ? a.root_parts : a.parts;
-        double mx = -INFINITY;
-#pragma unroll 4
-        for (int p = lane; p < np; p += 64) mx = fmax(mx, pt[2 * p]);
-        mx = wave_max(mx);
-        double Z;
-        if (a.greedy()) {  // the lowest id among the parts that hold the largest logit (parts are in id order)
-            double first = 4.0e9;
-            for (int p = lane; p < np; p += 64)
-                if (pt[2 * p] == mx) first = fmin(first, pt[2 * p + 1]);
-            Z = -wave_max(-first);
-        } else {
-            double sum = 0.0;
-#pragma unroll 4
-            for (int p = lane; p < np; p += 64)
-                if (pt[2 * p + 1] > 0.0) sum += pt[2 * p + 1] * exp(pt[2 * p] - mx);
-            Z = wave_sum(sum);
-        }
+        double mx, Z;
+        wave_row_stats(a, a.judge_index(i, j), mx, Z);
         if (lane == 0) {
             st.t[j][0] = mx;
             st.t[j][1] = Z;
@@ -239,115 +294,351 @@ __device__ __forceinline__ void fill_running_distribution(const SampleArgs& a, c
     __syncthreads();
 }
 
-// One workgroup per judging row r (0 = the root distribution, 1 + i*k + (j-1) = row (i, j)).  `prow` ([rows][V]
-// doubles) holds the row's probabilities while the threshold is searched: bit by bit from the top, the largest
-// logit key t with mass{key >= t} >= top_p * total (32 block sums in a fixed order), then as many of the ids that
-// sit exactly on the threshold, in ascending order, as the target still needs.
-// PT > 0: the vocabulary has at most PT * 1024 entries and every thread keeps its PT keys and probabilities in
-// registers for the 33 passes (they are latency-bound otherwise: 340 -> 120 us for nine rows of 32000); PT = 0: any
-// vocabulary, the passes re-read the row.
-template <int PT>
-__global__ __launch_bounds__(SAMPLE_THREADS) void sample_nucleus_kernel(SampleArgs a, double top_p, double* __restrict__ prow_all,
-                                                                        double* __restrict__ nuc_out) {
-    __shared__ double sm_d[16];
-    __shared__ int sm_i[SAMPLE_THREADS / 64 + 2];
-    __shared__ double sm_st[DUO_MAX_ROWS + 1][2];
-    const SeqStats st{sm_st};
+// ---- the nucleus of a judging row ------------------------------------------------------------------------------
+// Row r: 0 = the root distribution, 1 + i*k + (j-1) = row (i, j).  Wanted is the last token, in order of decreasing
+// logit and, among equal logits, ascending id, with which the mass reaches top_p * total.
+//
+// Masses are added as whole numbers, p in units of 2^-62: sums of whole numbers do not depend on their order, so LDS
+// atomics give repeatable results, and 128256 roundings of at most 2^-63 leave a sum closer to the exact one than a sum
+// of doubles (1e-17 against 1e-16 as a root mean square).
+//   1. every id goes into one of NUC_BINS bins of equal width in logit / T below the maximum (a monotone map, so the
+//      bins are in order of decreasing probability; the last bin takes everything from e^-42.6 down), and each bin's
+//      mass is added up: large vocabularies by nucleus_hist_kernel, G slices of a row on as many workgroups (the
+//      exponentials are the work: 4.2 million for 33 rows of 128256), small ones inside nucleus_cut_kernel;
+//   2. nucleus_cut_kernel, one workgroup per row: a scan over the bins finds the one in which the cut lies; its ids (a few
+//      hundred of 128256) are collected and, as long as there are more than a wave's worth, divided once more into bins of
+//      equal key range; the last few are ranked by one wave.
+// Measured: 5 rows of 32000 107 -> 26 us, 33 rows of 128256 2587 -> 44 us, against a bitwise search of the threshold key by one
+// workgroup per row (33 sums over the whole row).  What bounds it now: the exponentials of the first kernel and the chain of
+// block-wide steps of the second.
+constexpr int NUC_BINS = 2048;
+constexpr double NUC_BINS_PER_NAT = 48.0;
+constexpr int NUC_LIST = 2048;     // ids of one bin that are held in LDS; more (near-equal logits): passes over the row
+constexpr int NUC_SUB = 1024;      // bins of a refinement
+constexpr int NUC_SMALL_VOCAB = 8192;  // below: nucleus_cut_kernel<true> alone
+constexpr double NUC_ONE = 4611686018427387904.0;  // 2^62
+typedef unsigned long long u64;
+
+struct NucRow {  // what both kernels evaluate a row with (the same expressions: equal masses in both)
+    const float* row;
+    double iT, zmax, iZ;
+    __device__ __forceinline__ double below_max(float x) const { return fma(-(double)x, iT, zmax); }
+    __device__ __forceinline__ u64 mass(double d) const {
+        const double m = fma(exp(-d) * iZ, NUC_ONE, 0.5);
+        return m >= 1.0 ? (u64)m : 0ull;  // NaN: none
+    }
+    __device__ __forceinline__ int bin(double d) const { return (int)fmin(fmax(d * NUC_BINS_PER_NAT, 0.0), (double)(NUC_BINS - 1)); }
+};
+
+// Scratch of the two kernels inside p_rows ([rows][V] doubles): hist [rows][G][NUC_BINS] masses, then the ids' bins
+// [rows][bin_stride].
+struct NucBuf {
+    u64* hist;
+    uint16_t* bins;
+    int G, slice, bin_stride;
+    const double* row_stats;  // merged statistics {zmax, Z} of judging row jr at [2 * (jr + 1)], or nullptr: merge the parts
+};
+
+// wave 0 leaves the row's statistics in sm[0..1]; every thread gets the row's evaluator (contains a barrier)
+__device__ __forceinline__ NucRow nuc_row(const SampleArgs& a, const double* row_stats, int i, int j, double* sm) {
+    const int jr = a.judge_index(i, j);
+    if (threadIdx.x < 64) {
+        double zmax, Z;
+        if (row_stats) {
+            zmax = row_stats[2 * (jr + 1)];
+            Z = row_stats[2 * (jr + 1) + 1];
+        } else {
+            wave_row_stats(a, jr, zmax, Z);
+        }
+        if (threadIdx.x == 0) {
+            sm[0] = zmax;
+            sm[1] = Z;
+        }
+    }
+    __syncthreads();
+    return NucRow{a.judge_row(i, j), 1.0 / a.T, sm[0], 1.0 / sm[1]};
+}
+
+// grid (rows, G)
+__global__ __launch_bounds__(512) void nucleus_hist_kernel(SampleArgs a, NucBuf b) {
+    __shared__ u64 h[NUC_BINS];
+    __shared__ double sm[2];
     const int r = blockIdx.x, tid = threadIdx.x;
     const int i = r == 0 ? 0 : (r - 1) / a.k, j = r == 0 ? 0 : (r - 1) % a.k + 1;
-    const float* row = a.judge_row(i, j);
-    double* prow = prow_all + (size_t)r * a.V;
-    load_seq_stats(a, i, j, j, st);
-    double zmax, Z;
-    merged_stats(st, j, zmax, Z);
-    constexpr int NR = PT > 0 ? PT : 1;
-    uint32_t rk[NR];  // PT > 0: this thread's keys and probabilities, ids tid + e * 1024 (beyond the vocabulary: none)
-    double rp[NR];
-    double loc = 0.0;
-    if (PT > 0) {
-#pragma unroll
-        for (int e = 0; e < NR; ++e) {
-            const int v = tid + e * SAMPLE_THREADS;
-            const bool in = v < a.V;
-            const float x = row[in ? v : 0];
-            const double p = in ? exp((double)x / a.T - zmax) / Z : 0.0;
-            rk[e] = in ? logit_key(x) : 0u;
-            rp[e] = p;
-            if (in) prow[v] = p;
-            loc += p;
-        }
-    } else {
-        for (int v = tid; v < a.V; v += SAMPLE_THREADS) {
-            const double p = exp((double)row[v] / a.T - zmax) / Z;
-            prow[v] = p;
-            loc += p;
-        }
+    for (int e = tid; e < NUC_BINS; e += 512) h[e] = 0ull;
+    const NucRow n = nuc_row(a, b.row_stats, i, j, sm);  // its barrier also orders the zeros
+    const int v0 = min(a.V, (int)blockIdx.y * b.slice), v1 = min(a.V, v0 + b.slice);
+    uint16_t* bins = b.bins + (size_t)r * b.bin_stride;
+#pragma unroll 4
+    for (int v = v0 + tid; v < v1; v += 512) {
+        const double d = n.below_max(n.row[v]);
+        const int bin = n.bin(d);
+        bins[v] = (uint16_t)bin;
+        const u64 m = n.mass(d);
+        if (m) atomicAdd(&h[bin], m);
     }
-    const double target = top_p * block_sum_d(loc, sm_d);  // also orders the prow writes before the reads below
-    auto mass_from = [&](uint32_t t, bool strictly) {  // mass of the keys >= t (or > t); same order of additions either way
-        double s = 0.0;
-        if (PT > 0) {
-#pragma unroll
-            for (int e = 0; e < NR; ++e) s += (strictly ? rk[e] > t : rk[e] >= t) ? rp[e] : 0.0;
-        } else {
-            for (int v = tid; v < a.V; v += SAMPLE_THREADS) {
-                const uint32_t kx = logit_key(row[v]);
-                s += (strictly ? kx > t : kx >= t) ? prow[v] : 0.0;
-            }
-        }
-        return block_sum_d(s, sm_d);
-    };
-    uint32_t cur = 0u;
-    for (int b = 31; b >= 0; --b) {
-        const uint32_t t = cur | (1u << b);
-        if (mass_from(t, false) >= target) cur = t;  // same value in every thread
-    }
-    const double above = mass_from(cur, true);
-    // the ids on the threshold share one probability; ids in ascending order: contiguous ranges per thread
-    const int per = (a.V + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
-    const int v0 = min(a.V, tid * per), v1 = min(a.V, v0 + per);
-    int cnt = 0;
-    double pstar = 0.0;
-    for (int v = v0; v < v1; ++v)
-        if (logit_key(row[v]) == cur) {
-            ++cnt;
-            pstar = prow[v];
-        }
-    pstar = block_max_d(pstar, sm_d);
-    int need = (int)ceil((target - above) / pstar);
-    need = need < 1 ? 1 : need;
-    while (need > 1 && above + (double)(need - 1) * pstar >= target) --need;
-    while (above + (double)need * pstar < target) ++need;
-    // exclusive scan of the per-thread counts (lanes, then waves in index order)
-    const int lane = tid & 63, wave = tid >> 6;
-    int incl = cnt;
+    __syncthreads();
+    u64* out = b.hist + ((size_t)r * b.G + blockIdx.y) * NUC_BINS;
+    for (int e = tid; e < NUC_BINS; e += 512) out[e] = h[e];
+}
+
+// Inclusive sum of v over the threads of a 1024-thread workgroup in thread order; `total` gets the sum of all.
+__device__ __forceinline__ u64 block_scan_u64(u64 v, u64* sm, u64& total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += y;
+        const u64 y = __shfl_up(v, o, 64);
+        if (lane >= o) v += y;
     }
     __syncthreads();
-    if (lane == 63) sm_i[wave] = incl;
-    if (tid == 0) sm_i[SAMPLE_THREADS / 64] = a.V - 1;
+    if (lane == 63) sm[wave] = v;
     __syncthreads();
-    int before = incl - cnt, total_ties = 0;
+    total = 0ull;
+    u64 before = 0ull;
+#pragma unroll
     for (int w = 0; w < SAMPLE_THREADS / 64; ++w) {
-        if (w < wave) before += sm_i[w];
-        total_ties += sm_i[w];
+        if (w < wave) before += sm[w];
+        total += sm[w];
     }
-    need = need > total_ties ? total_ties : need;  // rounding asked for more than there are: all of them
-    if (cnt > 0 && before < need && need <= before + cnt) {  // the need-th tied id lies in this thread's range
-        int seen = before;
-        for (int v = v0; v < v1; ++v)
-            if (logit_key(row[v]) == cur && ++seen == need) sm_i[SAMPLE_THREADS / 64] = v;
+    return before + v;
+}
+
+// One workgroup per row.  FUSED: the bins of step 1 are filled here (V < NUC_SMALL_VOCAB), otherwise nucleus_hist_kernel
+// has filled them.  nuc_out[r] = {threshold key, last admitted id among the keys equal to it, kept mass, 0}.
+template <bool FUSED>
+__global__ __launch_bounds__(SAMPLE_THREADS) void nucleus_cut_kernel(SampleArgs a, double top_p, NucBuf b, double* __restrict__ nuc_out) {
+    __shared__ __align__(16) u64 h[NUC_BINS];   // also the refinements' masses [NUC_SUB] and counts
+    __shared__ __align__(16) u64 list_c[NUC_LIST], list_m[NUC_LIST];  // (key, complement of the id) and mass of the collected ids
+    __shared__ __align__(16) uint16_t own_bins[FUSED ? NUC_SMALL_VOCAB : 8];
+    __shared__ u64 sm_w[SAMPLE_THREADS / 64], sm_before;
+    __shared__ double sm[2];
+    __shared__ int sm_bin, sm_count;
+    __shared__ uint32_t sm_lo, sm_hi;
+    const int r = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = r == 0 ? 0 : (r - 1) / a.k, j = r == 0 ? 0 : (r - 1) % a.k + 1;
+    if (tid == 0) {
+        sm_bin = -1;
+        sm_before = 0ull;
+        sm_count = 0;
+    }
+    if (FUSED)
+        for (int e = tid; e < NUC_BINS; e += SAMPLE_THREADS) h[e] = 0ull;
+    const NucRow n = nuc_row(a, b.row_stats, i, j, sm);
+    u64 m0 = 0ull, m1 = 0ull;  // masses of bins 2*tid, 2*tid + 1
+    static_assert(NUC_BINS == 2 * SAMPLE_THREADS, "two bins per thread");
+    if (FUSED) {
+        for (int v = tid; v < a.V; v += SAMPLE_THREADS) {
+            const double d = n.below_max(n.row[v]);
+            const int bin = n.bin(d);
+            own_bins[v] = (uint16_t)bin;
+            const u64 m = n.mass(d);
+            if (m) atomicAdd(&h[bin], m);
+        }
+        __syncthreads();
+        m0 = h[2 * tid];
+        m1 = h[2 * tid + 1];
+    } else {
+        const u64* hist = b.hist + (size_t)r * b.G * NUC_BINS + 2 * tid;
+#pragma unroll 8
+        for (int g = 0; g < b.G; ++g) {
+            m0 += hist[(size_t)g * NUC_BINS];
+            m1 += hist[(size_t)g * NUC_BINS + 1];
+        }
+    }
+    u64 total;
+    const u64 incl = block_scan_u64(m0 + m1, sm_w, total);
+    // whole-number masses reach top_p * total exactly when they reach its ceiling (at least one token is kept)
+    const double tgt = ceil(top_p * (double)total);
+    const u64 target = tgt >= 1.0 ? (u64)tgt : 1ull;
+    {
+        const u64 before = incl - m0 - m1;
+        if (before < target && target <= before + m0) {
+            sm_bin = 2 * tid;
+            sm_before = before;
+        } else if (before + m0 < target && target <= incl) {
+            sm_bin = 2 * tid + 1;
+            sm_before = before + m0;
+        }
     }
     __syncthreads();
-    if (tid == 0) {
-        double* e = nuc_out + (size_t)r * 4;
-        e[0] = (double)cur;
-        e[1] = (double)sm_i[SAMPLE_THREADS / 64];
-        e[2] = above + (double)need * pstar;
-        e[3] = (double)need;
+    const int bin = sm_bin;
+    double* e = nuc_out + (size_t)r * 4;
+    if (bin < 0) {  // no mass at all (not-a-number or infinite logits): nothing is restricted
+        if (tid == 0) {
+            e[0] = 0.0;
+            e[1] = (double)(a.V - 1);
+            e[2] = 1.0;
+            e[3] = 0.0;
+        }
+        return;
+    }
+    // Calls f(first id of eight, mask of those that lie in the bin) wherever there are any.  Every thread visits its own ids;
+    // the loop has no barriers.
+    const uint16_t* bins = b.bins + (size_t)r * b.bin_stride;
+    auto eights_of_bin = [&](auto f) {
+        const int eights = (a.V + 7) >> 3;  // bin_stride covers whole eights; ids past the vocabulary are masked out
+#pragma unroll 4
+        for (int c = tid; c < eights; c += SAMPLE_THREADS) {
+            const u32x4 w = FUSED ? *reinterpret_cast<const u32x4*>(own_bins + c * 8) : *reinterpret_cast<const u32x4*>(bins + (size_t)c * 8);
+            uint32_t hit = 0u;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) hit |= (uint32_t)((int)((w[q >> 1] >> (16 * (q & 1))) & 0xffffu) == bin && c * 8 + q < a.V) << q;
+            if (hit) f(c * 8, hit);
+        }
+    };
+    auto each_of_bin = [&](auto f) {
+        eights_of_bin([&](int v0, uint32_t hit) {
+            for (; hit; hit &= hit - 1u) f(v0 + __ffs(hit) - 1);
+        });
+    };
+    // First the ids alone (a load behind every hit would be a trip to memory for every wave and position), then, a thread per
+    // id, their keys and masses.
+    eights_of_bin([&](int v0, uint32_t hit) {
+        int at = atomicAdd(&sm_count, __popc(hit));
+        for (; hit; hit &= hit - 1u, ++at)
+            if (at < NUC_LIST) list_c[at] = (u64)(v0 + __ffs(hit) - 1);
+    });
+    __syncthreads();
+    for (int q = tid; q < min(sm_count, NUC_LIST); q += SAMPLE_THREADS) {
+        const int v = (int)list_c[q];
+        const float x = n.row[v];
+        list_c[q] = ((u64)logit_key(x) << 32) | (uint32_t)~v;
+        list_m[q] = n.mass(n.below_max(x));
+    }
+    __syncthreads();
+    int count = sm_count;
+    bool listed = count <= NUC_LIST;
+    uint32_t klo = 0u, khi = 0xffffffffu;  // the ids still in question: those of the bin with klo <= key <= khi
+    // Calls f(key, id, mass) for every id still in question.
+    auto each_left = [&](auto f) {
+        if (listed) {
+            for (int q = tid; q < count; q += SAMPLE_THREADS) {
+                const uint32_t key = (uint32_t)(list_c[q] >> 32);
+                if (key >= klo && key <= khi) f(key, (int)~(uint32_t)list_c[q], list_m[q]);
+            }
+        } else {
+            each_of_bin([&](int v) {
+                const float x = n.row[v];
+                const uint32_t key = logit_key(x);
+                if (key >= klo && key <= khi) f(key, v, n.mass(n.below_max(x)));
+            });
+        }
+    };
+    u64* sub_m = h;
+    uint32_t* sub_n = reinterpret_cast<uint32_t*>(h + NUC_SUB);
+    int left = count;
+    while (left > 64) {
+        if (tid == 0) {
+            sm_lo = 0xffffffffu;
+            sm_hi = 0u;
+        }
+        sub_m[tid] = 0ull;
+        sub_n[tid] = 0u;
+        __syncthreads();
+        uint32_t lo = 0xffffffffu, hi = 0u;
+        each_left([&](uint32_t key, int, u64) {
+            lo = min(lo, key);
+            hi = max(hi, key);
+        });
+        if (lo <= hi) {
+            atomicMin(&sm_lo, lo);
+            atomicMax(&sm_hi, hi);
+        }
+        __syncthreads();
+        klo = sm_lo;
+        khi = sm_hi;
+        if (klo == khi) break;  // equal logits only: the ids decide
+        int sh = 0;
+        while (((khi - klo) >> sh) >= (uint32_t)NUC_SUB) ++sh;
+        each_left([&](uint32_t key, int, u64 m) {
+            const int q = (int)((khi - key) >> sh);  // 0: the largest keys
+            if (m) atomicAdd(&sub_m[q], m);
+            atomicAdd(&sub_n[q], 1u);
+        });
+        const u64 before0 = sm_before;
+        __syncthreads();
+        static_assert(NUC_SUB == SAMPLE_THREADS, "one refinement bin per thread");
+        u64 sub_total;
+        const u64 m = sub_m[tid];
+        const u64 in = block_scan_u64(m, sm_w, sub_total);
+        if (tid == 0) sm_bin = -1;
+        __syncthreads();
+        if (before0 + in - m < target && target <= before0 + in) {
+            sm_bin = tid;
+            sm_before = before0 + in - m;
+        }
+        __syncthreads();
+        if (sm_bin < 0) {  // cannot happen while both passes add the same masses; the smallest key then, and the loop ends
+            khi = klo;
+            break;
+        }
+        const uint32_t top = khi;
+        khi = top - ((uint32_t)sm_bin << sh);
+        klo = max(klo, (uint32_t)(khi - ((1u << sh) - 1u) > khi ? 0u : khi - ((1u << sh) - 1u)));
+        left = (int)sub_n[sm_bin];
+        __syncthreads();
+    }
+    const u64 before = sm_before;
+    if (left > 64) {
+        // equal logits, one key: as many of its ids, ascending, as the target still needs; contiguous ranges per thread
+        const int per = (a.V + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
+        const int v0 = min(a.V, tid * per), v1 = min(a.V, v0 + per);
+        u64 cnt = 0ull, m = 0ull;
+        for (int v = v0; v < v1; ++v)
+            if (logit_key(n.row[v]) == klo) {
+                ++cnt;
+                m = n.mass(n.below_max(n.row[v]));
+            }
+        u64 ties;
+        const u64 upto = block_scan_u64(cnt, sm_w, ties);
+        if (cnt) list_m[0] = m;  // every writer has the same value
+        __syncthreads();
+        m = list_m[0];
+        u64 need = m ? (target - before + m - 1) / m : 1ull;
+        need = need > ties ? ties : (need < 1ull ? 1ull : need);
+        if (cnt && upto - cnt < need && need <= upto) {  // the need-th of them lies in this thread's range
+            u64 seen = upto - cnt;
+            for (int v = v0; v < v1; ++v)
+                if (logit_key(n.row[v]) == klo && ++seen == need) {
+                    e[0] = (double)klo;
+                    e[1] = (double)v;
+                    e[2] = (double)(before + need * m) / NUC_ONE;
+                    e[3] = 0.0;
+                }
+        }
+        return;
+    }
+    // at most 64 ids: to the front of the list (in registers meanwhile), then one wave ranks them
+    __syncthreads();
+    if (tid == 0) sm_count = 0;
+    __syncthreads();
+    u64* fin_c = h;
+    u64* fin_m = h + 64;
+    each_left([&](uint32_t key, int v, u64 m) {
+        const int at = atomicAdd(&sm_count, 1);
+        if (at < 64) {
+            fin_c[at] = ((u64)key << 32) | (uint32_t)~v;
+            fin_m[at] = m;
+        }
+    });
+    __syncthreads();
+    if (wave != 0) return;
+    const int nf = min(sm_count, 64);
+    const u64 c = lane < nf ? fin_c[lane] : 0ull, m = lane < nf ? fin_m[lane] : 0ull;
+    u64 front = before;
+    bool last = true;  // no id behind this one is still short of the target
+    for (int q = 0; q < nf; ++q) {
+        const u64 cq = fin_c[q];
+        front += cq > c ? fin_m[q] : 0ull;
+    }
+    const bool in = lane < nf && front < target;  // the admitted ones
+    for (int q = 0; q < nf; ++q)
+        if (__shfl((int)in, q, 64) && fin_c[q] < c) last = false;
+    if (in && last) {
+        e[0] = (double)(uint32_t)(c >> 32);
+        e[1] = (double)(int)~(uint32_t)c;
+        e[2] = (double)(front + m) / NUC_ONE;
+        e[3] = 0.0;
     }
 }
 
@@ -543,7 +834,9 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_finish_kernel(SampleArg
 //                             added in index order), the id inside it, the commit record of a single sequence
 // Their scratch (SpreadBuf) lies in p_run, which this rule does not use otherwise.
 struct SpreadBuf {
-    double* row_stats;  // [R + n*k + 1][2], row judge_index + 1
+    // [R + n*k + 1][2], row judge_index + 1: written by sample_row_stats_kernel behind an LM head (vocab / 32 parts per
+    // row); nullptr when the caller's logits were the input (STATS_SPLIT parts: the kernels merge the rows they need)
+    double* row_stats;
     double* sums;       // [n][chunks][2]: correction weights, target probabilities
     int32_t* last;      // [n][chunks][2]
     int G, chunk;       // slices per sequence; ids per wave chunk (a multiple of 64); chunks = 16 * G
@@ -553,7 +846,7 @@ constexpr int SPREAD_MIN_VOCAB = 8192;   // below: sample_finish_kernel
 constexpr int SPREAD_MAX_GROUPS = 128;   // n * G at most: the records fit SPREAD_MIN_VOCAB doubles
 constexpr int SPREAD_MAX_SLICES = 32;
 
-__global__ __launch_bounds__(256) void sample_row_stats_kernel(SampleArgs a, SpreadBuf b) {
+__global__ __launch_bounds__(256) void sample_row_stats_kernel(SampleArgs a, double* __restrict__ row_stats) {
     __shared__ double sm[16];
     const int jr = (int)blockIdx.x - 1;
     if (jr < 0 && a.R) return;  // a root row judges the first tokens: the cached root logits are not in play
@@ -612,8 +905,18 @@ __global__ __launch_bounds__(256) void sample_row_stats_kernel(SampleArgs a, Spr
         Z = block_sum_d(sum, sm);
     }
     if (threadIdx.x == 0) {
-        b.row_stats[2 * blockIdx.x] = mx;
-        b.row_stats[2 * blockIdx.x + 1] = Z;
+        row_stats[2 * blockIdx.x] = mx;
+        row_stats[2 * blockIdx.x + 1] = Z;
+    }
+}
+
+// statistics of one judging row for one wave: the merged ones, or the parts merged here
+__device__ __forceinline__ void row_stats_of(const SampleArgs& a, const double* row_stats, int jr, double& zmax, double& Z) {
+    if (row_stats) {
+        zmax = row_stats[2 * (jr + 1)];
+        Z = row_stats[2 * (jr + 1) + 1];
+    } else {
+        wave_row_stats(a, jr, zmax, Z);
     }
 }
 
@@ -642,45 +945,22 @@ struct TokenWeights {
     __device__ __forceinline__ double r(double pv, int v) const { return fmax(pv - (double)qrow[v], 0.0); }
 };
 
-template <bool NUC>
-__global__ __launch_bounds__(SAMPLE_THREADS) void sample_spread_kernel(SampleArgs a, SpreadBuf b) {
-    __shared__ double sm_st[DUO_MAX_ROWS + 1][2];
-    __shared__ int sm_acc[DUO_MAX_ROWS];
-    const SeqStats st{sm_st};
-    const int i = blockIdx.x, g = blockIdx.y;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    if (tid <= a.k) {
-        const double* rs = b.row_stats + 2 * (a.judge_index(i, tid) + 1);
-        sm_st[tid][0] = rs[0];
-        sm_st[tid][1] = rs[1];
-    }
-    __syncthreads();
-    if (tid < a.k) sm_acc[tid] = accept_flag<NUC>(a, st, i, tid);
-    __syncthreads();
-    int acc_len = 0;
-    while (acc_len < a.k && sm_acc[acc_len]) ++acc_len;
-    if (g == 0 && tid == 0) a.accept_len[i] = acc_len;
-    const TokenWeights<NUC> w(a, i, acc_len, sm_st[acc_len][0], sm_st[acc_len][1]);
-    const int c = g * 16 + wave;
-    const int c0 = min(a.V, c * b.chunk), c1 = min(a.V, c0 + b.chunk);
+// One wave: the sums of both kinds of weights, f(v, p, r) with p the target probability and r the correction weight, over
+// wave chunk c of the vocabulary, and the last id of positive weight of each (-1: none): sums = {r, p}, last = {r, p}.
+template <class F>
+__device__ __forceinline__ void wave_chunk_sums(F f, int V, int c, int chunk, double* sums, int32_t* last) {
+    const int lane = threadIdx.x & 63;
+    const int c0 = min(V, c * chunk), c1 = min(V, c0 + chunk);
     double sum_r = 0.0, sum_p = 0.0;
     int last_r = -1, last_p = -1;
-    if (w.qrow) {
 #pragma unroll 4
-        for (int v = c0 + lane; v < c1; v += 64) {
-            const double pv = w.p(v), rv = w.r(pv, v);
-            sum_p += pv;
-            sum_r += rv;
-            if (pv > 0.0) last_p = v;
-            if (rv > 0.0) last_r = v;
-        }
-    } else {
-#pragma unroll 4
-        for (int v = c0 + lane; v < c1; v += 64) {
-            const double pv = w.p(v);
-            sum_p += pv;
-            if (pv > 0.0) last_p = v;
-        }
+    for (int v = c0 + lane; v < c1; v += 64) {
+        double pv, rv;
+        f(v, pv, rv);
+        sum_p += pv;
+        sum_r += rv;
+        if (pv > 0.0) last_p = v;
+        if (rv > 0.0) last_r = v;
     }
     sum_r = wave_sum(sum_r);
     sum_p = wave_sum(sum_p);
@@ -690,12 +970,40 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_spread_kernel(SampleArg
         last_p = max(last_p, __shfl_xor(last_p, o, 64));
     }
     if (lane == 0) {
-        const size_t e = ((size_t)i * b.chunks() + c) * 2;
-        b.sums[e] = sum_r;
-        b.sums[e + 1] = sum_p;
-        b.last[e] = last_r;
-        b.last[e + 1] = last_p;
+        sums[0] = sum_r;
+        sums[1] = sum_p;
+        last[0] = last_r;
+        last[1] = last_p;
     }
+}
+
+template <bool NUC>
+__global__ __launch_bounds__(SAMPLE_THREADS) void sample_spread_kernel(SampleArgs a, SpreadBuf b) {
+    __shared__ double sm_st[DUO_MAX_ROWS + 1][2];
+    __shared__ int sm_acc[DUO_MAX_ROWS];
+    const SeqStats st{sm_st};
+    const int i = blockIdx.x, g = blockIdx.y;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    if (b.row_stats) {
+        if (tid <= a.k) {
+            const double* rs = b.row_stats + 2 * (a.judge_index(i, tid) + 1);
+            sm_st[tid][0] = rs[0];
+            sm_st[tid][1] = rs[1];
+        }
+        __syncthreads();
+    } else {
+        load_seq_stats(a, i, 0, a.k, st);
+    }
+    if (tid < a.k) sm_acc[tid] = accept_flag<NUC>(a, st, i, tid);
+    __syncthreads();
+    int acc_len = 0;
+    while (acc_len < a.k && sm_acc[acc_len]) ++acc_len;
+    if (g == 0 && tid == 0) a.accept_len[i] = acc_len;
+    const TokenWeights<NUC> w(a, i, acc_len, sm_st[acc_len][0], sm_st[acc_len][1]);
+    const int c = g * 16 + wave;
+    const size_t e = ((size_t)i * b.chunks() + c) * 2;
+    if (w.qrow) wave_chunk_sums([&](int v, double& p, double& r) { p = w.p(v); r = w.r(p, v); }, a.V, c, b.chunk, b.sums + e, b.last + e);
+    else wave_chunk_sums([&](int v, double& p, double& r) { p = w.p(v); r = 0.0; }, a.V, c, b.chunk, b.sums + e, b.last + e);
 }
 
 // One wave.  Inverse CDF over the weights whose chunk sums (x[g]: chunk 64 * g + lane, zero beyond the last chunk) and
@@ -803,8 +1111,9 @@ __global__ __launch_bounds__(64) void sample_locate_kernel(SampleArgs a, SpreadB
         }
     }
     const int acc_len = a.accept_len[i];
-    const double* rs = b.row_stats + 2 * (a.judge_index(i, acc_len) + 1);
-    const TokenWeights<NUC> w(a, i, acc_len, rs[0], rs[1]);
+    double row_zmax, row_Z;
+    row_stats_of(a, b.row_stats, a.judge_index(i, acc_len), row_zmax, row_Z);
+    const TokenWeights<NUC> w(a, i, acc_len, row_zmax, row_Z);
     const double u = (double)a.u[i * (a.k + 1) + a.k];
     int tok = -1;
     if (w.qrow) {
@@ -937,6 +1246,312 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_deferred_kernel(SampleA
             a.commit[2] = tok;
             a.commit[3] = a.P + a.R + acc_len;
             if (d.prefix_len) *d.prefix_len = a.P + a.R + acc_len;
+        }
+    }
+}
+
+// ---- the sequential first-token rule for large vocabularies, spread over the chip --------------------------------
+// sample_paper_kernel and sample_deferred_kernel are one workgroup, whose compute unit evaluates the vocabulary's
+// double-precision exponentials and makes two passes over it per rejected candidate (128256 entries, four candidates:
+// 395 us behind an LM head).  Here candidate i is judged by launch i (seq_stage_kernel) on G workgroups, each a slice of the
+// vocabulary.  Every workgroup takes the decision for itself, from the same numbers; on a rejection it adds up its slice
+// of the residual max(0, p_i - q_i), whose total the next launch needs for p_{i+1} = residual / total.  The running
+// distribution itself is kept nowhere: an entry of p_i is evaluated from the logit, the draft distributions rejected so far and
+// their totals, which for a handful of candidates is less work than a pass through memory.  Launches behind the decision
+// return at once but cost 3 us each all the same, so there are at most b.stages of them, one per 8192 entries of the
+// vocabulary, three at least and no more than SEQ_STAGES, and seq_tail_kernel, one workgroup with the running distribution in memory, judges the
+// candidates beyond.  seq_locate_kernel draws the token from the sums of the launch that
+// decided and writes the results.
+struct SeqArgs {
+    const int32_t* tok;  // candidate i: first token tok[i * tok_stride], draft distribution q + i * q_stride, uniform u[i * u_stride]
+    int tok_stride;
+    const float* q;
+    size_t q_stride;
+    const float* u;
+    int u_stride;
+    int s;
+    int deferred;         // 0: the candidates are the call's n sequences; 1: Alg. 2 as listed (see DeferredArgs)
+    int32_t* prefix_len;  // device prefix length (may be NULL); advanced here in the deferred form, by commit_kernel otherwise
+};
+constexpr int SEQ_MIN_VOCAB = 12288;  // below: sample_paper_kernel, sample_deferred_kernel
+constexpr int SEQ_STAGES = 8;
+
+struct SeqBuf {
+    double* row_stats;  // merged statistics, or nullptr (see SpreadBuf)
+    double* inv_total;  // [SEQ_STAGES] 1 / total of candidate i's residual; 0: the residual vanished, p_i stays
+    int32_t* rec;       // [SEQ_STAGES + 1][8] what is known after launch i: {kind, selected, accepted length, launch, token}
+    double* sums;       // [2][chunks][2] by launch parity: chunk sums as in SpreadBuf
+    int32_t* last;      // [2][chunks][2]
+    int G, chunk;
+    int stages;         // launches of seq_stage_kernel when there are more candidates than that
+    __host__ __device__ int chunks() const { return 16 * G; }
+};
+constexpr int SEQ_OPEN = 0;   // every candidate so far was rejected
+constexpr int SEQ_DRAW = 1;   // the token is drawn from the sums of TokenWeights(selected or 0, accepted length)
+constexpr int SEQ_TAKEN = 2;  // deferred: a candidate was accepted, no token
+constexpr int SEQ_DONE = 3;   // the tail drew the token
+
+// p_m(v) after the rejection of candidates 0 .. m-1
+template <bool NUC>
+struct ChainWeights {
+    const TokenWeights<NUC>& base;
+    const SeqArgs& d;
+    const double* inv_total;
+    int m;
+    __device__ __forceinline__ double p(int v) const {
+        double x = base.p(v);
+        for (int i = 0; i < m; ++i) {
+            const double c = inv_total[i];
+            if (c > 0.0) x = fmax(x - (double)d.q[(size_t)i * d.q_stride + v], 0.0) * c;
+        }
+        return x;
+    }
+};
+
+// total of a launch's residual chunk sums, by one wave in a fixed order -> its reciprocal, 0 where there is none
+__device__ __forceinline__ double seq_inv_total(const SeqBuf& b, int launch) {
+    const double* sums = b.sums + (size_t)(launch & 1) * b.chunks() * 2;
+    double t = 0.0;
+    for (int c = threadIdx.x & 63; c < b.chunks(); c += 64) t += sums[2 * c];
+    t = wave_sum(t);
+    return t > 0.0 ? 1.0 / t : 0.0;
+}
+__device__ __forceinline__ void seq_record(int32_t* rec, int kind, int sel, int acc_len, int launch, int tok) {
+    rec[0] = kind;
+    rec[1] = sel;
+    rec[2] = acc_len;
+    rec[3] = launch;
+    rec[4] = tok;
+}
+__device__ __forceinline__ int first_token(const SeqArgs& d, int i, int V) {
+    const int t = d.tok[i * d.tok_stride];
+    return t < 0 ? 0 : (t >= V ? V - 1 : t);
+}
+
+// Rows j0 .. j1 of sequence i in st, then the leading accepts from position j0 on (same value in every thread).
+template <bool NUC>
+__device__ __forceinline__ int seq_accepts(const SampleArgs& a, const double* row_stats, int i, int j0, const SeqStats& st, int* sm_acc) {
+    const int tid = threadIdx.x;
+    if (row_stats) {
+        if (tid >= j0 && tid <= a.k) {
+            const double* rs = row_stats + 2 * (a.judge_index(i, tid) + 1);
+            st.t[tid][0] = rs[0];
+            st.t[tid][1] = rs[1];
+        }
+        __syncthreads();
+    } else {
+        load_seq_stats(a, i, j0, a.k, st);
+    }
+    if (tid >= j0 && tid < a.k) sm_acc[tid] = accept_flag<NUC>(a, st, i, tid);
+    __syncthreads();
+    int n = j0;
+    while (n < a.k && sm_acc[n]) ++n;
+    return n;
+}
+
+// grid (G): launch number `stage`, 0 .. min(candidates, b.stages) - 1 (deferred without candidates: launch 0 alone)
+template <bool NUC>
+__global__ __launch_bounds__(SAMPLE_THREADS) void seq_stage_kernel(SampleArgs a, SeqArgs d, SeqBuf b, int stage) {
+    __shared__ double sm_st[DUO_MAX_ROWS + 1][2];
+    __shared__ int sm_acc[DUO_MAX_ROWS];
+    __shared__ double sm_inv[SEQ_STAGES], sm_row[2];
+    const SeqStats st{sm_st};
+    const int g = blockIdx.x, tid = threadIdx.x, wave = tid >> 6;
+    const bool lead = g == 0 && tid == 0;
+    int32_t* rec = b.rec + stage * 8;
+    if (stage > 0) {
+        const int32_t* prev = rec - 8;
+        if (prev[0] != SEQ_OPEN) {  // same value in every thread of every workgroup
+            if (lead) seq_record(rec, prev[0], prev[1], prev[2], prev[3], prev[4]);
+            return;
+        }
+    } else if (d.deferred && g == 0 && tid < d.s && a.status) {
+        const int t = d.tok[tid * d.tok_stride];
+        if (t < 0 || t >= a.V) atomicOr(a.status, 1);
+    }
+    const int c = g * 16 + wave;
+    const size_t e = ((size_t)(stage & 1) * b.chunks() + c) * 2;
+    auto token_sums = [&](const TokenWeights<NUC>& w) {
+        if (w.qrow) wave_chunk_sums([&](int v, double& p, double& r) { p = w.p(v); r = w.r(p, v); }, a.V, c, b.chunk, b.sums + e, b.last + e);
+        else wave_chunk_sums([&](int v, double& p, double& r) { p = w.p(v); r = 0.0; }, a.V, c, b.chunk, b.sums + e, b.last + e);
+    };
+    if (d.deferred && stage == 0) {  // the unverified suffix comes first
+        const int acc_len = seq_accepts<NUC>(a, b.row_stats, 0, 0, st, sm_acc);
+        if (acc_len < a.k) {
+            token_sums(TokenWeights<NUC>(a, 0, acc_len, sm_st[acc_len][0], sm_st[acc_len][1]));
+            if (lead) seq_record(rec, SEQ_DRAW, -1, acc_len, stage, -1);
+            return;
+        }
+    }
+    const int jj = d.deferred ? a.k : 0;  // the row that judges the candidates
+    if (wave == 0) {
+        double zmax, Z;
+        row_stats_of(a, b.row_stats, a.judge_index(0, jj), zmax, Z);
+        if (tid == 0) {
+            sm_row[0] = zmax;
+            sm_row[1] = Z;
+        }
+    } else if (wave == 1 && stage > 0) {
+        const double inv = seq_inv_total(b, stage - 1);
+        if ((tid & 63) == 0) {
+            sm_inv[stage - 1] = inv;
+            if (g == 0) b.inv_total[stage - 1] = inv;
+        }
+    } else if (wave == 2 && (tid & 63) < stage - 1) {
+        sm_inv[tid & 63] = b.inv_total[tid & 63];
+    }
+    __syncthreads();
+    const TokenWeights<NUC> base(a, 0, jj, sm_row[0], sm_row[1]);
+    const ChainWeights<NUC> w{base, d, sm_inv, stage};
+    if (stage >= d.s) {  // no candidates at all (deferred): the token is drawn from the judging distribution
+        wave_chunk_sums([&](int v, double& p, double& r) { p = w.p(v); r = 0.0; }, a.V, c, b.chunk, b.sums + e, b.last + e);
+        if (lead) seq_record(rec, SEQ_OPEN, -1, jj, stage, -1);
+        return;
+    }
+    const float* qrow = d.q + (size_t)stage * d.q_stride;
+    const int t = first_token(d, stage, a.V);
+    if ((double)d.u[stage * d.u_stride] * (double)qrow[t] < w.p(t)) {  // accepted; same outcome in every thread
+        if (d.deferred) {
+            if (lead) seq_record(rec, SEQ_TAKEN, stage, jj, stage, -1);
+            return;
+        }
+        const int acc_len = seq_accepts<NUC>(a, b.row_stats, stage, 1, st, sm_acc);
+        token_sums(TokenWeights<NUC>(a, stage, acc_len, sm_st[acc_len][0], sm_st[acc_len][1]));
+        if (lead) seq_record(rec, SEQ_DRAW, stage, acc_len, stage, -1);
+        return;
+    }
+    wave_chunk_sums([&](int v, double& p, double& r) { p = w.p(v); r = fmax(p - (double)qrow[v], 0.0); }, a.V, c, b.chunk, b.sums + e,
+                    b.last + e);
+    if (lead) seq_record(rec, SEQ_OPEN, -1, jj, stage, -1);
+}
+
+// More than b.stages candidates, none of the first b.stages accepted: the others one by one, the running distribution in
+// p_run.  One workgroup.  The launches' scratch lies in p_run too: what is needed of it is read first, and the record of the
+// outcome is written when the running distribution has served.
+template <bool NUC>
+__global__ __launch_bounds__(SAMPLE_THREADS) void seq_tail_kernel(SampleArgs a, SeqArgs d, SeqBuf b) {
+    __shared__ double sm_d[16];
+    __shared__ int sm_i[4 + 16];
+    __shared__ double sm_st[DUO_MAX_ROWS + 1][2], sm_all[DUO_MAX_ROWS + 2][2];
+    __shared__ double sm_inv[SEQ_STAGES], sm_row[2];
+    const SeqStats st{sm_st};
+    const int tid = threadIdx.x, wave = tid >> 6;
+    int32_t* rec = b.rec + b.stages * 8;
+    const int32_t* prev = rec - 8;
+    if (prev[0] != SEQ_OPEN) {
+        if (tid == 0) seq_record(rec, prev[0], prev[1], prev[2], prev[3], prev[4]);
+        return;
+    }
+    const int jj = d.deferred ? a.k : 0;
+    if (wave == 0) {
+        double zmax, Z;
+        row_stats_of(a, b.row_stats, a.judge_index(0, jj), zmax, Z);
+        if (tid == 0) {
+            sm_row[0] = zmax;
+            sm_row[1] = Z;
+        }
+    } else if (wave == 1) {
+        const double inv = seq_inv_total(b, b.stages - 1);
+        if ((tid & 63) == 0) sm_inv[b.stages - 1] = inv;
+    } else if (wave == 2 && (tid & 63) < b.stages - 1) {
+        sm_inv[tid & 63] = b.inv_total[tid & 63];
+    }
+    if (b.row_stats && tid <= a.R + a.n * a.k) {
+        sm_all[tid][0] = b.row_stats[2 * tid];
+        sm_all[tid][1] = b.row_stats[2 * tid + 1];
+    }
+    __syncthreads();
+    {
+        const TokenWeights<NUC> base(a, 0, jj, sm_row[0], sm_row[1]);
+        const ChainWeights<NUC> w{base, d, sm_inv, b.stages};
+        for (int v = tid; v < a.V; v += SAMPLE_THREADS) a.p_run[v] = w.p(v);
+    }
+    __syncthreads();
+    int sel = sequential_first_tokens(a.p_run, a.V, d.s - b.stages, d.tok + b.stages * d.tok_stride, d.tok_stride,
+                                      d.q + (size_t)b.stages * d.q_stride, d.q_stride, d.u + b.stages * d.u_stride, d.u_stride, sm_d);
+    int acc_len = jj, tok = -1;
+    if (sel < 0) {
+        const double* pr = a.p_run;
+        auto pw = [=](int v) { return pr[v]; };
+        tok = block_inverse_cdf(pw, a.V, (double)a.u[(a.n - 1) * (a.k + 1) + a.k], sm_d, sm_i);
+    } else {
+        sel += b.stages;
+        if (!d.deferred) {
+            if (b.row_stats) {
+                if (tid >= 1 && tid <= a.k) {
+                    sm_st[tid][0] = sm_all[a.judge_index(sel, tid) + 1][0];
+                    sm_st[tid][1] = sm_all[a.judge_index(sel, tid) + 1][1];
+                }
+                __syncthreads();
+            } else {
+                load_seq_stats(a, sel, 1, a.k, st);
+            }
+            accept_flags<NUC>(a, st, sel, 1);
+            acc_len = leading_accepts(a, sel, 1);
+            tok = finish_token<NUC>(a, st, sel, acc_len, sm_d, sm_i);
+        }
+    }
+    __syncthreads();  // nobody reads the running distribution any more
+    if (tid == 0) seq_record(rec, SEQ_DONE, sel, acc_len, b.stages, tok);
+}
+
+// One wave.  `rec`: the record of the last launch (or the tail's); launches: stage launches made.
+template <bool NUC>
+__global__ __launch_bounds__(64) void seq_locate_kernel(SampleArgs a, SeqArgs d, SeqBuf b, const int32_t* rec, int launches) {
+    const int lane = threadIdx.x;
+    const int kind = rec[0], sel = rec[1], acc_len = rec[2], launch = rec[3];
+    int tok = rec[4];
+    if (kind == SEQ_OPEN || kind == SEQ_DRAW) {
+        const double* sums = b.sums + (size_t)(launch & 1) * b.chunks() * 2;
+        const int32_t* last = b.last + (size_t)(launch & 1) * b.chunks() * 2;
+        double xr[SPREAD_GROUPS64], xp[SPREAD_GROUPS64];
+        int lr[SPREAD_GROUPS64], lq[SPREAD_GROUPS64];
+#pragma unroll
+        for (int g = 0; g < SPREAD_GROUPS64; ++g) {
+            const int c = g * 64 + lane;
+            const bool in = c < b.chunks();
+            const int cc = in ? c : 0;
+            xr[g] = in ? sums[cc * 2] : 0.0;
+            xp[g] = in ? sums[cc * 2 + 1] : 0.0;
+            lr[g] = in ? last[cc * 2] : -1;
+            lq[g] = in ? last[cc * 2 + 1] : -1;
+        }
+        const bool open = kind == SEQ_OPEN;
+        const int i = open ? 0 : max(sel, 0), j = open ? (d.deferred ? a.k : 0) : acc_len;
+        double zmax, Z;
+        row_stats_of(a, b.row_stats, a.judge_index(i, j), zmax, Z);
+        const TokenWeights<NUC> w(a, i, j, zmax, Z);
+        const ChainWeights<NUC> ch{w, d, b.inv_total, open ? launches - 1 : 0};
+        const float* qrow = open ? (d.s > 0 ? d.q + (size_t)(launches - 1) * d.q_stride : nullptr) : w.qrow;
+        const int ui = open ? a.n - 1 : i;
+        const double u = (double)a.u[ui * (a.k + 1) + a.k];
+        auto pw = [&](int v) { return ch.p(v); };
+        if (qrow) {
+            auto rw = [&](int v) { return fmax(ch.p(v) - (double)qrow[v], 0.0); };
+            tok = wave_inverse_cdf(rw, a.V, u, xr, lr, b.chunks(), b.chunk);
+        }
+        if (tok < 0) tok = wave_inverse_cdf(pw, a.V, u, xp, lq, b.chunks(), b.chunk);  // nothing to subtract, or the residual vanished
+    }
+    if (d.deferred) {
+        if (lane == 0) {
+            a.accept_len[0] = acc_len;
+            a.next_token[0] = tok;
+        }
+    } else {
+        for (int i = lane; i < a.n; i += 64) {
+            a.accept_len[i] = sel < 0 ? 0 : (i < sel ? 0 : (i == sel ? acc_len : -1));
+            a.next_token[i] = i == sel ? tok : -1;
+        }
+    }
+    if (lane == 0) {
+        if (status_now(a.status) != 0) {
+            write_failed_commit(a.commit, d.prefix_len, a.P);
+        } else {
+            a.commit[0] = sel;
+            a.commit[1] = acc_len;
+            a.commit[2] = tok;
+            a.commit[3] = a.P + a.R + acc_len;
+            if (d.deferred && d.prefix_len) *d.prefix_len = a.P + a.R + acc_len;
         }
     }
 }
