@@ -224,11 +224,11 @@ void launch_attention(int mtw, int nwv, dim3 grid, const AttnArgs& a, hipStream_
 template <int NT, class Epi>
 void launch_projection(int cls, int M, const u16* X, const u16* W, int K, int tiles, const RowScale& rsc, const Epi& epi,
                        hipStream_t s) {
-    if (M > DUO_MAX_ROWS) {  // prefill pass: both operands staged in LDS; wider blocks once they still fill the chip
-        launch_block_rows<NT>(X, W, K, tiles * NT, M, rsc, epi, s, [&]() { prof(cls, s); });
+    prof(cls, s);
+    if (M > DUO_MAX_ROWS) {  // prefill pass: both operands staged in LDS
+        launch_block<NT>(X, W, K, tiles * NT, M, 1, rsc, epi, s);
         return;
     }
-    prof(cls, s);
     if (M <= 8) {
         if (!launch_wide_half<NT>(X, W, K, tiles, rsc, epi, s)) launch_gemm_rows<NT>(M, true, X, W, K, tiles, rsc, epi, s);
         return;
@@ -263,7 +263,7 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, const 
     const int MH = (M + 15) / 16, d = er.N;
     if (!residual_is_split(M, K, d)) {
         prof(cls, s);
-        if (M > DUO_MAX_ROWS) launch_block<4, 4, 1>(X, W, K, d / 16, M, 1, none, er, s);
+        if (M > DUO_MAX_ROWS) launch_block<1>(X, W, K, d / 16, M, 1, none, er, s);
         else launch_gemm_rows<1>(M, true, X, W, K, d / 16, none, er, s);
         return;
     }
@@ -271,7 +271,7 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, const 
     prof(cls, s);
     if (M > DUO_MAX_ROWS) {
         EpiStoreF32 e{d, M, 1, split, d, (size_t)M * d};
-        S = launch_block<4, 4, 1>(X, W, K, d / 16, M, block_splits(M, d), none, e, s);
+        S = launch_block<1>(X, W, K, d / 16, M, block_splits(M, d), none, e, s);
     } else switch (MH) {
         case 2: S = launch_wide_split<2>(X, W, K, d, M, split, none, s); break;
         case 3: S = launch_wide_split<3>(X, W, K, d, M, split, none, s); break;
@@ -380,7 +380,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     // 18.5 against 21.1 us for up to eight rows, 18.8 / 21.8 / 28.7 / 32.4 against 22.0 / 24.8 / 32.1 / 35.2 us for
     // 16 / 32 / 64 / 80 rows; at 384 bands the same or slightly better beyond eight rows).
     const int qkv_bands = (Hq + 2 * Hkv) * (D / 16);
-    const int qkv_nt = M > DUO_MAX_ROWS ? 2 : (M <= 8 ? ((qkv_bands > 512 && qkv_bands <= 768) ? 1 : 2) : (qkv_bands <= 768 ? 1 : 2));
+    const int qkv_nt = M > DUO_MAX_ROWS ? 1 : (M <= 8 ? ((qkv_bands > 512 && qkv_bands <= 768) ? 1 : 2) : (qkv_bands <= 768 ? 1 : 2));
     // the Q/K/V projection as K-split product + finish kernel (see the loop): 49..80 rows, one band per wave, partial results fit
     const bool qkv_split = M > 48 && M <= DUO_MAX_ROWS && qkv_nt == 1 && (size_t)QKV_SPLITS * M * qkv_bands * 16 <= ws.split_floats;
     for (int l = 0; l < c.n_layers; ++l) {
@@ -876,7 +876,7 @@ int duo_block_gemm(const uint16_t* x, const uint16_t* w, float* y, int rows, int
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     (void)hipGetLastError();
     EpiStoreF32 e{N, rows, 1, y, N, 0};
-    launch_block<4, 4, 1>(x, w, K, (N + 15) / 16, rows, 1, RowScale{nullptr, 0, 0.f, 0.f, nullptr}, e, s);
+    launch_block<1>(x, w, K, (N + 15) / 16, rows, 1, RowScale{nullptr, 0, 0.f, 0.f, nullptr}, e, s);
     return hip_ok(hipGetLastError(), "duo_block_gemm launch");
 }
 

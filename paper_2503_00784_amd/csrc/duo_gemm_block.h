@@ -12,8 +12,8 @@
 // memory inside the loop.
 //
 // Per K step a wave reads (2*WM + WN) KiB from LDS for 2*WM*WN MFMAs: 12 KiB per 32 MFMAs (512 cycles) at
-// WM = WN = 4, i.e. 96 B/clk per compute unit, inside what LDS delivers; the block pulls (4*WM + 2*WN) KiB
-// per K step through L2.
+// WM = WN = 4, i.e. 96 B/clk per compute unit, 20 KiB per 96 MFMAs at (4, 12), 53 B/clk; the block pulls
+// (4*WM + 2*WN) KiB per K step through L2.
 //
 // Grid: x = blocks of bands, y = K splits (partial results, see EpiStoreF32), z = blocks of rows.
 // ENT = bands per epilogue tile (2 for the rotary and SwiGLU epilogues, 1 otherwise).
@@ -22,7 +22,7 @@
 
 template <int WM, int WN, int KS, int ENT, class Epi>
 __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__ X, const u16* __restrict__ W, int K,
-                                                         int split_steps, int band_base, int nbands, int mh_total, int quads, RowScale rsc,
+                                                         int split_steps, int nbands, int mh_total, int quads, RowScale rsc,
                                                          Epi epi) {
     constexpr int BMT = 2 * WM, BNT = 2 * WN;  // row tiles (hi) and bands per workgroup
     constexpr int PER = 2 * BMT + BNT;         // tiles per K step
@@ -30,6 +30,7 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
     constexpr int NBUF = 3;
     static_assert(ST <= 63, "a stage's loads fit the memory counter");
     static_assert(WN % ENT == 0, "whole epilogue tiles per wave");
+    static_assert(WN <= 8 || WN % 2 == 0, "two equal halves");
     __shared__ u32x4 lds[NBUF * ST * 64];
     __shared__ float row_scale[BMT * 16];
 
@@ -38,7 +39,7 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
     const int k0 = blockIdx.y * split_steps;
     const int ns = min(steps - k0, split_steps);  // K steps of this split (the host makes it positive)
     const int rounds = (ns + KS - 1) / KS;
-    const int row_tile0 = blockIdx.z * BMT, band0 = band_base + blockIdx.x * BNT;  // bands [band_base, nbands) are this launch's
+    const int row_tile0 = blockIdx.z * BMT, band0 = blockIdx.x * BNT;
     const int row0 = row_tile0 * 16, nrows = quads * 4;
 
     // RMSNorm factors of this block's rows (all five waves)
@@ -122,20 +123,34 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
                     ah[m] = f.v;
                     al[m] = g.v;
                 }
+                auto load_bands = [&](int t0, int t1) {
 #pragma unroll
-                for (int t = 0; t < WN; ++t) {
-                    Frag8 f;
-                    f.q = st[(2 * BMT + wn * WN + t) * 64];
-                    b[t] = f.v;
+                    for (int t = t0; t < t1; ++t) {
+                        Frag8 f;
+                        f.q = st[(2 * BMT + wn * WN + t) * 64];
+                        b[t] = f.v;
+                    }
+                };
+                auto products = [&](int t0, int t1) {
+#pragma unroll
+                    for (int m = 0; m < WM; ++m)
+#pragma unroll
+                        for (int t = t0; t < t1; ++t) acc[m][t] = mfma16(b[t], ah[m], acc[m][t]);
+#pragma unroll
+                    for (int m = 0; m < WM; ++m)
+#pragma unroll
+                        for (int t = t0; t < t1; ++t) acc[m][t] = mfma16(b[t], al[m], acc[m][t]);
+                };
+                if constexpr (WN <= 8) {
+                    load_bands(0, WN);
+                    products(0, WN);
+                } else {  // in two halves: operands and accumulators (WM = 4, WN = 12: 192) within the 256 registers of a wave of five
+                    load_bands(0, WN / 2);
+                    products(0, WN / 2);
+                    __builtin_amdgcn_sched_barrier(0);
+                    load_bands(WN / 2, WN);
+                    products(WN / 2, WN);
                 }
-#pragma unroll
-                for (int m = 0; m < WM; ++m)
-#pragma unroll
-                    for (int t = 0; t < WN; ++t) acc[m][t] = mfma16(b[t], ah[m], acc[m][t]);
-#pragma unroll
-                for (int m = 0; m < WM; ++m)
-#pragma unroll
-                    for (int t = 0; t < WN; ++t) acc[m][t] = mfma16(b[t], al[m], acc[m][t]);
             }
         }
         __syncthreads();  // stage r + 1 is in LDS; stage r's buffer may be refilled
@@ -159,10 +174,10 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
     }
 }
 
-// Launch for M rows (operand of 2 * mh_total row tiles: hi tiles, then lo tiles) over the bands [band_begin, band_end) of
-// 16 columns each, K split `splits` ways over the grid's y dimension (returns the number of splits actually used).
+// Launch for M rows (operand of 2 * mh_total row tiles: hi tiles, then lo tiles) over nbands bands of 16 columns each, K
+// split `splits` ways over the grid's y dimension (returns the number of splits actually used).
 template <int WM, int WN, int ENT, class Epi>
-static inline int launch_block_range(const u16* X, const u16* W, int K, int band_begin, int band_end, int M, int splits,
+static inline int launch_block_range(const u16* X, const u16* W, int K, int nbands, int M, int splits,
                                      const RowScale& rsc, const Epi& epi, hipStream_t s) {
     constexpr int KS = (2 * (4 * WM + 2 * WN) <= 48) ? 2 : 1;  // stage of at most 48 KiB
     const int mh_total = pair_rows_for(M) / 16, quads = pair_rows_for(M) / 4;
@@ -170,44 +185,55 @@ static inline int launch_block_range(const u16* X, const u16* W, int K, int band
     int split_steps = (steps + splits - 1) / splits;
     split_steps = (split_steps + KS - 1) / KS * KS;
     const int S = (steps + split_steps - 1) / split_steps;
-    const dim3 grid((band_end - band_begin + 2 * WN - 1) / (2 * WN), S, (mh_total + 2 * WM - 1) / (2 * WM));
+    const dim3 grid((nbands + 2 * WN - 1) / (2 * WN), S, (mh_total + 2 * WM - 1) / (2 * WM));
     DUO_KERNEL_NAME("gemm_block_kernel<%d, %d, %d, %d, %s>", WM, WN, KS, ENT, Epi::NAME);
-    DUO_LAUNCH((gemm_block_kernel<WM, WN, KS, ENT, Epi>), grid, dim3(320), s, X, W, K, split_steps, band_begin, band_end, mh_total,
+    DUO_LAUNCH((gemm_block_kernel<WM, WN, KS, ENT, Epi>), grid, dim3(320), s, X, W, K, split_steps, nbands, mh_total,
                quads, rsc, epi);
     return S;
 }
-template <int WM, int WN, int ENT, class Epi>
-static inline int launch_block(const u16* X, const u16* W, int K, int nbands, int M, int splits, const RowScale& rsc,
-                               const Epi& epi, hipStream_t s) {
-    return launch_block_range<WM, WN, ENT>(X, W, K, 0, nbands, M, splits, rsc, epi, s);
+
+// The block shape of a launch.  A workgroup has a compute unit to itself (its stages take most of the LDS), so a launch costs
+// its rounds of workgroups, one per compute unit, times what a K step costs a workgroup of that shape.  Measured over K = 4096 with
+// 230..256 workgroups (us per K step): WM = 4: 0.37 / 0.41 / 0.50 / 0.57 / 0.64 / 0.82 / 0.93 / 1.14 for WN = 2 / 3 / 4 / 5 / 6 /
+// 8 / 10 / 12, WM = 3: 0.31 / 0.35 / 0.42 / 0.52 / 0.67 for 2 / 3 / 4 / 6 / 8, WM = 2: 0.28 / 0.30 / 0.44 / 0.53 for 2 / 3 / 6 / 8,
+// all within a tenth of 0.18 + WN * (0.006 + 0.0186 * WM).  Full rounds matter more than large tiles: Q/K/V at 1024 rows
+// (768 bands) takes 195 us as 384 workgroups of (4, 8), 157 us as 512 of (4, 6), 148 us = 1.39 PFLOP/s as 256 of (4, 12).
+struct BlockShape {
+    int wm, wn;
+    float cost;
+};
+template <int ENT>
+static inline BlockShape block_shape(int nbands, int M, int steps, int splits) {
+    constexpr int CUS = 256;
+    static const int shapes[][2] = {{4, 12}, {4, 10}, {4, 8}, {4, 6}, {4, 5}, {4, 4}, {4, 3}, {4, 2}, {3, 12}, {3, 10}, {3, 8}, {3, 6},
+                                    {3, 5},  {3, 4},  {3, 3}, {3, 2}, {2, 8}, {2, 6}, {2, 4}, {2, 3}, {2, 2}};
+    const int mh = pair_rows_for(M) / 16;
+    BlockShape best{4, 4, 1e30f};
+    for (const auto& c : shapes) {
+        if (c[1] % ENT != 0) continue;
+        const int wgs = ((nbands + 2 * c[1] - 1) / (2 * c[1])) * ((mh + 2 * c[0] - 1) / (2 * c[0])) * splits;
+        const float cost = (float)((wgs + CUS - 1) / CUS) * (float)((steps + splits - 1) / splits) *
+                           (0.18f + (float)c[1] * (0.006f + 0.0186f * (float)c[0]));
+        if (cost < best.cost) best = BlockShape{c[0], c[1], cost};
+    }
+    return best;
 }
 
-// A projection whose epilogue finishes the rows (no K split), for M > 80 rows.  Workgroups of 64 x 128 wave tiles are the
-// faster ones but come in few, large units: when their count leaves the last round of workgroups (one per compute unit)
-// mostly empty, the bands of that round are given to workgroups of 64 x 64 wave tiles instead, in a second launch.
-// Cost model in rounds of the large tile: a round of small tiles takes 0.55 of one.
-// `before_launch` is called in front of every launch (the caller's per-kernel timer).
-template <int ENT, class Epi, class Hook>
-static inline void launch_block_rows(const u16* X, const u16* W, int K, int nbands, int M, const RowScale& rsc, const Epi& epi,
-                                     hipStream_t s, Hook before_launch) {
-    constexpr int CUS = 256;
-    const int rb = (pair_rows_for(M) / 16 + 7) / 8;  // row blocks (128 rows)
-    const int n_large = (nbands + 15) / 16, n_small = (nbands + 7) / 8;
-    const auto rounds = [](int wgs) { return (wgs + CUS - 1) / CUS; };
-    const float all_large = (float)rounds(n_large * rb), all_small = 0.55f * (float)rounds(n_small * rb);
-    const int full = (n_large * rb) / CUS;                    // full rounds of large workgroups
-    const int main_blocks = full * CUS / rb;                  // whole band blocks (256 columns) inside them
-    const int rest_bands = nbands - main_blocks * 16;
-    const float mixed = (full > 0 && rest_bands > 0) ? (float)rounds(main_blocks * rb) + 0.55f * (float)rounds((rest_bands + 7) / 8 * rb)
-                                                      : 1e30f;
-    before_launch();
-    if (mixed < all_large && mixed < all_small) {
-        launch_block_range<4, 8, ENT>(X, W, K, 0, main_blocks * 16, M, 1, rsc, epi, s);
-        before_launch();
-        launch_block_range<4, 4, ENT>(X, W, K, main_blocks * 16, nbands, M, 1, rsc, epi, s);
-    } else if (all_large <= all_small && n_large * rb >= 160) {
-        launch_block_range<4, 8, ENT>(X, W, K, 0, nbands, M, 1, rsc, epi, s);
-    } else {
-        launch_block_range<4, 4, ENT>(X, W, K, 0, nbands, M, 1, rsc, epi, s);
+// A projection over M > 80 rows in the shape that block_shape picks; K split `splits` ways (returns the number used).
+template <int ENT, class Epi>
+static inline int launch_block(const u16* X, const u16* W, int K, int nbands, int M, int splits, const RowScale& rsc, const Epi& epi,
+                               hipStream_t s) {
+    const BlockShape b = block_shape<ENT>(nbands, M, K >> 5, splits);
+#define DUO_BLOCK_CASE(WM, WN)                                                                                         \
+    case WM * 16 + WN:                                                                                                 \
+        if constexpr (WN % ENT == 0) return launch_block_range<WM, WN, ENT>(X, W, K, nbands, M, splits, rsc, epi, s); \
+        break;
+    switch (b.wm * 16 + b.wn) {
+        DUO_BLOCK_CASE(4, 12) DUO_BLOCK_CASE(4, 10) DUO_BLOCK_CASE(4, 8) DUO_BLOCK_CASE(4, 6) DUO_BLOCK_CASE(4, 5)
+        DUO_BLOCK_CASE(4, 3) DUO_BLOCK_CASE(4, 2) DUO_BLOCK_CASE(3, 12) DUO_BLOCK_CASE(3, 10) DUO_BLOCK_CASE(3, 8)
+        DUO_BLOCK_CASE(3, 6) DUO_BLOCK_CASE(3, 5) DUO_BLOCK_CASE(3, 4) DUO_BLOCK_CASE(3, 3) DUO_BLOCK_CASE(3, 2)
+        DUO_BLOCK_CASE(2, 8) DUO_BLOCK_CASE(2, 6) DUO_BLOCK_CASE(2, 4) DUO_BLOCK_CASE(2, 3) DUO_BLOCK_CASE(2, 2)
     }
+#undef DUO_BLOCK_CASE
+    return launch_block_range<4, 4, ENT>(X, W, K, nbands, M, splits, rsc, epi, s);
 }
