@@ -941,7 +941,7 @@ static inline void launch_gemm_rows(int M, bool paired, const u16* X, const u16*
 constexpr int WIDE_MAX_SPLIT = 8;
 constexpr int WIDE_PF = 8, WIDE_AG = 4;
 
-template <int MH, int NT, int NG, int NK, class Epi, bool HALF = false, bool STREAM = true>
+template <int MH, int NT, int NG, int NK, class Epi, bool HALF = false, bool STREAM = true, int PFW = WIDE_PF>
 static inline void launch_wide_cfg(const u16* X, const u16* W, int K, int tiles, int quads, int splits, const RowScale& rsc,
                                    const Epi& epi, hipStream_t s, int* splits_out) {
     // rounds of NK * AG K steps; a round's operand tiles (2*MH per step) must fit the producer's counted wait
@@ -952,9 +952,9 @@ static inline void launch_wide_cfg(const u16* X, const u16* W, int K, int tiles,
     split_steps = (split_steps + RS - 1) / RS * RS;  // whole rounds: only the last split has a ragged end
     const int S = (steps + split_steps - 1) / split_steps;
     if (splits_out) *splits_out = S;
-    DUO_KERNEL_NAME("gemm_wide_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s>", MH, NT, NG, NK, WIDE_PF, AG, Epi::NAME, HALF ? "true" : "false",
+    DUO_KERNEL_NAME("gemm_wide_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s>", MH, NT, NG, NK, PFW, AG, Epi::NAME, HALF ? "true" : "false",
                     STREAM ? "true" : "false");
-    DUO_LAUNCH((gemm_wide_kernel<MH, NT, NG, NK, WIDE_PF, AG, Epi, HALF, STREAM>), dim3((tiles + NG - 1) / NG, S),
+    DUO_LAUNCH((gemm_wide_kernel<MH, NT, NG, NK, PFW, AG, Epi, HALF, STREAM>), dim3((tiles + NG - 1) / NG, S),
                dim3((NG * NK + 1) * 64), s, X, W, K, split_steps, tiles, quads, rsc, epi);
 }
 
@@ -967,6 +967,12 @@ static inline void launch_wide(const u16* X, const u16* W, int K, int tiles, int
     if (ng <= 1) launch_wide_cfg<MH, NT, 1, 2>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
     else if (ng == 2) launch_wide_cfg<MH, NT, 2, 2>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
     else if (ng == 3) launch_wide_cfg<MH, NT, 3, 1>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
+    // many bands: eight waves of four weight slots stage the operand half as often.  A round of such workgroups takes 1.55
+    // (80 rows) to 1.9 (9 rows) rounds of the smaller ones.  4008 tiles (a 128k vocabulary, two rounds against four): 267 -> 212 us
+    // at 80 rows, 216 -> 197 at 32, 197 -> 188 at 12; 1250 tiles (one against two): 110 -> 90, 77 -> 62, 73 -> 56; 2500 tiles
+    // (two against three) stay; 2048 tiles, two full rounds: 135 -> 107 at 80 rows but 95 -> 100 at 32
+    else if (1.75f * (float)((tiles + 2047) / 2048) < (float)((tiles + 1023) / 1024) && (MH > 2 || tiles <= 1792 || tiles > 2048))
+        launch_wide_cfg<MH, NT, 8, 1, Epi, false, true, 4>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
     else launch_wide_cfg<MH, NT, 4, 1>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
 }
 
