@@ -251,10 +251,12 @@ static_assert(WIDE_MAX_SPLIT <= 8, "residual_reduce_kernel holds at most eight s
 // Whether the residual projection over K input channels runs as K-split partial products + reduce kernel: beyond 16
 // rows.  (At 32 rows x 4096 input channels the split form alone is no faster, 10.3 + 4.2 against 14.0 us, but the reduce
 // kernel leaves whole-row sums of squares, which the next projection turns into its factors 2.5 us sooner than the 256
-// partial sums per row of the one-kernel form: 3.62 -> 3.53 ms per step at 32 rows of the 7B shape.)
-bool residual_is_split(int M, int /*K*/, int N) {
+// partial sums per row of the one-kernel form: 3.62 -> 3.53 ms per step at 32 rows of the 7B shape.)  At 9..16 rows only for
+// long K: the down projection 22.7 -> 17 + 4.3 us at 11008 input channels, 29.5 -> 20.5 + 4.3 at 14336, and the next Q/K/V starts
+// sooner (a layer 3.5 and 6.4 us shorter); the O projection's 4096 channels 10.6 -> 8.7 + 4.3 us, which the step does not gain from.
+bool residual_is_split(int M, int K, int N) {
     if (M > DUO_MAX_ROWS) return block_splits(M, N) > 1;
-    return M > 16;
+    return M > 16 || (M > 8 && K >= 8192);
 }
 
 void launch_residual_projection(int M, const u16* X, const u16* W, int K, const EpiResidual& er, float* split,
@@ -273,6 +275,7 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, const 
         EpiStoreF32 e{d, M, 1, split, d, (size_t)M * d};
         S = launch_block<1>(X, W, K, d / 16, M, block_splits(M, d), none, e, s);
     } else switch (MH) {
+        case 1: S = launch_wide_split<1>(X, W, K, d, M, split, none, s); break;
         case 2: S = launch_wide_split<2>(X, W, K, d, M, split, none, s); break;
         case 3: S = launch_wide_split<3>(X, W, K, d, M, split, none, s); break;
         case 4: S = launch_wide_split<4>(X, W, K, d, M, split, none, s); break;
