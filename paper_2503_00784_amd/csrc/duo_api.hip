@@ -287,7 +287,8 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, const 
 
 template <int D>
 void launch_attention_shared(int mtw, int nwv, int ksplit, dim3 grid, const AttnArgs& a, hipStream_t s) {
-    if (mtw == 2) DUO_LAUNCH((attn_shared_kernel<D, 2, 7>), grid, dim3(512), s, a);  // 8 waves: 256 registers each
+    if (ksplit == 2 && nwv == 10) DUO_LAUNCH((attn_shared_kernel<D, 1, 10, 2>), grid, dim3(704), s, a);
+    else if (mtw == 2) DUO_LAUNCH((attn_shared_kernel<D, 2, 7>), grid, dim3(512), s, a);  // 8 waves: 256 registers each
     else if (ksplit == 2 && nwv == 8) DUO_LAUNCH((attn_shared_kernel<D, 1, 8, 2>), grid, dim3(576), s, a);
     else if (ksplit == 2) DUO_LAUNCH((attn_shared_kernel<D, 1, 4, 2>), grid, dim3(320), s, a);
     else DUO_LAUNCH((attn_shared_kernel<D, 1, 8>), grid, dim3(576), s, a);
@@ -340,11 +341,21 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         // one query tile per wave, about 256 workgroups (one per compute unit): measured best for 4 tiles x 32 heads and 16 tiles x 8 heads
         // Up to four tiles: two teams of waves share the blocks (two waves per SIMD: 20.7 against 23.2 us at 4 tiles,
         // 11.8 against 14.4 us at 2 tiles, measured on 32 heads x 4160 / 2080 keys).
-        sh_mtw = MqT > 16 ? 2 : 1;
-        sh_ksplit = (MqT <= 4 || (MqT > 8 && MqT <= 16)) ? 2 : 1;  // 9..16 tiles (64 rows x a GQA group of 4): 27.3 against 28.2 us at 8192 keys
-        sh_nwv = MqT > 16 ? 7 : (MqT > 2 ? 8 : 4);
+        sh_mtw = many && MqT > 16 ? 2 : 1;
+        // 9..16 tiles (64 rows x a GQA group of 4): 27.3 against 28.2 us at 8192 keys; 17..20 tiles (65..80 rows) in the same shape
+        // against two tiles per wave: 33.8 against 43.4 us at 8192 keys, 14.1 against 18.6 at 2048, 10.9 against 13.4 at 700
+        sh_ksplit = (MqT <= 4 || (MqT > 8 && sh_mtw == 1)) ? 2 : 1;
+        sh_nwv = sh_mtw == 2 ? 7 : (MqT > 2 ? 8 : 4);
+        if (MqT == 5 && NB >= 64) {
+            // five tiles (65..80 rows of a head without a group) on a long context: two teams of five against eight waves of which
+            // five have a tile, 25.9 -> 22.3 us on 32 heads x 4161 keys, 17.9 -> 17.3 at 2127 (at 577 keys 9.1 -> 10.3: not there)
+            sh_ksplit = 2;
+            sh_nwv = 10;
+        }
         sh_zg = (MqT + (sh_nwv / sh_ksplit) * sh_mtw - 1) / ((sh_nwv / sh_ksplit) * sh_mtw);
-        int target = (256 + Hkv * sh_zg - 1) / (Hkv * sh_zg);
+        // LDS (teams) or registers (nine waves) leave room for one workgroup per compute unit, so no more than 256 of them (40
+        // heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us)
+        int target = 256 / (Hkv * sh_zg);
         target = target < 1 ? 1 : (target > max_chunks ? max_chunks : target);
         if (many) {
             // many row groups: the chunk count that leaves the fewest compute units idle in the last round of

@@ -1,4 +1,5 @@
-"""Launch shapes that depend on the number of rows: the LM head of a large vocabulary, the K-split down projection of nine to sixteen rows.  Whole steps against the oracle."""
+"""Launch shapes that depend on the number of rows: attention over five and over seventeen to twenty query tiles per KV head,
+the LM head of a large vocabulary, the K-split down projection of nine to sixteen rows.  Whole steps against the oracle."""
 import dataclasses
 
 import pytest
@@ -15,6 +16,25 @@ def B():
     from paper_2503_00784_amd import binding
     binding.load()
     return binding
+
+
+# heads of 64 in groups of four (tiles = rows * 4 / 16): 16, 17, 18, 20 tiles, a short and a longer prefix
+@pytest.mark.parametrize("P", [30, 700])
+@pytest.mark.parametrize("n,k,root", [(4, 16, -1), (4, 16, 5), (3, 23, 1), (5, 16, -1)])
+def test_attention_beyond_sixteen_tiles(B, P, n, k, root):
+    say(f"MID P={P} n={n} k={k} root={root}")
+    w, oshape, eng, cache = _engine_and_oracle(B, inputs.MID, P, (P + 96 + 31) // 32 * 32, seed=P, synthetic_cache=True)
+    _check_step(B, inputs.MID, w, oshape, eng, cache, n, k, seed=n, mode=0, root_token=root)
+
+
+# no groups: 65..80 rows are five tiles; 64 blocks of 32 keys is where the two teams of five take over
+@pytest.mark.parametrize("shape", ["NARROW64", "NARROW128"])
+@pytest.mark.parametrize("P,n,k,root", [(1940, 4, 16, 5), (1968, 5, 16, -1), (1984, 4, 16, 5), (3001, 6, 13, -1)])
+def test_attention_of_five_tiles(B, shape, P, n, k, root):
+    s = inputs.ModelShape(2, 320, 5, 5, 64, 640, 1000) if shape == "NARROW64" else inputs.ModelShape(1, 384, 3, 3, 128, 512, 1000)
+    say(f"{shape} P={P} n={n} k={k} root={root}")
+    w, oshape, eng, cache = _engine_and_oracle(B, s, P, (P + 96 + 31) // 32 * 32, seed=P, synthetic_cache=True)
+    _check_step(B, s, w, oshape, eng, cache, n, k, seed=n, mode=0, root_token=root)
 
 
 # 4008 tiles of 32 entries and a ragged last workgroup (100003 entries: 3126 tiles)
