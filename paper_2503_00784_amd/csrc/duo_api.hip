@@ -248,32 +248,51 @@ void launch_projection(int cls, int M, const u16* X, const u16* W, int K, int ti
 // second kernel that adds them in split order and does EpiResidual's work.
 static_assert(WIDE_MAX_SPLIT <= 8, "residual_reduce_kernel holds at most eight splits in registers");
 
-// Whether the residual projection over K input channels runs as K-split partial products + reduce kernel: beyond 16
-// rows.  (At 32 rows x 4096 input channels the split form alone is no faster, 10.3 + 4.2 against 14.0 us, but the reduce
-// kernel leaves whole-row sums of squares, which the next projection turns into its factors 2.5 us sooner than the 256
-// partial sums per row of the one-kernel form: 3.62 -> 3.53 ms per step at 32 rows of the 7B shape.)  At 9..16 rows only for
-// long K: the down projection 22.7 -> 17 + 4.3 us at 11008 input channels, 29.5 -> 20.5 + 4.3 at 14336, and the next Q/K/V starts
-// sooner (a layer 3.5 and 6.4 us shorter); the O projection's 4096 channels 10.6 -> 8.7 + 4.3 us, which the step does not gain from.
-bool residual_is_split(int M, int K, int N) {
-    if (M > DUO_MAX_ROWS) return block_splits(M, N) > 1;
-    return M > 16 || (M > 8 && K >= 8192);
+// K splits of a residual projection over K input channels: 1 = one kernel (EpiResidual), more = K-split partial products + reduce
+// kernel.  `floats`: room for the partial results.
+// Up to 80 rows: split beyond 16 rows.  (At 32 rows x 4096 input channels the split form alone is no faster, 10.3 + 4.2 against
+// 14.0 us, but the reduce kernel leaves whole-row sums of squares, which the next projection turns into its factors 2.5 us sooner
+// than the 256 partial sums per row of the one-kernel form: 3.62 -> 3.53 ms per step at 32 rows of the 7B shape.)  At 9..16 rows
+// only for long K: the down projection 22.7 -> 17 + 4.3 us at 11008 input channels, 29.5 -> 20.5 + 4.3 at 14336, and the next Q/K/V
+// starts sooner (a layer 3.5 and 6.4 us shorter); the O projection's 4096 channels 10.6 -> 8.7 + 4.3 us, which the step does not gain
+// from.
+// More rows: the number of splits whose product (see block_shape) and second kernel together cost least.  The reduce kernel takes
+// 5 us and the time of writing and reading the partial results, 0.53 us per MB (333 rows of 4096: 11 us for two splits); the
+// row sums behind an unsplit projection 4 us.
+int residual_splits(int M, int K, int N, size_t floats) {
+    if (M <= DUO_MAX_ROWS) return (M > 16 || (M > 8 && K >= 8192)) ? WIDE_MAX_SPLIT : 1;
+    int best = 1;
+    float best_cost = 1e30f;
+    for (int S = 1; S <= WIDE_MAX_SPLIT && (S == 1 || (size_t)S * M * N <= floats); ++S) {
+        const float mb = 4e-6f * (float)S * (float)M * (float)N;
+        const float cost = block_shape<1>(N / 16, M, K >> 5, S).cost + (S > 1 ? 5.f + 0.53f * mb : 4.f);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best = S;
+        }
+    }
+    return best;
 }
 
-void launch_residual_projection(int M, const u16* X, const u16* W, int K, const EpiResidual& er, float* split,
+void launch_residual_projection(int M, const u16* X, const u16* W, int K, int splits, const EpiResidual& er, float* split,
                                 float* ssq_full, int cls, hipStream_t s) {
     const RowScale none{nullptr, 0, 0.f, 0.f, nullptr};
     const int MH = (M + 15) / 16, d = er.N;
-    if (!residual_is_split(M, K, d)) {
-        prof(cls, s);
-        if (M > DUO_MAX_ROWS) launch_block<1>(X, W, K, d / 16, M, 1, none, er, s);
-        else launch_gemm_rows<1>(M, true, X, W, K, d / 16, none, er, s);
+    prof(cls, s);
+    if (splits == 1) {
+        if (M <= DUO_MAX_ROWS) {
+            launch_gemm_rows<1>(M, true, X, W, K, d / 16, none, er, s);
+            return;
+        }
+        launch_block<1>(X, W, K, d / 16, M, 1, none, er, s);
+        prof(DUO_PROF_RESID_REDUCE, s);
+        DUO_LAUNCH(row_sums_kernel, dim3((M + 3) / 4), dim3(256), s, er.ssq_part, d / 16, M, ssq_full);
         return;
     }
     int S = 1;
-    prof(cls, s);
     if (M > DUO_MAX_ROWS) {
         EpiStoreF32 e{d, M, 1, split, d, (size_t)M * d};
-        S = launch_block<1>(X, W, K, d / 16, M, block_splits(M, d), none, e, s);
+        S = launch_block<1>(X, W, K, d / 16, M, splits, none, e, s);
     } else switch (MH) {
         case 1: S = launch_wide_split<1>(X, W, K, d, M, split, none, s); break;
         case 2: S = launch_wide_split<2>(X, W, K, d, M, split, none, s); break;
@@ -311,8 +330,14 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     // (embedding gather, K-split reduce) and the consumer is the LDS-shared kernel, which reads them directly.
     const RowScale norm_part{ws.ssq, NP, 1.0f / (float)d, c.rms_eps, nullptr};
     const RowScale norm_full{ws.ssq, NP, 1.0f / (float)d, c.rms_eps, ws.ssq_full};
-    const bool o_split = residual_is_split(M, qd, d), down_split = residual_is_split(M, F, d);
+    // partial results of split residual projections: their own part of the workspace, or the nucleus search's rows, which are idle
+    // until the pass has left its logits, where those are larger
+    const size_t idle_floats = (size_t)(DUO_MAX_ROWS + 1) * V * 2;
+    float* const split = ws.split_floats >= idle_floats ? ws.split : reinterpret_cast<float*>(ws.p_rows);
+    const size_t split_floats = std::max(ws.split_floats, idle_floats);
+    const int o_splits = residual_splits(M, qd, d, split_floats), down_splits = residual_splits(M, F, d, split_floats);
     const bool many = M > DUO_MAX_ROWS;  // prefill pass: logits of the last row only (to logits[0 .. V))
+    const bool o_full = many || o_splits > 1, down_full = many || down_splits > 1;  // whole-row sums of squares behind it
     const int max_chunks = many ? MAX_CHUNKS_MANY_ROWS : MAX_CHUNKS;
     const bool stats = temperature >= 0.0;
     const bool root_stats = stats && plan.R == 0;
@@ -402,7 +427,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         u16* vc = cache.v + (size_t)l * Hkv * c.max_seq * D;
         EpiQKV eq{Hq, Hkv, D, half, D / 16, qkv_nt, ws.q, qd, ws.q_plane, kc, vc, c.max_seq, ws.rope_c, ws.rope_s, plan,
                   cache.prefix_len, 1};
-        const RowScale& qkv_norm = (l == 0 || down_split) ? norm_full : norm_part;
+        const RowScale& qkv_norm = (l == 0 || down_full) ? norm_full : norm_part;
         if (qkv_split) {
             // 49..80 rows: K split two or four ways over workgroups of as many times the bands, each staging its part of the
             // operand (22.1 against 27.1 us for the product at 64 rows x 768 bands), partial results to the workspace, and a
@@ -453,29 +478,29 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
 
         // the residual projections leave x, the next norm's operand u = x * gain and its partial sums
         EpiResidual eo{d, M, ws.x, d, w.g_ffn[l], ws.h, PR, AT, ws.ssq};
-        launch_residual_projection(M, ws.attn, w.wo[l], qd, eo, ws.split, ws.ssq_full, DUO_PROF_OPROJ, s);
+        launch_residual_projection(M, ws.attn, w.wo[l], qd, o_splits, eo, split, ws.ssq_full, DUO_PROF_OPROJ, s);
 
         EpiSwiGLU eg{F, M, ws.act, AT, PR};
-        launch_projection<2>(DUO_PROF_GATEUP, M, ws.h, w.w_gate_up[l], d, F / 16, o_split ? norm_full : norm_part, eg, s);
+        launch_projection<2>(DUO_PROF_GATEUP, M, ws.h, w.w_gate_up[l], d, F / 16, o_full ? norm_full : norm_part, eg, s);
 
         const u16* gnext = l + 1 < c.n_layers ? w.g_attn[l + 1] : w.g_final;
         EpiResidual ed{d, M, ws.x, d, gnext, ws.h, PR, AT, ws.ssq};
-        launch_residual_projection(M, ws.act, w.w_down[l], F, ed, ws.split, ws.ssq_full, DUO_PROF_DOWN, s);
+        launch_residual_projection(M, ws.act, w.w_down[l], F, down_splits, ed, split, ws.ssq_full, DUO_PROF_DOWN, s);
     }
     if (many) {
         prof(DUO_PROF_LMHEAD, s);
         DUO_LAUNCH(last_row_operand_kernel, dim3(d / 32), dim3(64), s, ws.h, M - 1, PR, AT, ws.h_last);
-        const RowScale last{ws.ssq + (size_t)(M - 1) * NP, NP, 1.0f / (float)d, c.rms_eps, down_split ? ws.ssq_full + (size_t)(M - 1) * RowScale::FULL_PARTS : nullptr};
+        const RowScale last{ws.ssq + (size_t)(M - 1) * NP, NP, 1.0f / (float)d, c.rms_eps, ws.ssq_full + (size_t)(M - 1) * RowScale::FULL_PARTS};
         EpiStoreF32 el{V, 1, 2, logits, V};
         launch_projection<2>(DUO_PROF_LMHEAD, 1, ws.h_last, w.lm_head, d, (V + 31) / 32, last, el, s);
         return;
     }
     if (stats) {
         EpiLogitsStats el{V, M, 2, logits, V, ws.stats_rows, ws.stats_parts, temperature};
-        launch_projection<2>(DUO_PROF_LMHEAD, M, ws.h, w.lm_head, d, (V + 31) / 32, down_split ? norm_full : norm_part, el, s);
+        launch_projection<2>(DUO_PROF_LMHEAD, M, ws.h, w.lm_head, d, (V + 31) / 32, down_full ? norm_full : norm_part, el, s);
     } else {
         EpiStoreF32 el{V, M, 2, logits, V};
-        launch_projection<2>(DUO_PROF_LMHEAD, M, ws.h, w.lm_head, d, (V + 31) / 32, down_split ? norm_full : norm_part, el, s);
+        launch_projection<2>(DUO_PROF_LMHEAD, M, ws.h, w.lm_head, d, (V + 31) / 32, down_full ? norm_full : norm_part, el, s);
     }
 }
 

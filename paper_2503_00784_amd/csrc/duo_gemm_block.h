@@ -42,21 +42,6 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
     const int row_tile0 = blockIdx.z * BMT, band0 = blockIdx.x * BNT;
     const int row0 = row_tile0 * 16, nrows = quads * 4;
 
-    // RMSNorm factors of this block's rows (all five waves)
-    if (rsc.full) {
-        for (int i = threadIdx.x; i < BMT * 16; i += 320) {
-            const int m = row0 + i;
-            row_scale[i] = m < nrows ? 1.0f / sqrtf(rsc.full_row(m) * rsc.inv_d + rsc.eps) : 0.f;
-        }
-    } else if (rsc.part) {
-        f32x4 rsv[RowScale::MAXQ];
-        const int rend = min(row0 + BMT * 16, nrows);
-        for (int r0 = row0 + wave * 8; r0 < rend; r0 += 5 * 8) {
-            rsc.load(rsv, r0, nrows, lane);
-            rsc.reduce(rsv, row_scale - row0, r0, nrows, lane);
-        }
-    }
-
     if (wave == 4) {
         // ---- producer: stage r goes to ring buffer r % 3; steps past the end re-read the last step
         const u32x4* xg = reinterpret_cast<const u32x4*>(X) + lane;
@@ -87,7 +72,7 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
         constexpr int WAIT_ALL_BUT_ONE_STAGE = (ST & 15) | ((ST >> 4) << 14) | (7 << 4) | (15 << 8);
         issue(0);
         issue(1);
-        __builtin_amdgcn_s_waitcnt(WAIT_ALL_BUT_ONE_STAGE & ~(15 << 8));  // and lgkmcnt(0): this wave's row scales are written
+        __builtin_amdgcn_s_waitcnt(WAIT_ALL_BUT_ONE_STAGE);
         __builtin_amdgcn_s_barrier();
         for (int r = 0; r < rounds; ++r) {
             issue(r + 2);  // its buffer was drained in round r - 1
@@ -100,6 +85,14 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
 
     // ---- consumers: wave (wm, wn) of the 2 x 2 grid
     epi.arm();
+    // RMSNorm factors of this block's rows, from whole-row sums of squares (many-row passes always have them), while the producer's
+    // first stages are on their way
+    if (rsc.full) {
+        for (int i = threadIdx.x; i < BMT * 16; i += 256) {
+            const int m = row0 + i;
+            row_scale[i] = m < nrows ? 1.0f / sqrtf(rsc.full_row(m) * rsc.inv_d + rsc.eps) : 0.f;
+        }
+    }
     const int wm = wave >> 1, wn = wave & 1;
     f32x4 acc[WM][WN];
 #pragma unroll
@@ -161,7 +154,7 @@ __global__ __launch_bounds__(320) void gemm_block_kernel(const u16* __restrict__
 #pragma unroll
     for (int m = 0; m < WM; ++m) {
         const int row = (row_tile0 + wm * WM + m) * 16 + (lane & 15);
-        const float rs = (rsc.part && row < nrows) ? row_scale[row - row0] : 1.f;
+        const float rs = (rsc.full && row < nrows) ? row_scale[row - row0] : 1.f;
 #pragma unroll
         for (int t = 0; t < WN; t += ENT) {
             const int band = band0 + wn * WN + t;

@@ -71,8 +71,8 @@ __global__ __launch_bounds__(256) void embed_kernel(const u16* __restrict__ embe
 // workgroup's whole column range (RowScale::full), which the consumer reads instead of 256 partials per row.
 // grid = (rows, P): workgroup (m, pt) takes columns pt * d/P .. of row m (d/P a multiple of 64; P <= FULL_PARTS),
 // NWV waves, eight consecutive channels per thread and turn; the loads of all
-// splits are issued together (S <= 8, indices beyond S re-read the last split and are not added).
-template <int NWV>
+// splits are issued together (S <= MAXS <= 8, indices beyond S re-read the last split and are not added).
+template <int NWV, int MAXS>
 __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* __restrict__ part, int S, size_t split_stride,
                                                                    float* __restrict__ x, const u16* __restrict__ gain,
                                                                    u16* __restrict__ h, int d, int pair_rows, int tiles,
@@ -83,9 +83,9 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* 
     for (int j8 = c0 + threadIdx.x * 8; j8 < c0 + cols; j8 += NWV * 64 * 8) {  // lanes leave in pairs
         float* xr = x + (size_t)m * d + j8;
         const float* pr = part + (size_t)m * d + j8;
-        f32x4 p0[8], p1[8];
+        f32x4 p0[MAXS], p1[MAXS];
 #pragma unroll
-        for (int sp = 0; sp < 8; ++sp) {
+        for (int sp = 0; sp < MAXS; ++sp) {
             const float* ps = pr + (size_t)(sp < S ? sp : S - 1) * split_stride;
             p0[sp] = *reinterpret_cast<const f32x4*>(ps);
             p1[sp] = *reinterpret_cast<const f32x4*>(ps + 4);
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* 
         Frag8 gv, hi, lo;
         gv.q = *reinterpret_cast<const u32x4*>(gain + j8);
 #pragma unroll
-        for (int sp = 0; sp < 8; ++sp) {
+        for (int sp = 0; sp < MAXS; ++sp) {
             if (sp < S) {
                 a0 += p0[sp];
                 a1 += p1[sp];
@@ -133,10 +133,38 @@ static inline void launch_residual_reduce(int M, const float* part, int S, size_
                                           hipStream_t s) {
     const int P = reduce_parts(M, d), cols = d / P;
     const dim3 grid(M, P);
-    if (cols <= 512) DUO_LAUNCH(residual_reduce_kernel<1>, grid, dim3(64), s, part, S, split_stride, x, gain, h, d, pair_rows, tiles, ssq_part, ssq_full);
-    else if (cols <= 1024) DUO_LAUNCH(residual_reduce_kernel<2>, grid, dim3(128), s, part, S, split_stride, x, gain, h, d, pair_rows, tiles, ssq_part, ssq_full);
-    else if (cols <= 2048) DUO_LAUNCH(residual_reduce_kernel<4>, grid, dim3(256), s, part, S, split_stride, x, gain, h, d, pair_rows, tiles, ssq_part, ssq_full);
-    else DUO_LAUNCH(residual_reduce_kernel<8>, grid, dim3(512), s, part, S, split_stride, x, gain, h, d, pair_rows, tiles, ssq_part, ssq_full);
+#define DUO_REDUCE(NWV, MAXS)                                                                                                  \
+    DUO_LAUNCH((residual_reduce_kernel<NWV, MAXS>), grid, dim3(NWV * 64), s, part, S, split_stride, x, gain, h, d, pair_rows, tiles, \
+               ssq_part, ssq_full)
+#define DUO_REDUCE_COLS(MAXS)                     \
+    do {                                          \
+        if (cols <= 512) DUO_REDUCE(1, MAXS);     \
+        else if (cols <= 1024) DUO_REDUCE(2, MAXS); \
+        else if (cols <= 2048) DUO_REDUCE(4, MAXS); \
+        else DUO_REDUCE(8, MAXS);                 \
+    } while (0)
+    // few splits (prompt chunks): no loads of splits that are not there
+    if (S <= 2) DUO_REDUCE_COLS(2);
+    else if (S <= 4) DUO_REDUCE_COLS(4);
+    else DUO_REDUCE_COLS(8);
+#undef DUO_REDUCE_COLS
+#undef DUO_REDUCE
+}
+
+// Whole-row sums of squares (RowScale::full) from the partial sums per 16-column tile that a one-kernel residual projection
+// leaves, one wave per row.  Without it every workgroup of the next projection adds up the partial sums of its 128 rows itself, four
+// trips to memory at its start: gate/up of 512 rows (two rounds of workgroups) 205 us against 189 us + 3 us here.
+__global__ __launch_bounds__(256) void row_sums_kernel(const float* __restrict__ ssq_part, int n_part, int M, float* __restrict__ ssq_full) {
+    const int m = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (m >= M) return;
+    const f32x4* row = reinterpret_cast<const f32x4*>(ssq_part + (size_t)m * n_part);
+    float s = 0.f;
+    for (int q = lane; q < (n_part >> 2); q += 64) {
+        const f32x4 v = row[q];
+        s += (v.x + v.y) + (v.z + v.w);
+    }
+    s = wave_sum(s);
+    if (lane < RowScale::FULL_PARTS) ssq_full[(size_t)m * RowScale::FULL_PARTS + lane] = lane == 0 ? s : 0.f;
 }
 
 // Second half of a Q/K/V projection whose K range was split over workgroups (64 rows and more: each workgroup then
