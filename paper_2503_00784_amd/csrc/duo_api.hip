@@ -305,12 +305,11 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, int sp
 }
 
 template <int D>
-void launch_attention_shared(int mtw, int nwv, int ksplit, dim3 grid, const AttnArgs& a, hipStream_t s) {
-    if (ksplit == 2 && nwv == 10) DUO_LAUNCH((attn_shared_kernel<D, 1, 10, 2>), grid, dim3(704), s, a);
-    else if (mtw == 2) DUO_LAUNCH((attn_shared_kernel<D, 2, 7>), grid, dim3(512), s, a);  // 8 waves: 256 registers each
-    else if (ksplit == 2 && nwv == 8) DUO_LAUNCH((attn_shared_kernel<D, 1, 8, 2>), grid, dim3(576), s, a);
-    else if (ksplit == 2) DUO_LAUNCH((attn_shared_kernel<D, 1, 4, 2>), grid, dim3(320), s, a);
-    else DUO_LAUNCH((attn_shared_kernel<D, 1, 8>), grid, dim3(576), s, a);
+void launch_attention_shared(int nwv, int ksplit, dim3 grid, const AttnArgs& a, hipStream_t s) {
+    if (ksplit == 2 && nwv == 10) DUO_LAUNCH((attn_shared_kernel<D, 10, 2>), grid, dim3(704), s, a);
+    else if (ksplit == 2 && nwv == 8) DUO_LAUNCH((attn_shared_kernel<D, 8, 2>), grid, dim3(576), s, a);
+    else if (ksplit == 2) DUO_LAUNCH((attn_shared_kernel<D, 4, 2>), grid, dim3(320), s, a);
+    else DUO_LAUNCH((attn_shared_kernel<D, 8, 1>), grid, dim3(576), s, a);
 }
 
 // The target pass over the rows of `plan`: fills the cache slots P .. P+M-1 and writes fp32
@@ -360,37 +359,39 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     // Two or more query tiles per kv head: the kernel that stages K/V blocks in LDS for all query tiles
     // (two tiles on a short context stay with the per-wave kernel, which then needs no chunk merge).
     const bool shared_kv = MqT > 2 || (MqT == 2 && NB > 32);
-    int sh_mtw = 1, sh_nwv = 4, sh_zg = 1, sh_ksplit = 1;
+    int sh_nwv = 4, sh_zg = 1, sh_ksplit = 1;
     int nwv, bpw, nchunks;
     if (shared_kv) {
         // one query tile per wave, about 256 workgroups (one per compute unit): measured best for 4 tiles x 32 heads and 16 tiles x 8 heads
         // Up to four tiles: two teams of waves share the blocks (two waves per SIMD: 20.7 against 23.2 us at 4 tiles,
         // 11.8 against 14.4 us at 2 tiles, measured on 32 heads x 4160 / 2080 keys).
-        sh_mtw = many && MqT > 16 ? 2 : 1;
         // 9..16 tiles (64 rows x a GQA group of 4): 27.3 against 28.2 us at 8192 keys; 17..20 tiles (65..80 rows) in the same shape
-        // against two tiles per wave: 33.8 against 43.4 us at 8192 keys, 14.1 against 18.6 at 2048, 10.9 against 13.4 at 700
-        sh_ksplit = (MqT <= 4 || (MqT > 8 && sh_mtw == 1)) ? 2 : 1;
-        sh_nwv = sh_mtw == 2 ? 7 : (MqT > 2 ? 8 : 4);
+        // against two tiles per wave: 33.8 against 43.4 us at 8192 keys, 14.1 against 18.6 at 2048, 10.9 against 13.4 at 700.
+        // Prompt chunks likewise, in one chunk of keys where there are enough row groups: 70 against 93 + 14 us (chunk merge) for
+        // 1024 rows behind 1024 keys on 32 heads, 75 against 96 + 25 us on 8 heads x 4.
+        sh_ksplit = (MqT <= 4 || MqT > 8 || many) ? 2 : 1;
+        sh_nwv = MqT > 2 ? 8 : 4;
         if (MqT == 5 && NB >= 64) {
             // five tiles (65..80 rows of a head without a group) on a long context: two teams of five against eight waves of which
             // five have a tile, 25.9 -> 22.3 us on 32 heads x 4161 keys, 17.9 -> 17.3 at 2127 (at 577 keys 9.1 -> 10.3: not there)
             sh_ksplit = 2;
             sh_nwv = 10;
         }
-        sh_zg = (MqT + (sh_nwv / sh_ksplit) * sh_mtw - 1) / ((sh_nwv / sh_ksplit) * sh_mtw);
+        sh_zg = (MqT + sh_nwv / sh_ksplit - 1) / (sh_nwv / sh_ksplit);
         // LDS (teams) or registers (nine waves) leave room for one workgroup per compute unit, so no more than 256 of them (40
         // heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us)
         int target = 256 / (Hkv * sh_zg);
         target = target < 1 ? 1 : (target > max_chunks ? max_chunks : target);
         if (many) {
-            // many row groups: the chunk count that leaves the fewest compute units idle in the last round of
-            // workgroups (160 (head, row group) pairs: 3 chunks = 480 workgroups, not 2 = 320), few chunks preferred
-            float best = -1.f;
+            // the chunk count that costs least: rounds of workgroups times (5 us + 1.15 us per ring stage of two blocks), and for
+            // more than one chunk the merge, 4 us and the time of writing and reading its input
+            float best = 1e30f;
             for (int t = 1; t <= max_chunks; ++t) {
-                const int wgs = Hkv * sh_zg * t;
-                const float eff = (float)wgs / (float)((wgs + 255) / 256 * 256) - 0.04f * (float)t;
-                if (eff > best) {
-                    best = eff;
+                const int stages = ((NB + t - 1) / t + 1) / 2;
+                const float cost = (float)((Hkv * sh_zg * t + 255) / 256) * (5.f + 1.15f * (float)stages) +
+                                   (t > 1 ? 4.f + 2e-6f * (float)t * (float)MQ * (float)Hkv * (float)D : 0.f);
+                if (cost < best) {
+                    best = cost;
                     target = t;
                 }
             }
@@ -460,8 +461,8 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         prof(DUO_PROF_ATTN, s);
         if (shared_kv) {
             const dim3 grid(nchunks, Hkv, sh_zg);
-            if (D == 128) launch_attention_shared<128>(sh_mtw, sh_nwv, sh_ksplit, grid, aa, s);
-            else launch_attention_shared<64>(sh_mtw, sh_nwv, sh_ksplit, grid, aa, s);
+            if (D == 128) launch_attention_shared<128>(sh_nwv, sh_ksplit, grid, aa, s);
+            else launch_attention_shared<64>(sh_nwv, sh_ksplit, grid, aa, s);
         } else if (NB <= 32 && MqT == 1) {  // short context, one query tile: the no-loop kernel
             if (D == 128) DUO_LAUNCH((attn_small_kernel<128, 4>), dim3(1, Hkv), dim3(512), s, aa);
             else DUO_LAUNCH((attn_small_kernel<64, 4>), dim3(1, Hkv), dim3(512), s, aa);

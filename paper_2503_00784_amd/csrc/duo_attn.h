@@ -510,7 +510,7 @@ __global__ __launch_bounds__(512) void attn_small_kernel(AttnArgs a) {
 // registers beyond two tiles, so more tiles meant more workgroups re-reading the same keys.  Here it is
 // the other way round: a workgroup takes one (kv head, key chunk); each 32-key block of K and V^T is put
 // in LDS once, in MFMA operand layout (the same 1 KiB tiles the other kernels load straight into
-// registers), and each of the NWV consumer waves owns MTW query tiles and runs over all blocks of the
+// registers), and each of the NWV consumer waves owns one query tile and runs over all blocks of the
 // chunk, so nothing is merged between waves.  One extra wave does nothing but move the blocks: 16-byte
 // global -> LDS loads (no registers, no LDS store instructions) into a ring of three buffers, two blocks
 // ahead of the MFMAs; its barriers are bare s_barrier instructions behind a counted wait.  One barrier per
@@ -530,7 +530,7 @@ __device__ __forceinline__ void wait_vector_loads_but() {  // vmcnt(N); expcnt a
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-template <int D, int MTW, int NWV, int KSPLIT = 1>
+template <int D, int NWV, int KSPLIT>
 __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a) {
     constexpr int KS = D / 32, DT = D / 16;
     constexpr int KT = 2 * KS;      // K tiles per block (2 key halves x KS)
@@ -539,7 +539,7 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     constexpr int TW = NWV / KSPLIT;  // query-tile waves per team
     constexpr int STL = KSPLIT * TILES;  // tiles per ring stage: one block for every team
     static_assert(STL <= 63, "a stage's loads fit the producer's memory counter");
-    static_assert(NWV % KSPLIT == 0 && (KSPLIT == 1 || MTW == 1), "teams of equal size; one query tile per wave when the blocks are dealt to teams");
+    static_assert(NWV % KSPLIT == 0, "teams of equal size");
     __shared__ u32x4 lds_kv[NBUF][STL * 64];
     __shared__ f32x4 lds_team_o[KSPLIT > 1 ? (KSPLIT - 1) * TW * DT * 64 : 1];
     __shared__ float lds_team_ml[KSPLIT > 1 ? (KSPLIT - 1) * TW * 2 * 64 : 1];
@@ -557,7 +557,7 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     {
         // No row sees a key behind its own slot: the blocks behind the slot of this workgroup's last query row
         // are masked for all of its rows and are left out (a prompt chunk's early rows skip the chunk's late keys).
-        const int r_last = min(a.plan.M * a.group, (zg + 1) * TW * MTW * 16) - 1;
+        const int r_last = min(a.plan.M * a.group, (zg + 1) * TW * 16) - 1;
         const int nb_vis = (a.plan.P + r_last / a.group) / 32 + 1 - b0;
         nb = nb_vis < nb ? (nb_vis < 0 ? 0 : nb_vis) : nb;
     }
@@ -634,36 +634,30 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     // ---- consumers
     const int MQ = a.plan.M * a.group;
     const int team = wave / TW, tw = wave - team * TW;
-    const int tile0 = (zg * TW + tw) * MTW;  // first query tile of this wave
-    elem8 qf[MTW][KS], ql[MTW][KS];
-    int vis_lo[MTW], vis_hi[MTW];
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        const int r = (tile0 + mt) * 16 + c;
+    const int tile = zg * TW + tw;  // this wave's query tile
+    elem8 qf[KS], ql[KS];
+    int vis_lo, vis_hi;
+    {
+        const int r = tile * 16 + c;
         const bool ok = r < MQ;
         const int m = ok ? r / a.group : 0, gq = ok ? r % a.group : 0;
         const int R = a.plan.R;
-        vis_lo[mt] = !ok ? 0x7fffffff : (m < R ? 0 : R + ((m - R) / a.plan.k) * a.plan.k);
-        vis_hi[mt] = ok ? m : -1;
+        vis_lo = !ok ? 0x7fffffff : (m < R ? 0 : R + ((m - R) / a.plan.k) * a.plan.k);
+        vis_hi = ok ? m : -1;
         const u16* qp = a.q + (size_t)m * a.ldq + (hk * a.group + gq) * D + g * 8;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             Frag8 f;
             f.q = ok ? *reinterpret_cast<const u32x4*>(qp + ks * 32) : u32x4{0u, 0u, 0u, 0u};
-            qf[mt][ks] = f.v;
+            qf[ks] = f.v;
             f.q = ok ? *reinterpret_cast<const u32x4*>(qp + a.q_plane + ks * 32) : u32x4{0u, 0u, 0u, 0u};
-            ql[mt][ks] = f.v;
+            ql[ks] = f.v;
         }
     }
-    f32x4 o[MTW][DT];
-    float m_run[MTW], l_run[MTW];
+    f32x4 o[DT];
+    float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        m_run[mt] = -INFINITY;
-        l_run[mt] = 0.f;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) o[mt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+    for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     auto use_block = [&](const u32x4* buf, int kb) {
         const bool masked = kb + 32 > a.plan.P;  // block touches draft slots or the end
         const bool tail = kb + 32 > a.Ktot;      // slots at or beyond Ktot may hold anything: zero their V
@@ -672,59 +666,51 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
             f.q = buf[j * 64 + lane];
             return f;
         };
-        float scs[MTW][8];
+        float sc[8];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             elem8 kf[KS];
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) kf[ks] = frag(t * KS + ks).v;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};  // lo and hi query parts into one accumulator; the scale comes with the exponent
 #pragma unroll
-            for (int mt = 0; mt < MTW; ++mt) {  // lo and hi query parts into one accumulator; the scale comes with the exponent
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) {
-                    acc = mfma16(kf[ks], ql[mt][ks], acc);
-                    acc = mfma16(kf[ks], qf[mt][ks], acc);
-                }
-#pragma unroll
-                for (int i = 0; i < 4; ++i) scs[mt][t * 4 + i] = acc[i];
+            for (int ks = 0; ks < KS; ++ks) {
+                acc = mfma16(kf[ks], ql[ks], acc);
+                acc = mfma16(kf[ks], qf[ks], acc);
             }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sc[t * 4 + i] = acc[i];
         }
-        Frag8 pf[MTW], pl[MTW];
-        float alpha[MTW];
-#pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-            float* sc = scs[mt];
-            if (masked) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int mk = kb + g * 8 + j - a.plan.P;
-                    const bool vis = (mk < a.plan.R) | ((mk >= vis_lo[mt]) & (mk <= vis_hi[mt]));
-                    sc[j] = vis ? sc[j] : -INFINITY;
-                }
-            }
-            float bm = sc[0];
-#pragma unroll
-            for (int j = 1; j < 8; ++j) bm = fmaxf(bm, sc[j]);
-            bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
-            bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
-            const float m_new = fmaxf(m_run[mt], bm * a.scale_log2);  // the running maximum is kept in scaled units
-            const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-            alpha[mt] = exp2_raw(m_run[mt] - m_safe);
-            m_run[mt] = m_new;
-            float pw[8], ps = 0.f;
+        Frag8 pf, pl;
+        if (masked) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                pw[j] = exp2_raw(fmaf(sc[j], a.scale_log2, -m_safe));
-                ps += pw[j];
+                const int mk = kb + g * 8 + j - a.plan.P;
+                const bool vis = (mk < a.plan.R) | ((mk >= vis_lo) & (mk <= vis_hi));
+                sc[j] = vis ? sc[j] : -INFINITY;
             }
-            split_elem8(pw, pf[mt].q, pl[mt].q);  // softmax weights as bf16 pairs (hi + lo)
-            l_run[mt] = l_run[mt] * alpha[mt] + ps;
-            // the running maximum rarely moves after the first blocks: rescale only when some row's did
-            if (__ballot(alpha[mt] != 1.0f) != 0) {
+        }
+        float bm = sc[0];
 #pragma unroll
-                for (int dt = 0; dt < DT; ++dt) o[mt][dt] = o[mt][dt] * alpha[mt];
-            }
+        for (int j = 1; j < 8; ++j) bm = fmaxf(bm, sc[j]);
+        bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
+        bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
+        const float m_new = fmaxf(m_run, bm * a.scale_log2);  // the running maximum is kept in scaled units
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = exp2_raw(m_run - m_safe);
+        m_run = m_new;
+        float pw[8], ps = 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            pw[j] = exp2_raw(fmaf(sc[j], a.scale_log2, -m_safe));
+            ps += pw[j];
+        }
+        split_elem8(pw, pf.q, pl.q);  // softmax weights as bf16 pairs (hi + lo)
+        l_run = l_run * alpha + ps;
+        // the running maximum rarely moves after the first blocks: rescale only when some row's did
+        if (__ballot(alpha != 1.0f) != 0) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[dt] = o[dt] * alpha;
         }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
@@ -734,18 +720,15 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
                 for (int e = 0; e < 8; ++e)
                     if (kb + g * 8 + e >= a.Ktot) vf.h[e] = 0;
             }
-#pragma unroll
-            for (int mt = 0; mt < MTW; ++mt) {
-                f32x4 acc = mfma16(vf.v, pl[mt].v, o[mt][dt]);
-                o[mt][dt] = mfma16(vf.v, pf[mt].v, acc);
-            }
+            const f32x4 acc = mfma16(vf.v, pl.v, o[dt]);
+            o[dt] = mfma16(vf.v, pf.v, acc);
         }
     };
 
     // No row of this wave sees a key behind the slot of the wave's last query row: such blocks are masked for all of its
     // rows, so the wave leaves out their products and softmax (a prompt chunk's early rows against the chunk's late
     // keys: causal attention per query tile, not only per workgroup) and only keeps the ring's pace.
-    const int r_wave_last = min(MQ, (tile0 + MTW) * 16) - 1;
+    const int r_wave_last = min(MQ, (tile + 1) * 16) - 1;
     const int kb_last = r_wave_last >= 0 ? a.plan.P + r_wave_last / a.group : -1;  // key slot of that row
     __syncthreads();  // block 0 is in LDS
     for (int st = 0; st < nst; ++st) {
@@ -759,9 +742,9 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
         if (team > 0) {
             const int slot = (team - 1) * TW + tw;
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) lds_team_o[(slot * DT + dt) * 64 + lane] = o[0][dt];
-            lds_team_ml[(slot * 2 + 0) * 64 + lane] = m_run[0];
-            lds_team_ml[(slot * 2 + 1) * 64 + lane] = l_run[0];
+            for (int dt = 0; dt < DT; ++dt) lds_team_o[(slot * DT + dt) * 64 + lane] = o[dt];
+            lds_team_ml[(slot * 2 + 0) * 64 + lane] = m_run;
+            lds_team_ml[(slot * 2 + 1) * 64 + lane] = l_run;
         }
         __syncthreads();
         if (team > 0) return;
@@ -769,43 +752,38 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
         for (int z = 1; z < KSPLIT; ++z) {  // team order
             const int slot = (z - 1) * TW + tw;
             const float mz = lds_team_ml[(slot * 2 + 0) * 64 + lane], lz = lds_team_ml[(slot * 2 + 1) * 64 + lane];
-            const float m_new = fmaxf(m_run[0], mz);
+            const float m_new = fmaxf(m_run, mz);
             const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-            const float s0 = exp2f(m_run[0] - m_safe), sz = exp2f(mz - m_safe);  // exp2(-inf) = 0: an empty state adds nothing
-            m_run[0] = m_new;
-            l_run[0] = l_run[0] * s0 + lz * sz;
+            const float s0 = exp2f(m_run - m_safe), sz = exp2f(mz - m_safe);  // exp2(-inf) = 0: an empty state adds nothing
+            m_run = m_new;
+            l_run = l_run * s0 + lz * sz;
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) o[0][dt] = o[0][dt] * s0 + lds_team_o[(slot * DT + dt) * 64 + lane] * sz;
+            for (int dt = 0; dt < DT; ++dt) o[dt] = o[dt] * s0 + lds_team_o[(slot * DT + dt) * 64 + lane] * sz;
         }
     }
 
+    l_run += __shfl_xor(l_run, 16, 64);
+    l_run += __shfl_xor(l_run, 32, 64);
+    const int r = tile * 16 + c;
+    if (r >= MQ) return;
+    if (a.nchunks == 1) {
+        const int m = r / a.group, col0 = (hk * a.group + r % a.group) * D;
+        const float inv = 1.0f / l_run;
 #pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        l_run[mt] += __shfl_xor(l_run[mt], 16, 64);
-        l_run[mt] += __shfl_xor(l_run[mt], 32, 64);
-        const int r = (tile0 + mt) * 16 + c;
-        if (r >= MQ) continue;
-        if (a.nchunks == 1) {
-            const int m = r / a.group, col0 = (hk * a.group + r % a.group) * D;
-            const float inv = 1.0f / l_run[mt];
+        for (int dt = 0; dt < DT; ++dt) {  // four consecutive channels: 8 bytes of an operand chunk
+            u32x2 hi, lo;
+            split_elem4(o[dt] * inv, hi, lo);
+            const int col = col0 + dt * 16 + g * 4;
+            *reinterpret_cast<u32x2*>(a.out + operand_offset(m, col, a.out_tiles)) = hi;
+            *reinterpret_cast<u32x2*>(a.out + operand_offset(a.pair_rows + m, col, a.out_tiles)) = lo;
+        }
+    } else {
+        float* pp = a.part + (((size_t)hk * a.mq_pad + r) * a.nchunks + cb) * (D + 4);
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float v = o[mt][dt][i] * inv;
-                    const u16 hi = f32_to_elem(v);
-                    const int col = col0 + dt * 16 + g * 4 + i;
-                    a.out[operand_offset(m, col, a.out_tiles)] = hi;
-                    a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = f32_to_elem(v - elem_to_f32(hi));
-                }
-        } else {
-            float* pp = a.part + (((size_t)hk * a.mq_pad + r) * a.nchunks + cb) * (D + 4);
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(pp + dt * 16 + g * 4) = o[mt][dt];
-            if (g == 0) {
-                pp[D] = m_run[mt];
-                pp[D + 1] = l_run[mt];
-            }
+        for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(pp + dt * 16 + g * 4) = o[dt];
+        if (g == 0) {
+            pp[D] = m_run;
+            pp[D + 1] = l_run;
         }
     }
 }
