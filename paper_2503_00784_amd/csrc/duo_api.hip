@@ -329,23 +329,22 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     // (embedding gather, K-split reduce) and the consumer is the LDS-shared kernel, which reads them directly.
     const RowScale norm_part{ws.ssq, NP, 1.0f / (float)d, c.rms_eps, nullptr};
     const RowScale norm_full{ws.ssq, NP, 1.0f / (float)d, c.rms_eps, ws.ssq_full};
-    // partial results of split residual projections: their own part of the workspace, or the nucleus search's rows, which are idle
-    // until the pass has left its logits, where those are larger
-    const size_t idle_floats = (size_t)(DUO_MAX_ROWS + 1) * V * 2;
+    const bool many = M > DUO_MAX_ROWS;  // prefill pass: logits of the last row only (to logits[0 .. V))
+    // partial results of split residual projections: their own part of the workspace, or in a prompt chunk the nucleus search's
+    // rows, which are idle then, where those are larger (up to 80 rows the Q/K/V projection's partial results lie in the same place,
+    // which the caches then hold)
+    const size_t idle_floats = many ? (size_t)(DUO_MAX_ROWS + 1) * V * 2 : 0;
     float* const split = ws.split_floats >= idle_floats ? ws.split : reinterpret_cast<float*>(ws.p_rows);
     const size_t split_floats = std::max(ws.split_floats, idle_floats);
     const int o_splits = residual_splits(M, qd, d, split_floats), down_splits = residual_splits(M, F, d, split_floats);
-    const bool many = M > DUO_MAX_ROWS;  // prefill pass: logits of the last row only (to logits[0 .. V))
     const bool o_full = many || o_splits > 1, down_full = many || down_splits > 1;  // whole-row sums of squares behind it
     const int max_chunks = many ? MAX_CHUNKS_MANY_ROWS : MAX_CHUNKS;
     const bool stats = temperature >= 0.0;
     const bool root_stats = stats && plan.R == 0;
     prof(DUO_PROF_SETUP, s);
-    DUO_LAUNCH(rope_table_kernel, dim3(M + (root_stats ? ROOT_STATS_PARTS : 0)), dim3(256), s, plan, D, (double)c.rope_theta, ws.rope_c,
-               ws.rope_s, status, RootStatsArgs{root_stats ? cache.root_logits : nullptr, V, temperature, ws.stats_root});
-    prof(DUO_PROF_SETUP, s);
-    DUO_LAUNCH(embed_kernel, dim3(M), dim3(256), s, w.embed, tokens, root_token, plan, V, cache.prefix_len,
-                       status, ws.x, w.g_attn[0], ws.h, d, PR, AT, ws.ssq, ws.ssq_full);
+    DUO_LAUNCH(setup_kernel, dim3(M + (root_stats ? ROOT_STATS_PARTS : 0)), dim3(256), s, w.embed, tokens, root_token, plan, V,
+               cache.prefix_len, status, ws.x, w.g_attn[0], ws.h, d, PR, AT, ws.ssq, ws.ssq_full, D, (double)c.rope_theta, ws.rope_c,
+               ws.rope_s, RootStatsArgs{root_stats ? cache.root_logits : nullptr, V, temperature, ws.stats_root});
 
     // Attention launch shape.  Short contexts: one workgroup of 8 waves per (kv head, row group) does
     // the whole head and writes the output itself.  Long contexts: the keys are cut into chunks for

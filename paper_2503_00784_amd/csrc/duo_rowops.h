@@ -20,46 +20,85 @@ __device__ __forceinline__ void block_row_sum(float v, float* wsum, float* out) 
     }
 }
 
-// x[m] = E[token_m], plus what the first RMSNorm needs (see RowScale in duo_gemm.h): u = x * gain as
-// bf16 pairs in the QKV projection's operand buffer and the per-tile partial sums of x^2.  Also the
-// device-side input checks: token ids in range, device prefix length equal to the host's.
-// One workgroup (256 threads) per row; a thread handles runs of eight consecutive channels.
-__global__ __launch_bounds__(256) void embed_kernel(const u16* __restrict__ embed, const int32_t* __restrict__ tokens,
-                                                     int root_token, RowPlan plan, int vocab, const int32_t* prefix_len,
-                                                     int32_t* status, float* __restrict__ x, const u16* __restrict__ gain,
-                                                     u16* __restrict__ h, int d, int pair_rows, int tiles,
-                                                     float* __restrict__ ssq_part, float* __restrict__ ssq_full) {
+// The first kernel of a pass, one workgroup (256 threads) per row and more for the root statistics:
+//   - x[m] = E[token_m], plus what the first RMSNorm needs (see RowScale in duo_gemm.h): u = x * gain as bf16 pairs in the QKV
+//     projection's operand buffer, the per-tile partial sums of x^2 and the whole row's; runs of eight channels per thread;
+//   - the row's rotary factors: cos/sin of pos(m) * theta^(-2d/D), evaluated in double and rounded once to fp32;
+//   - workgroup 0: the device-side input checks (token ids in range, device prefix length equal to the host's) into the status
+//     word, which the kernels after this one only read;
+//   - for a pass that will be followed by sampling from cached root logits (root.logits != nullptr), the last ROOT_STATS_PARTS
+//     workgroups leave the softmax statistics of those logits, slice by slice (see SampleArgs in duo_sample.h): work that is off
+//     the critical path here and would otherwise need a launch of its own.
+// One launch instead of two (a launch costs a small model 4 us of 98).
+struct RootStatsArgs {
+    const float* logits;  // fp32 [V], or nullptr: no statistics wanted
+    int V;
+    double T;
+    double* out;  // [ROOT_STATS_PARTS][2]
+};
+
+__global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embed, const int32_t* __restrict__ tokens, int root_token,
+                                                     RowPlan plan, int vocab, const int32_t* prefix_len, int32_t* status,
+                                                     float* __restrict__ x, const u16* __restrict__ gain, u16* __restrict__ h, int d,
+                                                     int pair_rows, int tiles, float* __restrict__ ssq_part, float* __restrict__ ssq_full,
+                                                     int D, double theta, float* __restrict__ rc, float* __restrict__ rs, RootStatsArgs root) {
     __shared__ float wsum[4];
+    __shared__ double sm[16];
     const int m = blockIdx.x;
-    float total = 0.f;
-    if (m == 0 && threadIdx.x == 0 && prefix_len && status && *prefix_len != plan.P)
-        atomicOr(status, 2);
-    int tok = m < plan.R ? root_token : tokens[m - plan.R];
-    if (tok < 0 || tok >= vocab) {
-        if (threadIdx.x == 0 && status) atomicOr(status, 1);
-        tok = tok < 0 ? 0 : vocab - 1;
+    if (m >= plan.M) {  // statistics of one slice of the root logits
+        if (!root.logits) return;
+        const int sl = m - plan.M, len = (root.V + ROOT_STATS_PARTS - 1) / ROOT_STATS_PARTS;
+        const int v0 = sl * len, v1 = min(root.V, v0 + len);
+        double zmax, Z;
+        slice_stats(root.logits, v0, v1, root.T, sm, zmax, Z);
+        if (threadIdx.x == 0) {
+            root.out[2 * sl] = zmax;
+            root.out[2 * sl + 1] = Z;
+        }
+        return;
     }
+    if (m == 0 && status) {
+        int bad = 0;
+        for (int i = threadIdx.x; i < plan.M; i += 256) {
+            const int t = i < plan.R ? root_token : tokens[i - plan.R];
+            bad |= t < 0 || t >= vocab;
+        }
+        bad = __syncthreads_or(bad);
+        if (threadIdx.x == 0) *status = (bad ? 1 : 0) | (prefix_len && *prefix_len != plan.P ? 2 : 0);
+    }
+    int tok = m < plan.R ? root_token : tokens[m - plan.R];
+    tok = tok < 0 ? 0 : (tok >= vocab ? vocab - 1 : tok);
     const u16* e = embed + (size_t)tok * d;
     float* xr = x + (size_t)m * d;
+    float total = 0.f;
     for (int j8 = threadIdx.x * 8; j8 < d; j8 += 256 * 8) {
         Frag8 ev, gv, hi, lo;
         ev.q = *reinterpret_cast<const u32x4*>(e + j8);
         gv.q = *reinterpret_cast<const u32x4*>(gain + j8);
         float sq = 0.f;
+        f32x4 xv[2];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float xv = elem_to_f32(ev.h[j]);
-            xr[j8 + j] = xv;
-            sq += xv * xv;
-            const float u = xv * elem_to_f32(gv.h[j]);
+            const float v = elem_to_f32(ev.h[j]);
+            xv[j >> 2][j & 3] = v;
+            sq += v * v;
+            const float u = v * elem_to_f32(gv.h[j]);
             hi.h[j] = f32_to_elem(u);
             lo.h[j] = f32_to_elem(u - elem_to_f32(hi.h[j]));
         }
+        *reinterpret_cast<f32x4*>(xr + j8) = xv[0];
+        *reinterpret_cast<f32x4*>(xr + j8 + 4) = xv[1];
         *reinterpret_cast<u32x4*>(h + operand_offset(m, j8, tiles)) = hi.q;
         *reinterpret_cast<u32x4*>(h + operand_offset(pair_rows + m, j8, tiles)) = lo.q;
         total += sq;
         sq += __shfl_xor(sq, 1, 64);  // two runs of eight = one 16-column tile
         if (!(threadIdx.x & 1)) ssq_part[(size_t)m * (d >> 4) + (j8 >> 4)] = sq;
+    }
+    const int half = D / 2;
+    for (int i = threadIdx.x; i < half; i += 256) {
+        const double ang = (double)plan.pos(m) * pow(theta, -2.0 * (double)i / (double)D);
+        rc[m * half + i] = (float)cos(ang);
+        rs[m * half + i] = (float)sin(ang);
     }
     block_row_sum<4>(total, wsum, ssq_full + (size_t)m * RowScale::FULL_PARTS);  // one range: the whole row
     if (threadIdx.x >= 1 && threadIdx.x < RowScale::FULL_PARTS) ssq_full[(size_t)m * RowScale::FULL_PARTS + threadIdx.x] = 0.f;
@@ -251,42 +290,6 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvFinishArgs a) {
             vp[v_cache_offset(D, a.plan.slot(m), dd)] = f32_to_elem(x_lo);
             vp[v_cache_offset(D, a.plan.slot(m), half + dd)] = f32_to_elem(x_hi);
         }
-    }
-}
-
-// cos/sin of pos(m) * theta^(-2d/D), evaluated in double and rounded once to fp32.  As the first kernel of a
-// pass it also clears the status word that the later kernels OR their flags into, and, for a pass that will be
-// followed by sampling from cached root logits (root.logits != nullptr), its last ROOT_STATS_PARTS workgroups leave the
-// softmax statistics of those logits, slice by slice (see SampleArgs in duo_sample.h): work that is off the
-// critical path here and would otherwise need a launch of its own.
-struct RootStatsArgs {
-    const float* logits;  // fp32 [V], or nullptr: no statistics wanted
-    int V;
-    double T;
-    double* out;  // [ROOT_STATS_PARTS][2]
-};
-
-__global__ __launch_bounds__(256) void rope_table_kernel(RowPlan plan, int D, double theta, float* __restrict__ rc,
-                                                          float* __restrict__ rs, int32_t* status, RootStatsArgs root) {
-    __shared__ double sm[16];
-    const int m = blockIdx.x, half = D / 2;
-    if (m == 0 && threadIdx.x == 0 && status) *status = 0;
-    if (m >= plan.M) {  // statistics of one slice of the root logits
-        if (!root.logits) return;
-        const int sl = m - plan.M, len = (root.V + ROOT_STATS_PARTS - 1) / ROOT_STATS_PARTS;
-        const int v0 = sl * len, v1 = min(root.V, v0 + len);
-        double zmax, Z;
-        slice_stats(root.logits, v0, v1, root.T, sm, zmax, Z);
-        if (threadIdx.x == 0) {
-            root.out[2 * sl] = zmax;
-            root.out[2 * sl + 1] = Z;
-        }
-        return;
-    }
-    for (int d = threadIdx.x; d < half; d += blockDim.x) {
-        const double ang = (double)plan.pos(m) * pow(theta, -2.0 * (double)d / (double)D);
-        rc[m * half + d] = (float)cos(ang);
-        rs[m * half + d] = (float)sin(ang);
     }
 }
 
