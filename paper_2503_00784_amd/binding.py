@@ -232,6 +232,30 @@ def _stream_ptr():
     return torch.cuda.current_stream().cuda_stream
 
 
+class _Results:
+    """The integer results of a call, one device buffer (one fill, one copy to the host) seen as the tensors of duo_result;
+    `extra` more words behind them."""
+
+    def __init__(self, max_n: int, device, extra: int = 0):
+        import torch
+        self.max_n = max_n
+        self.buffer = torch.zeros(2 * max_n + 5 + extra, dtype=torch.int32, device=device)
+        self.accept_len, self.next_token = self.buffer[:max_n], self.buffer[max_n:2 * max_n]
+        self.commit, self.status = self.buffer[2 * max_n:2 * max_n + 4], self.buffer[2 * max_n + 4:2 * max_n + 5]
+        self.extra = self.buffer[2 * max_n + 5:]
+
+    def c(self, logits_out=None) -> Result:
+        return Result(self.accept_len.data_ptr(), self.next_token.data_ptr(), self.commit.data_ptr(), self.status.data_ptr(),
+                      _ptr(logits_out))
+
+    def fetch(self, n: int):
+        """(results of the first n sequences, the extra words), after a copy that waits for the current stream."""
+        h, m = self.buffer.cpu().numpy(), self.max_n
+        c = h[2 * m:2 * m + 4]
+        return {"accept_len": h[:n].copy(), "next_token": h[m:m + n].copy(), "selected": int(c[0]), "commit_len": int(c[1]),
+                "commit_token": int(c[2]), "new_prefix_len": int(c[3]), "status": int(h[2 * m + 4])}, h[2 * m + 5:]
+
+
 _LAYER_KEYS = ("wqkv", "wo", "w_gate_up", "w_down", "g_attn", "g_ffn")
 
 
@@ -320,16 +344,14 @@ class VerifyEngine:
         # planes of max_seq * D elements in the library's tiled layouts (see k_rows_to_tiles / v_rows_to_tiles)
         self.k = torch.zeros((L, H, max_seq * D), dtype=torch.int16, device=device)
         self.vT = torch.zeros((L, H, max_seq * D), dtype=torch.int16, device=device)
-        self.prefix_len = torch.zeros(1, dtype=torch.int32, device=device)
+        self.outputs = _Results(DUO_MAX_ROWS, device, extra=1)
+        self.accept_len, self.next_token = self.outputs.accept_len, self.outputs.next_token
+        self.commit, self.status, self.prefix_len = self.outputs.commit, self.outputs.status, self.outputs.extra
         self.root_logits = torch.zeros(shape.vocab, dtype=torch.float32, device=device)
         # verify calls take up to DUO_MAX_ROWS rows, prefill chunks up to DUO_MAX_PREFILL_ROWS (a larger workspace)
         self.max_prefill_rows = max(int(max_prefill_rows), min(int(max_rows), DUO_MAX_ROWS))
         self.ws_bytes = max(workspace_bytes(self.cfg, min(max_rows, DUO_MAX_ROWS)), workspace_bytes(self.cfg, self.max_prefill_rows))
         self.workspace = torch.zeros(self.ws_bytes, dtype=torch.uint8, device=device)
-        self.accept_len = torch.zeros(DUO_MAX_ROWS, dtype=torch.int32, device=device)
-        self.next_token = torch.zeros(DUO_MAX_ROWS, dtype=torch.int32, device=device)
-        self.commit = torch.zeros(4, dtype=torch.int32, device=device)
-        self.status = torch.zeros(1, dtype=torch.int32, device=device)
         self.cache_c = KVCache(self.k.data_ptr(), self.vT.data_ptr(), self.prefix_len.data_ptr(),
                                self.root_logits.data_ptr())
         self.host_prefix_len = 0
@@ -382,8 +404,7 @@ class VerifyEngine:
         draft_tokens int32 [n][k], draft_probs fp32 [n][k][V], uniforms fp32 [n][k+1]."""
         n, k = draft_tokens.shape
         call = Call(n, k, float(temperature), int(select_mode), int(root_token), self.host_prefix_len, float(top_p))
-        res = Result(self.accept_len.data_ptr(), self.next_token.data_ptr(), self.commit.data_ptr(),
-                     self.status.data_ptr(), _ptr(logits_out))
+        res = self.outputs.c(logits_out)
         rc = self.lib.duo_verify(C.byref(self.cfg), C.byref(self.weights.c), C.byref(self.cache_c),
                                  draft_tokens.data_ptr(), draft_probs.data_ptr(), uniforms.data_ptr(), C.byref(call),
                                  C.byref(res), self.workspace.data_ptr(), self.ws_bytes, _stream_ptr())
@@ -398,8 +419,7 @@ class VerifyEngine:
         l = 0 if unverified_tokens is None else int(unverified_tokens.shape[0])  # None: an empty suffix
         s_new = 0 if first_tokens is None else int(first_tokens.shape[0])
         call = Call(1, l, float(temperature), SELECT_PAPER_SEQUENTIAL, int(root_token), self.host_prefix_len, float(top_p))
-        res = Result(self.accept_len.data_ptr(), self.next_token.data_ptr(), self.commit.data_ptr(),
-                     self.status.data_ptr(), _ptr(logits_out))
+        res = self.outputs.c(logits_out)
         rc = self.lib.duo_verify_deferred(C.byref(self.cfg), C.byref(self.weights.c), C.byref(self.cache_c),
                                           _ptr(unverified_tokens) if l else None, _ptr(unverified_probs) if l else None,
                                           uniforms.data_ptr(),
@@ -410,13 +430,11 @@ class VerifyEngine:
 
     def results(self, n: int) -> Dict[str, object]:
         """Synchronise and fetch the outputs of the last verify call."""
-        self.torch.cuda.synchronize()
-        commit = self.commit.cpu().numpy()
-        self.host_prefix_len = int(commit[3])  # the commit advanced the device-side prefix length
-        return {"accept_len": self.accept_len[:n].cpu().numpy(), "next_token": self.next_token[:n].cpu().numpy(),
-                "selected": int(commit[0]), "commit_len": int(commit[1]), "commit_token": int(commit[2]),
-                "new_prefix_len": int(commit[3]), "status": int(self.status.cpu().numpy()[0]),
-                "device_prefix_len": int(self.prefix_len.cpu().numpy()[0])}
+        self.torch.cuda.synchronize()  # the call may have been made on another stream
+        out, extra = self.outputs.fetch(n)
+        self.host_prefix_len = out["new_prefix_len"]  # the commit advanced the device-side prefix length
+        out["device_prefix_len"] = int(extra[0])
+        return out
 
 
 def spec_sample(logits, root_logits, draft_tokens, draft_probs, uniforms, temperature: float = 1.0,
@@ -431,20 +449,13 @@ def spec_sample(logits, root_logits, draft_tokens, draft_probs, uniforms, temper
     _check(lib.duo_sample_workspace_bytes(vocab, n, k, C.byref(nbytes)), "duo_sample_workspace_bytes")
     dev = logits.device
     ws = torch.empty(nbytes.value, dtype=torch.uint8, device=dev)
-    accept_len = torch.zeros(n, dtype=torch.int32, device=dev)
-    next_token = torch.zeros(n, dtype=torch.int32, device=dev)
-    commit = torch.zeros(4, dtype=torch.int32, device=dev)
-    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    out = _Results(n, dev)
     call = Call(n, k, float(temperature), int(select_mode), 0 if has_root else -1, int(prefix_len), float(top_p))
-    res = Result(accept_len.data_ptr(), next_token.data_ptr(), commit.data_ptr(), status.data_ptr(), None)
+    res = out.c()
     rc = lib.duo_spec_sample(logits.data_ptr(), _ptr(root_logits), vocab, draft_tokens.data_ptr(), draft_probs.data_ptr(),
                              uniforms.data_ptr(), C.byref(call), C.byref(res), ws.data_ptr(), nbytes.value, _stream_ptr())
     _check(rc, "duo_spec_sample")
-    torch.cuda.synchronize()
-    c = commit.cpu().numpy()
-    return {"accept_len": accept_len.cpu().numpy(), "next_token": next_token.cpu().numpy(), "selected": int(c[0]),
-            "commit_len": int(c[1]), "commit_token": int(c[2]), "new_prefix_len": int(c[3]),
-            "status": int(status.cpu().numpy()[0])}
+    return out.fetch(n)[0]
 
 
 class NoAllocSampler:
@@ -452,11 +463,9 @@ class NoAllocSampler:
     nothing and takes no workspace.  Inputs are device tensors; `run` enqueues, `fetch` synchronises and reads."""
 
     def __init__(self, max_n: int = DUO_MAX_ROWS, device: str = "cuda:0"):
-        import torch
-        self.accept_len = torch.zeros(max_n, dtype=torch.int32, device=device)
-        self.next_token = torch.zeros(max_n, dtype=torch.int32, device=device)
-        self.commit = torch.zeros(4, dtype=torch.int32, device=device)
-        self.status = torch.zeros(1, dtype=torch.int32, device=device)
+        self.outputs = _Results(max_n, device)
+        self.accept_len, self.next_token = self.outputs.accept_len, self.outputs.next_token
+        self.commit, self.status = self.outputs.commit, self.outputs.status
 
     def run(self, logits, root_logits, draft_tokens, draft_probs, uniforms, temperature: float = 1.0,
             select_mode: int = SELECT_INDEPENDENT_LONGEST, has_root: bool = False, prefix_len: int = 0, top_p: float = 0.0,
@@ -465,18 +474,15 @@ class NoAllocSampler:
         n, k = draft_tokens.shape
         vocab = logits.shape[-1]
         call = Call(n, k, float(temperature), int(select_mode), 0 if has_root else -1, int(prefix_len), float(top_p))
-        res = Result(self.accept_len.data_ptr(), self.next_token.data_ptr(), self.commit.data_ptr(), self.status.data_ptr(), None)
+        res = self.outputs.c()
         return int(load(dtype).duo_spec_sample_noalloc(logits.data_ptr(), _ptr(root_logits), vocab, draft_tokens.data_ptr(),
                                                        draft_probs.data_ptr(), uniforms.data_ptr(), C.byref(call), C.byref(res),
                                                        _stream_ptr()))
 
     def fetch(self, n: int) -> Dict[str, object]:
         import torch
-        torch.cuda.synchronize()
-        c = self.commit.cpu().numpy()
-        return {"accept_len": self.accept_len[:n].cpu().numpy(), "next_token": self.next_token[:n].cpu().numpy(),
-                "selected": int(c[0]), "commit_len": int(c[1]), "commit_token": int(c[2]), "new_prefix_len": int(c[3]),
-                "status": int(self.status.cpu().numpy()[0])}
+        torch.cuda.synchronize()  # the call may have been made on another stream
+        return self.outputs.fetch(n)[0]
 
 
 def deferred_sample(logits, root_logits, unverified_tokens, unverified_probs, uniforms, first_tokens=None,
@@ -493,22 +499,16 @@ def deferred_sample(logits, root_logits, unverified_tokens, unverified_probs, un
     _check(lib.duo_sample_workspace_bytes(vocab, 1, l, C.byref(nbytes)), "duo_sample_workspace_bytes")
     dev = (logits if logits is not None else root_logits).device
     ws = torch.empty(nbytes.value, dtype=torch.uint8, device=dev)
-    accept_len = torch.zeros(1, dtype=torch.int32, device=dev)
-    next_token = torch.zeros(1, dtype=torch.int32, device=dev)
-    commit = torch.zeros(4, dtype=torch.int32, device=dev)
-    status = torch.zeros(1, dtype=torch.int32, device=dev)
+    out = _Results(1, dev)
     call = Call(1, l, float(temperature), SELECT_PAPER_SEQUENTIAL, 0 if has_root else -1, int(prefix_len), float(top_p))
-    res = Result(accept_len.data_ptr(), next_token.data_ptr(), commit.data_ptr(), status.data_ptr(), None)
+    res = out.c()
     rc = lib.duo_deferred_sample(_ptr(logits), _ptr(root_logits), vocab, _ptr(unverified_tokens) if l else None,
                                  _ptr(unverified_probs) if l else None, uniforms.data_ptr(), _ptr(first_tokens), _ptr(first_probs),
                                  _ptr(uniforms_first), s_new, C.byref(call), C.byref(res), ws.data_ptr(), nbytes.value,
                                  _stream_ptr())
     _check(rc, "duo_deferred_sample")
-    torch.cuda.synchronize()
-    c = commit.cpu().numpy()
-    return {"accept_len": int(accept_len.cpu().numpy()[0]), "next_token": int(next_token.cpu().numpy()[0]),
-            "selected": int(c[0]), "commit_len": int(c[1]), "commit_token": int(c[2]), "new_prefix_len": int(c[3]),
-            "status": int(status.cpu().numpy()[0])}
+    got = out.fetch(1)[0]
+    return {**got, "accept_len": int(got["accept_len"][0]), "next_token": int(got["next_token"][0])}
 
 
 def skinny_gemm(x_bits, w_bits, dtype: str = "bf16"):
