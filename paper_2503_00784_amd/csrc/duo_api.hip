@@ -192,7 +192,8 @@ struct Profiler {
 Profiler g_prof;
 constexpr size_t PROF_POOL = 8192;  // pairs
 
-// Called right before a launch of class `cls`: arms DUO_LAUNCH with the next event pair.
+// Called right before a launch of class `cls`: arms DUO_LAUNCH with the next event pair.  Where no launch follows, the pair is
+// counted and never recorded, and duo_profile_read fails on it: not in front of a condition.
 inline void prof(int cls, hipStream_t) {
     if (!g_prof.on || cls < 0) return;
     if (g_prof.used >= g_prof.cls.size()) {
@@ -537,9 +538,9 @@ void enqueue_nucleus(const SampleArgs& sa, float top_p, const Workspace& ws, con
 // row merge it themselves (a launch less: 4.4 us), nullptr is returned.
 // status_ready: the call's status word has been initialised by an earlier kernel.
 double* enqueue_statistics(const SampleArgs& sa, hipStream_t s, bool have_stats, bool status_ready, bool merge) {
-    prof(DUO_PROF_SAMPLE, s);
     if (!have_stats) {
         const dim3 grid(sa.R + sa.n * sa.k + (sa.R ? 0 : 1), STATS_SPLIT);
+        prof(DUO_PROF_SAMPLE, s);
         if (sa.V <= 1024 * STATS_SPLIT) DUO_LAUNCH(sample_stats_kernel<256>, grid, dim3(256), s, sa, status_ready ? 0 : 1);
         else DUO_LAUNCH(sample_stats_kernel<SAMPLE_THREADS>, grid, dim3(SAMPLE_THREADS), s, sa, status_ready ? 0 : 1);
         return nullptr;
@@ -548,6 +549,7 @@ double* enqueue_statistics(const SampleArgs& sa, hipStream_t s, bool have_stats,
     static_assert(2 * (DUO_MAX_ROWS + 2) <= 256 && SPREAD_MIN_VOCAB >= 256, "the merged statistics are the first 256 doubles of p_run");
     // (letting every slice merge the statistics of its sequence's rows itself saves this launch and costs more:
     // 2 x 11.6 against 3 x 6.9 us at 9 rows of 1000 parts)
+    prof(DUO_PROF_SAMPLE, s);
     DUO_LAUNCH(sample_row_stats_kernel, dim3(sa.R + sa.n * sa.k + 1), dim3(256), s, sa, sa.p_run);
     return sa.p_run;
 }
