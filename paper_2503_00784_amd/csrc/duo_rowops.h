@@ -105,7 +105,8 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
 }
 
 // Second half of a residual projection whose K range was split over workgroups: x[m] += sum of the S
-// partial results (added in split order), then what EpiResidual does for the next RMSNorm: u = x * gain
+// partial results (added to each other in split order, then to x: one rounding at the size of the residual stream, as in
+// EpiResidual, instead of S), then what EpiResidual does for the next RMSNorm: u = x * gain
 // as bf16 pairs in operand layout and the partial sums of x^2 per 16-column tile, plus the sum of squares over this
 // workgroup's whole column range (RowScale::full), which the consumer reads instead of 256 partials per row.
 // grid = (rows, P): workgroup (m, pt) takes columns pt * d/P .. of row m (d/P a multiple of 64; P <= FULL_PARTS),
@@ -133,12 +134,14 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* 
         Frag8 gv, hi, lo;
         gv.q = *reinterpret_cast<const u32x4*>(gain + j8);
 #pragma unroll
-        for (int sp = 0; sp < MAXS; ++sp) {
+        for (int sp = 1; sp < MAXS; ++sp) {
             if (sp < S) {
-                a0 += p0[sp];
-                a1 += p1[sp];
+                p0[0] += p0[sp];
+                p1[0] += p1[sp];
             }
         }
+        a0 += p0[0];
+        a1 += p1[0];
         *reinterpret_cast<f32x4*>(xr) = a0;
         *reinterpret_cast<f32x4*>(xr + 4) = a1;
         float sq = 0.f;
