@@ -95,10 +95,11 @@ __device__ __forceinline__ void attn_merge_row(const AttnArgs& a, int hk, int r,
 #pragma unroll
     for (int e = 0; e < D / 64; ++e) {
         const float o = acc[e] / L;
-        const u16 hi = f32_to_elem(o);
+        u16 hi, lo;
+        split_elem(o, hi, lo);
         const int col = col0 + lane + e * 64;
         a.out[operand_offset(m, col, a.out_tiles)] = hi;
-        a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = f32_to_elem(o - elem_to_f32(hi));
+        a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = lo;
     }
 }
 
@@ -313,11 +314,11 @@ __global__ __launch_bounds__(NWV * 64) void attn_partial_kernel(AttnArgs a) {
             for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float v = o[mt][dt][i] * inv;
-                    const u16 hi = f32_to_elem(v);
+                    u16 hi, lo;
+                    split_elem(o[mt][dt][i] * inv, hi, lo);
                     const int col = col0 + dt * 16 + g * 4 + i;
                     a.out[operand_offset(m, col, a.out_tiles)] = hi;
-                    a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = f32_to_elem(v - elem_to_f32(hi));
+                    a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = lo;
                 }
         } else {
             float* pp = a.part + (((size_t)hk * a.mq_pad + r) * a.nchunks + cb) * (D + 4);
@@ -497,11 +498,11 @@ __global__ __launch_bounds__(512) void attn_small_kernel(AttnArgs a) {
     const float inv = 1.0f / L;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float v = acc[i] * inv;
-        const u16 hi = f32_to_elem(v);
+        u16 hi, lo;
+        split_elem(acc[i] * inv, hi, lo);
         const int col = col0 + wave * 16 + g * 4 + i;
         a.out[operand_offset(m, col, a.out_tiles)] = hi;
-        a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = f32_to_elem(v - elem_to_f32(hi));
+        a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = lo;
     }
 }
 

@@ -41,10 +41,15 @@ static LaunchEvents g_launch_events;
 // bit patterns of whichever type the build uses; inputs here are finite.
 #ifdef DUO_FP16
 typedef _Float16 elem_t;
+// Fixes a converted value.  Without it the compiler may convert the same product twice, once rounded to fp32 before and once not
+// (a multiplication fused into the conversion), and subtract another hi half than the one that is stored: a whole step of hi off,
+// once in 2^14 values.
+__device__ __forceinline__ void settle(uint32_t& h) { asm("" : "+v"(h)); }
 __device__ __forceinline__ float elem_to_f32(u16 b) { return (float)__builtin_bit_cast(_Float16, b); }
 __device__ __forceinline__ u16 f32_to_elem(float f) { return __builtin_bit_cast(u16, (_Float16)f); }
 #else
 typedef __bf16 elem_t;
+__device__ __forceinline__ void settle(uint32_t&) {}  // no multiplication is fused into a conversion to bf16
 __device__ __forceinline__ float elem_to_f32(u16 b) { return __uint_as_float(((uint32_t)b) << 16); }
 __device__ __forceinline__ u16 f32_to_elem(float f) {
     uint32_t u = __float_as_uint(f);
@@ -64,11 +69,19 @@ __device__ __forceinline__ uint32_t pack_elem2(float a, float b) {
 // the two halves of such a register back as floats
 __device__ __forceinline__ float elem2_lo_f32(uint32_t p) { return elem_to_f32((u16)(p & 0xffffu)); }
 __device__ __forceinline__ float elem2_hi_f32(uint32_t p) { return elem_to_f32((u16)(p >> 16)); }
-// x[0..7] -> hi = elem(x), lo = elem(x - hi), as MFMA operand registers
+// x -> hi = elem(x), lo = elem(x - hi)
+__device__ __forceinline__ void split_elem(float x, u16& hi, u16& lo) {
+    uint32_t h = f32_to_elem(x);
+    settle(h);
+    hi = (u16)h;
+    lo = f32_to_elem(x - elem_to_f32(hi));
+}
+// x[0..7] -> the same, as MFMA operand registers
 __device__ __forceinline__ void split_elem8(const float (&x)[8], u32x4& hi, u32x4& lo) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const uint32_t h = pack_elem2(x[2 * j], x[2 * j + 1]);
+        uint32_t h = pack_elem2(x[2 * j], x[2 * j + 1]);
+        settle(h);
         hi[j] = h;
         lo[j] = pack_elem2(x[2 * j] - elem2_lo_f32(h), x[2 * j + 1] - elem2_hi_f32(h));
     }

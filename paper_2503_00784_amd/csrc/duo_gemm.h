@@ -499,7 +499,8 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ void split_elem4(const f32x4& x, u32x2& hi, u32x2& lo) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-        const uint32_t h = pack_elem2(x[2 * j], x[2 * j + 1]);
+        uint32_t h = pack_elem2(x[2 * j], x[2 * j + 1]);
+        settle(h);
         hi[j] = h;
         lo[j] = pack_elem2(x[2 * j] - elem2_lo_f32(h), x[2 * j + 1] - elem2_hi_f32(h));
     }
@@ -694,10 +695,10 @@ struct EpiResidual {
                 const float xn = (use_pre ? p.x[i] : X[(size_t)m * ldx + n]) + v[0][i];
                 X[(size_t)m * ldx + n] = xn;
                 sq[i] = xn * xn;
-                const float u = xn * gn;
-                const u16 hi = f32_to_elem(u);
+                u16 hi, lo;
+                split_elem(xn * gn, hi, lo);
                 h[operand_offset(m, n, h_tiles)] = hi;
-                h[operand_offset(pair_rows + m, n, h_tiles)] = f32_to_elem(u - elem_to_f32(hi));
+                h[operand_offset(pair_rows + m, n, h_tiles)] = lo;
             }
         }
 #pragma unroll
@@ -750,10 +751,10 @@ struct EpiSwiGLU {
             const int m = qi * 4 + i;
             if (m < M) {
                 const float gate = v[0][i], up = v[1][i];
-                const float a = gate / (1.f + expf(-gate)) * up;
-                const u16 hi = f32_to_elem(a);
+                u16 hi, lo;
+                split_elem(gate / (1.f + expf(-gate)) * up, hi, lo);
                 act[operand_offset(m, n, act_tiles)] = hi;
-                act[operand_offset(pair_rows + m, n, act_tiles)] = f32_to_elem(a - elem_to_f32(hi));
+                act[operand_offset(pair_rows + m, n, act_tiles)] = lo;
             }
         }
     }
@@ -838,9 +839,7 @@ struct EpiQKV {
                     const float r = upper ? mine * cs + other * sn : mine * cs - other * sn;
                     if (head < Hq) {
                         u16* q = q_out + (size_t)m * ldq + head * D + ch;
-                        const u16 r1 = f32_to_elem(r);
-                        q[0] = r1;
-                        q[q_plane] = f32_to_elem(r - elem_to_f32(r1));
+                        split_elem(r, q[0], q[q_plane]);
                     } else if (cache_ok) {
                         u16* kp = kc + (size_t)(head - Hq) * max_seq * D;
                         kp[k_cache_offset(D, plan.slot(m), ch)] = f32_to_elem(r);

@@ -82,9 +82,7 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
             const float v = elem_to_f32(ev.h[j]);
             xv[j >> 2][j & 3] = v;
             sq += v * v;
-            const float u = v * elem_to_f32(gv.h[j]);
-            hi.h[j] = f32_to_elem(u);
-            lo.h[j] = f32_to_elem(u - elem_to_f32(hi.h[j]));
+            split_elem(v * elem_to_f32(gv.h[j]), hi.h[j], lo.h[j]);
         }
         *reinterpret_cast<f32x4*>(xr + j8) = xv[0];
         *reinterpret_cast<f32x4*>(xr + j8 + 4) = xv[1];
@@ -149,9 +147,7 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* 
         for (int j = 0; j < 8; ++j) {
             const float xv = j < 4 ? a0[j] : a1[j - 4];
             sq += xv * xv;
-            const float u = xv * elem_to_f32(gv.h[j]);
-            hi.h[j] = f32_to_elem(u);
-            lo.h[j] = f32_to_elem(u - elem_to_f32(hi.h[j]));
+            split_elem(xv * elem_to_f32(gv.h[j]), hi.h[j], lo.h[j]);
         }
         *reinterpret_cast<u32x4*>(h + operand_offset(m, j8, tiles)) = hi.q;
         *reinterpret_cast<u32x4*>(h + operand_offset(pair_rows + m, j8, tiles)) = lo.q;
@@ -278,11 +274,8 @@ __global__ __launch_bounds__(256) void qkv_finish_kernel(QkvFinishArgs a) {
             const float r_lo = x_lo * cs[it] - x_hi * sn[it], r_hi = x_hi * cs[it] + x_lo * sn[it];
             if (head < a.Hq) {
                 u16* q = a.q_out + (size_t)m * a.ldq + head * D;
-                const u16 h_lo = f32_to_elem(r_lo), h_hi = f32_to_elem(r_hi);
-                q[dd] = h_lo;
-                q[half + dd] = h_hi;
-                q[a.q_plane + dd] = f32_to_elem(r_lo - elem_to_f32(h_lo));
-                q[a.q_plane + half + dd] = f32_to_elem(r_hi - elem_to_f32(h_hi));
+                split_elem(r_lo, q[dd], q[a.q_plane + dd]);
+                split_elem(r_hi, q[half + dd], q[a.q_plane + half + dd]);
             } else if (cache_ok) {
                 u16* kp = a.kc + (size_t)(head - a.Hq) * a.max_seq * D;
                 kp[k_cache_offset(D, a.plan.slot(m), dd)] = f32_to_elem(r_lo);
