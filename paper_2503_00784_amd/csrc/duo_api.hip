@@ -541,8 +541,13 @@ double* enqueue_statistics(const SampleArgs& sa, hipStream_t s, bool have_stats,
     if (!have_stats) {
         const dim3 grid(sa.R + sa.n * sa.k + (sa.R ? 0 : 1), STATS_SPLIT);
         prof(DUO_PROF_SAMPLE, s);
-        if (sa.V <= 1024 * STATS_SPLIT) DUO_LAUNCH(sample_stats_kernel<256>, grid, dim3(256), s, sa, status_ready ? 0 : 1);
-        else DUO_LAUNCH(sample_stats_kernel<SAMPLE_THREADS>, grid, dim3(SAMPLE_THREADS), s, sa, status_ready ? 0 : 1);
+        // the fewest threads that hold a slice in registers: fewer waves to wait for and to fit in, and 80 rows are 640 workgroups.  256 /
+        // 512 / 1024 threads, 9 and 73 rows: 12288 entries 4.5, 5.0 / 4.5, 6.1 / 5.5, 10.2 us; 32000: 5.9, 7.1 / 5.3, 7.7 / 6.1, 11.8;
+        // 64000 (256 threads read it twice): 12.2, 13.2 / 6.6, 10.4 / 7.2, 14.5; 128256: 21.3, 42.6 / 12.1, 26.7 / 9.3, 21.1
+        const int len = (sa.V + STATS_SPLIT - 1) / STATS_SPLIT;
+        if (len <= 256 * STATS_PER_THREAD) DUO_LAUNCH(sample_stats_kernel<256>, grid, dim3(256), s, sa, status_ready ? 0 : 1);
+        else if (len <= 512 * STATS_PER_THREAD) DUO_LAUNCH(sample_stats_kernel<512>, grid, dim3(512), s, sa, status_ready ? 0 : 1);
+        else DUO_LAUNCH(sample_stats_kernel<1024>, grid, dim3(1024), s, sa, status_ready ? 0 : 1);
         return nullptr;
     }
     if (!merge) return nullptr;

@@ -112,6 +112,7 @@ __device__ __forceinline__ Nucleus nucleus_of(const SampleArgs& a, int i, int j)
 
 constexpr int SAMPLE_THREADS = 1024;
 constexpr int STATS_SPLIT = 8;        // workgroups per row of logits in sample_stats_kernel
+constexpr int STATS_PER_THREAD = 16;  // values of a slice that a thread of it holds in registers
 constexpr int ROOT_STATS_PARTS = 32;  // slices of the cached root logits when the verify pass's first kernel takes their statistics
 
 __device__ __forceinline__ double block_sum_d(double v, double* sm) {
@@ -159,11 +160,11 @@ __device__ __forceinline__ void slice_stats(const float* __restrict__ row, int v
 // there is no root row.  Used when the logits come from the caller; the verify step's LM head leaves the same
 // statistics itself (EpiLogitsStats in duo_gemm.h) and the pass's first kernel those of root_logits.  As the first kernel
 // of a sampling-only call it also sets the status word (set_status): its first workgroup checks the draft tokens.
-// A thread holds its share of the slice in registers between the maximum and the sum (up to 16 values, i.e. a vocabulary of
-// 131072 with 1024 threads; longer slices are read twice): one trip to memory, and 16 waves per slice for the
-// double-precision exponentials the kernel is bound by (128256 entries, 65 rows: with four waves that read the slice
-// twice 46 us).  At most 64 registers, so that two workgroups of 1024 fit a compute unit: 65 rows are 520 workgroups, three
-// rounds of one per compute unit otherwise.  Slices of up to 1024 entries are left to four waves, whose block sums are shorter.
+// A thread holds its share of the slice in registers between the maximum and the sum (up to STATS_PER_THREAD values, i.e. a
+// vocabulary of 131072 with 1024 threads; longer slices are read twice): one trip to memory.  Bound by the latency of that trip, of
+// the block sums and of the double-precision exponentials of few waves: 128256 entries and 65 rows 20.2 us with 1024 threads against 46
+// with 256 that read the slice twice; but no more threads than a slice needs (see the launch).  At most 64 registers, so that two
+// workgroups of 1024 fit a compute unit: 65 rows are 520 workgroups, three rounds of one per compute unit otherwise.
 template <int TH>
 __global__ __launch_bounds__(TH, 8) void sample_stats_kernel(SampleArgs a, int set_status) {
     __shared__ double sm[16];
@@ -171,7 +172,7 @@ __global__ __launch_bounds__(TH, 8) void sample_stats_kernel(SampleArgs a, int s
     const float* row = r < rows ? a.logits + (size_t)r * a.ld : a.root_logits;
     const int len = (a.V + STATS_SPLIT - 1) / STATS_SPLIT;
     const int v0 = min(a.V, sl * len), v1 = min(a.V, v0 + len);
-    constexpr int PER = 16;
+    constexpr int PER = STATS_PER_THREAD;
     const bool in_regs = len <= PER * TH;
     float x[PER];
     float lm = -INFINITY;
