@@ -559,17 +559,23 @@ double* enqueue_statistics(const SampleArgs& sa, hipStream_t s, bool have_stats,
     return sa.p_run;
 }
 
-// The sequential first-token rule (both forms) for vocabularies of SEQ_MIN_VOCAB entries and more.  Whole calls on caller-supplied
-// logits, one workgroup against many launches (n sequences of k tokens, 32000 entries): 1 x 8 47.5 -> 23 us, 3 x 11 54 -> 32 us, 8 x 4 51 -> 34 us;
-// 128256 entries: 170 -> 29, 312 -> 60, 365 -> 80 us; 12288 entries: 27 -> 22, 27 -> 28, 27 -> 28 us, where the line is drawn.
+// Whether the sequential first-token rule over s candidates (both forms) runs as the seq_* launches: where it is faster whether the
+// first candidate is accepted or none.  Calls on caller-supplied logits, first accepted / all rejected, one workgroup against the
+// launches: 12288 entries, 2 candidates 16.1 / 33.4 -> 14.5 / 27.5 us; 32000 entries, 4: 28 / 95 -> 20 / 49 us; 128256 entries, 8:
+// 90 / 667 -> 32 / 113 us.  Four candidates are a launch more (12288 entries, first accepted: 16.0 -> 17.7; 16000: 18.1 -> 18.0).  More
+// than that end in seq_tail_kernel below 32768 entries: 8 candidates 16.1 / 73 -> 17.7 / 82 at 12288, 23 / 121 -> 20 / 120 at 24000
+// and, behind an LM head, 112 / 210 -> 93 / 211 (whole step of a small model) at 28000.
+bool sequential_on_many(int V, int s) { return V >= (s <= 3 ? SEQ_MIN_VOCAB : s == 4 ? 16384 : 28672); }
+
 void enqueue_sequential(const SampleArgs& sa, const SeqArgs& d, double* row_stats, hipStream_t s) {
     const int G = std::min(SPREAD_MAX_SLICES, sa.V / 2048);
     const int chunk = ((sa.V + 16 * G - 1) / (16 * G) + 63) / 64 * 64;
     static_assert(256 + SEQ_STAGES + (SEQ_STAGES + 1) * 4 <= 512, "totals and records lie between the merged statistics and the sums");
     static_assert(512 + 2 * 16 * SPREAD_MAX_SLICES * 3 <= SEQ_MIN_VOCAB, "the records fit p_run");
+    int stages = std::max(3, std::min(SEQ_STAGES, sa.V / 8192));
+    if (d.s == stages + 1 && d.s <= SEQ_STAGES) stages = d.s;  // one launch too, and not a workgroup alone with the vocabulary
     SeqBuf b{row_stats, sa.p_run + 256, reinterpret_cast<int32_t*>(sa.p_run + 256 + SEQ_STAGES), sa.p_run + 512,
-             reinterpret_cast<int32_t*>(sa.p_run + 512 + (size_t)2 * 16 * G * 2), G, chunk,
-             std::max(3, std::min(SEQ_STAGES, sa.V / 8192))};
+             reinterpret_cast<int32_t*>(sa.p_run + 512 + (size_t)2 * 16 * G * 2), G, chunk, stages};
     const int launches = std::max(1, std::min(d.s, b.stages));
     for (int i = 0; i < launches; ++i) {
         prof(DUO_PROF_SAMPLE, s);
@@ -591,7 +597,7 @@ void enqueue_sequential(const SampleArgs& sa, const SeqArgs& d, double* row_stat
 void enqueue_sampling(const SampleArgs& sa, float top_p, const Workspace& ws, int mode, u16* kc, u16* vc,
                       const duo_model_config* c, int32_t* prefix_len, hipStream_t s, bool have_stats = false) {
     // the one-workgroup rules merge the parts themselves
-    const bool merged = sa.V >= (mode == DUO_SELECT_INDEPENDENT_LONGEST ? SPREAD_MIN_VOCAB : SEQ_MIN_VOCAB);
+    const bool merged = mode == DUO_SELECT_INDEPENDENT_LONGEST ? sa.V >= SPREAD_MIN_VOCAB : sequential_on_many(sa.V, sa.n);
     double* row_stats = enqueue_statistics(sa, s, have_stats, have_stats, merged);
     enqueue_nucleus(sa, top_p, ws, row_stats, s);
     if (mode == DUO_SELECT_INDEPENDENT_LONGEST) {
@@ -614,7 +620,7 @@ void enqueue_sampling(const SampleArgs& sa, float top_p, const Workspace& ws, in
         } else if (sa.nuc) DUO_LAUNCH(sample_finish_kernel<true>, dim3(sa.n), dim3(SAMPLE_THREADS), s, sa, self_commit ? 1 : 0, prefix_len);
         else DUO_LAUNCH(sample_finish_kernel<false>, dim3(sa.n), dim3(SAMPLE_THREADS), s, sa, self_commit ? 1 : 0, prefix_len);
         if (self_commit) return;
-    } else if (sa.V >= SEQ_MIN_VOCAB) {
+    } else if (merged) {
         enqueue_sequential(sa, SeqArgs{sa.tokens, sa.k, sa.q, (size_t)sa.k * sa.V, sa.u, sa.k + 1, sa.n, 0, prefix_len}, row_stats, s);
         if (!kc) return;  // nothing to move, and the commit record is written
     } else {
@@ -826,9 +832,10 @@ static int check_deferred(const duo_call* call, int vocab, const int32_t* first_
 
 static void enqueue_deferred_sampling(const SampleArgs& sa, float top_p, const Workspace& ws, const DeferredArgs& da,
                                       hipStream_t s, bool have_stats = false, bool status_ready = false) {
-    double* row_stats = enqueue_statistics(sa, s, have_stats, status_ready, sa.V >= SEQ_MIN_VOCAB);
+    const bool many = sequential_on_many(sa.V, da.s);
+    double* row_stats = enqueue_statistics(sa, s, have_stats, status_ready, many);
     enqueue_nucleus(sa, top_p, ws, row_stats, s);
-    if (sa.V >= SEQ_MIN_VOCAB) {
+    if (many) {
         enqueue_sequential(sa, SeqArgs{da.first_tokens, 1, da.first_probs, (size_t)sa.V, da.uniforms_first, 1, da.s, 1, da.prefix_len}, row_stats, s);
         return;
     }

@@ -1261,7 +1261,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_deferred_kernel(SampleA
 // their totals, which for a handful of candidates is less work than a pass through memory.  Launches behind the decision
 // return at once but cost 3 us each all the same, so there are at most b.stages of them, one per 8192 entries of the
 // vocabulary, three at least and no more than SEQ_STAGES, and seq_tail_kernel, one workgroup with the running distribution in memory, judges the
-// candidates beyond.  seq_locate_kernel draws the token from the sums of the launch that
+// candidates beyond (a single one gets a launch of its own instead).  seq_locate_kernel draws the token from the sums of the launch that
 // decided and writes the results.
 struct SeqArgs {
     const int32_t* tok;  // candidate i: first token tok[i * tok_stride], draft distribution q + i * q_stride, uniform u[i * u_stride]
@@ -1274,7 +1274,7 @@ struct SeqArgs {
     int deferred;         // 0: the candidates are the call's n sequences; 1: Alg. 2 as listed (see DeferredArgs)
     int32_t* prefix_len;  // device prefix length (may be NULL); advanced here in the deferred form, by commit_kernel otherwise
 };
-constexpr int SEQ_MIN_VOCAB = 12288;  // below: sample_paper_kernel, sample_deferred_kernel
+constexpr int SEQ_MIN_VOCAB = 12288;  // below, and with more candidates up to 28672: sample_paper_kernel, sample_deferred_kernel
 constexpr int SEQ_STAGES = 8;
 
 struct SeqBuf {
