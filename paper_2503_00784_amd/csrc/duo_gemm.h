@@ -966,11 +966,14 @@ static inline void launch_wide(const u16* X, const u16* W, int K, int tiles, int
     if (ng <= 1) launch_wide_cfg<MH, NT, 1, 2>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
     else if (ng == 2) launch_wide_cfg<MH, NT, 2, 2>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
     else if (ng == 3) launch_wide_cfg<MH, NT, 3, 1>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
-    // many bands: eight waves of four weight slots stage the operand half as often.  A round of such workgroups takes 1.55
-    // (80 rows) to 1.9 (9 rows) rounds of the smaller ones.  4008 tiles (a 128k vocabulary, two rounds against four): 267 -> 212 us
-    // at 80 rows, 216 -> 197 at 32, 197 -> 188 at 12; 1250 tiles (one against two): 110 -> 90, 77 -> 62, 73 -> 56; 2500 tiles
-    // (two against three) stay; 2048 tiles, two full rounds: 135 -> 107 at 80 rows but 95 -> 100 at 32
-    else if (1.75f * (float)((tiles + 2047) / 2048) < (float)((tiles + 1023) / 1024) && (MH > 2 || tiles <= 1792 || tiles > 2048))
+    // Many bands: eight waves of four weight slots stage the operand half as often.  What counts are rounds of workgroups, one per
+    // compute unit: a full round of eight waves takes 2.03 / 1.98 / 1.96 / 1.84 / 1.65 rounds of four at 16 / 32 / 48 / 64 / 80 rows.
+    // An odd number of small rounds leaves the last large one half empty (3072 tiles x 4096 channels: 135 / 144 / 156 / 166 / 178 us
+    // with four waves, 150 / 159 / 162 / 167 / 165 with eight); an even number wins by the last small round that was partly empty (1250
+    // tiles: 70 / 74 / 75 / 82 / 89 against 54 / 58 / 63 / 67 / 72) and by fewer rounds (4096 tiles: 195 / 215 / 206 / 219 / 236 against
+    // 189 / 196 / 201 / 204 / 194).  Neither is left where two small rounds are full (2048 tiles, 16 and 32 rows: 91 / 93 against
+    // 94 / 95; even at 1792: 80 / 84 against 80 / 81) nor, at 16 rows, over many rounds (8192 tiles: 372 against 378).
+    else if (const int rounds = (tiles + 1023) / 1024; rounds % 2 == 0 && (MH > 2 || (rounds == 2 ? tiles <= 1792 : (MH == 2 || rounds == 4))))
         launch_wide_cfg<MH, NT, 8, 1, Epi, false, true, 4>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
     else launch_wide_cfg<MH, NT, 4, 1>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
 }
