@@ -313,6 +313,49 @@ void launch_attention_shared(int nwv, int ksplit, dim3 grid, const AttnArgs& a, 
     else DUO_LAUNCH((attn_shared_kernel<D, 8, 1>), grid, dim3(576), s, a);
 }
 
+// Attention of a prompt chunk: query tiles of attn_shared_kernel's workgroups (a tile per wave of a team) and chunks of keys.  A
+// workgroup has a compute unit to itself and takes 6 us and, per ring stage of a block for each team, 1.02 us with two teams of four
+// waves, 1.27 with two of five, 1.06 as one team of eight (heads of 128; of 64: 0.68 of it), about the same per tile and block: what
+// decides is how evenly the groups of 4, 5 or 8 tiles fill the chip.  The late rows see the most keys and go first, so the launch takes its
+// mean load or, where the last workgroups come as an odd few, (rounds + 1) times the length of those.  More than one chunk: the merge, 4 us
+// and 1.5 us per million values.  In us with the merge, groups of four tiles
+// alone against this choice: 32 heads, 640 rows behind 4000 keys 139 -> 108, behind 16000 420 -> 371; 40 heads, 200 rows behind 8000
+// 110 -> 98; 8 heads x 8, 800 rows behind 8000 533 -> 478.  1024 rows behind 1024 keys on 32 heads keep them: 69, against 93 + 14 with two
+// tiles per wave.
+struct PromptAttention {
+    int nwv, ksplit, chunks;
+};
+PromptAttention prompt_attention(int D, int Hkv, int group, int M, int P, int max_chunks) {
+    constexpr int CUS = 256;
+    static const struct {
+        int nwv, ksplit;
+        float stage;
+    } shapes[] = {{8, 2, 1.02f}, {10, 2, 1.27f}, {8, 1, 1.06f}};
+    const int NB = (P + M + 31) / 32, MQ = M * group;
+    PromptAttention best{8, 2, 1};
+    float best_cost = 1e30f;
+    for (const auto& s : shapes) {
+        const int rows = s.nwv / s.ksplit * 16, groups = (MQ + rows - 1) / rows;  // query rows of a workgroup, row groups
+        const auto blocks_seen = [&](int z) { return std::min(NB, (P + (std::min(MQ, (z + 1) * rows) - 1) / group) / 32 + 1); };
+        for (int t = 1; t <= max_chunks; ++t) {
+            const int bl = std::max(2, (NB + t - 1) / t), n = (NB + bl - 1) / bl;  // blocks per chunk, chunks
+            const float mean_stages = 0.5f * (float)(blocks_seen(0) + blocks_seen(groups - 1)) / (float)s.ksplit;  // all chunks of a row group
+            float cost = (float)(Hkv * groups) * (6.f * (float)n + s.stage * mean_stages) / (float)CUS;
+            for (int r = 0; r * CUS < Hkv * groups * n; ++r) {  // 256 r workgroups came first: the next one is the longest that is left
+                const int seen = std::min(bl, blocks_seen(groups - 1 - r * CUS / (n * Hkv)));
+                cost = std::max(cost, (float)(r + 1) * (6.f + s.stage * (float)((seen + s.ksplit - 1) / s.ksplit)));
+            }
+            if (D == 64) cost *= 0.68f;
+            if (n > 1) cost += 4.f + 1.5e-6f * (float)n * (float)MQ * (float)Hkv * (float)D;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = PromptAttention{s.nwv, s.ksplit, t};
+            }
+        }
+    }
+    return best;
+}
+
 // The target pass over the rows of `plan`: fills the cache slots P .. P+M-1 and writes fp32
 // logits [M][V] (row stride V) to `logits`.
 // `temperature` >= 0: the pass is followed by sampling at that temperature, so the LM head also leaves the softmax
@@ -367,11 +410,14 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         // 11.8 against 14.4 us at 2 tiles, measured on 32 heads x 4160 / 2080 keys).
         // 9..16 tiles (64 rows x a GQA group of 4): 27.3 against 28.2 us at 8192 keys; 17..20 tiles (65..80 rows) in the same shape
         // against two tiles per wave: 33.8 against 43.4 us at 8192 keys, 14.1 against 18.6 at 2048, 10.9 against 13.4 at 700.
-        // Prompt chunks likewise, in one chunk of keys where there are enough row groups: 70 against 93 + 14 us (chunk merge) for
-        // 1024 rows behind 1024 keys on 32 heads, 75 against 96 + 25 us on 8 heads x 4.
-        sh_ksplit = (MqT <= 4 || MqT > 8 || many) ? 2 : 1;
+        sh_ksplit = (MqT <= 4 || MqT > 8) ? 2 : 1;
         sh_nwv = MqT > 2 ? 8 : 4;
-        if (MqT == 5 && NB >= 64) {
+        PromptAttention prompt{0, 0, 0};
+        if (many) {
+            prompt = prompt_attention(D, Hkv, group, M, plan.P, max_chunks);
+            sh_ksplit = prompt.ksplit;
+            sh_nwv = prompt.nwv;
+        } else if (MqT == 5 && NB >= 64) {
             // five tiles (65..80 rows of a head without a group) on a long context: two teams of five against eight waves of which
             // five have a tile, 25.9 -> 22.3 us on 32 heads x 4161 keys, 17.9 -> 17.3 at 2127 (at 577 keys 9.1 -> 10.3: not there)
             sh_ksplit = 2;
@@ -382,20 +428,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         // heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us)
         int target = 256 / (Hkv * sh_zg);
         target = target < 1 ? 1 : (target > max_chunks ? max_chunks : target);
-        if (many) {
-            // the chunk count that costs least: rounds of workgroups times (5 us + 1.15 us per ring stage of two blocks), and for
-            // more than one chunk the merge, 4 us and the time of writing and reading its input
-            float best = 1e30f;
-            for (int t = 1; t <= max_chunks; ++t) {
-                const int stages = ((NB + t - 1) / t + 1) / 2;
-                const float cost = (float)((Hkv * sh_zg * t + 255) / 256) * (5.f + 1.15f * (float)stages) +
-                                   (t > 1 ? 4.f + 2e-6f * (float)t * (float)MQ * (float)Hkv * (float)D : 0.f);
-                if (cost < best) {
-                    best = cost;
-                    target = t;
-                }
-            }
-        }
+        if (many) target = prompt.chunks;
         bpw = (NB + target - 1) / target;  // blocks per chunk
         bpw = bpw < 2 ? 2 : bpw;
         nchunks = (NB + bpw - 1) / bpw;
