@@ -321,12 +321,12 @@ int duo_stream_read_probe(const void *src, size_t bytes, uint32_t *sink, int sin
  * not allocation-free or capturable.  Not thread-safe.
  * ms and launches are HOST arrays of DUO_PROF_CLASSES entries.
  */
-#define DUO_PROF_SETUP     0  /* rotary table, embedding gather + first RMSNorm */
+#define DUO_PROF_SETUP     0  /* rotary table, embedding gather + first RMSNorm, input checks, root statistics */
 #define DUO_PROF_QKV       1  /* fused QKV projection + rotary + KV scatter */
 #define DUO_PROF_ATTN      2  /* masked attention over prefix + drafts (chunk partials) */
 #define DUO_PROF_ATTN_COMB 3  /* merge of the chunk partials (long contexts only) */
 #define DUO_PROF_OPROJ     4  /* O projection + residual */
-#define DUO_PROF_RESID_REDUCE 5 /* more than 16 rows: sum of the K-split O/down partial results + residual */
+#define DUO_PROF_RESID_REDUCE 5 /* sum of the K-split O/down partial results + residual (more than 16 rows; from 9 rows on where d_ff >= 8192); prompt chunks of more than 80 rows: also the row sums of squares behind an unsplit one */
 #define DUO_PROF_GATEUP    6  /* gate/up projection + SwiGLU */
 #define DUO_PROF_DOWN      7  /* down projection + residual */
 #define DUO_PROF_LMHEAD    8  /* LM head */

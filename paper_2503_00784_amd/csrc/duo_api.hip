@@ -50,8 +50,9 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 constexpr int MAX_CHUNKS = 64;
 constexpr int MAX_CHUNKS_MANY_ROWS = 8;  // key chunks of the attention kernels in passes of more than DUO_MAX_ROWS rows
 
-// K splits of a residual projection (N = d_model columns) in the many-row pass: enough workgroups of 128 x 128 for
-// the chip, at most eight partial results.
+// Partial results of a residual projection (N = d_model columns) that the workspace of a many-row pass has a part of its own for: as
+// many as make enough workgroups of 128 x 128 for the chip, at most eight.  (How many ways a launch splits K is residual_splits'
+// business; the nucleus search's rows hold more of them where they are larger.)
 int block_splits(int M, int N) {
     const int mh = pair_rows_for(M) / 16;
     const int wgs = ((N / 16 + 7) / 8) * ((mh + 7) / 8);
@@ -246,7 +247,7 @@ void launch_projection(int cls, int M, const u16* X, const u16* W, int K, int ti
 
 // x += act W^T (O and down projections, N = d_model columns) followed by the preparation of the next RMSNorm.
 // Few rows: one kernel (EpiResidual).  Many rows: K split over workgroups, partial results, and a small
-// second kernel that adds them in split order and does EpiResidual's work.
+// second kernel that adds them up in split order, adds the sum to x and does the rest of EpiResidual's work.
 static_assert(WIDE_MAX_SPLIT <= 8, "residual_reduce_kernel holds at most eight splits in registers");
 
 // K splits of a residual projection over K input channels: 1 = one kernel (EpiResidual), more = K-split partial products + reduce

@@ -189,7 +189,9 @@ static inline int launch_block_range(const u16* X, const u16* W, int K, int nban
 // its rounds of workgroups, one per compute unit, times what a K step costs a workgroup of that shape.  Measured over K = 4096 with
 // 230..256 workgroups (us per K step): WM = 4: 0.37 / 0.41 / 0.50 / 0.57 / 0.64 / 0.82 / 0.93 / 1.14 for WN = 2 / 3 / 4 / 5 / 6 /
 // 8 / 10 / 12, WM = 3: 0.31 / 0.35 / 0.42 / 0.52 / 0.67 for 2 / 3 / 4 / 6 / 8, WM = 2: 0.28 / 0.30 / 0.44 / 0.53 for 2 / 3 / 6 / 8,
-// all within a tenth of 0.18 + WN * (0.006 + 0.0186 * WM).  Full rounds matter more than large tiles: Q/K/V at 1024 rows
+// all within a tenth of 0.18 + WN * (0.006 + 0.0186 * WM).  Every shape is there because rounds come out fullest with it somewhere: over
+// the matrices of the repository's models at 81..1024 rows the cheapest of the others costs 2 (for (4, 3) and (2, 8)) to 15 % more in the
+// mean where a shape is the pick, (4, 10) 13, (3, 10) 4, (4, 5) 14, by this model.  Full rounds matter more than large tiles: Q/K/V at 1024 rows
 // (768 bands) takes 195 us as 384 workgroups of (4, 8), 157 us as 512 of (4, 6), 148 us = 1.39 PFLOP/s as 256 of (4, 12).
 struct BlockShape {
     int wm, wn;

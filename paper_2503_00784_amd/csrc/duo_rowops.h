@@ -25,7 +25,7 @@ __device__ __forceinline__ void block_row_sum(float v, float* wsum, float* out) 
 //     projection's operand buffer, the per-tile partial sums of x^2 and the whole row's; runs of eight channels per thread;
 //   - the row's rotary factors: cos/sin of pos(m) * theta^(-2d/D), evaluated in double and rounded once to fp32;
 //   - workgroup 0: the device-side input checks (token ids in range, device prefix length equal to the host's) into the status
-//     word, which the kernels after this one only read;
+//     word, which it thereby initialises: the kernels after this one read it or OR into it (the deferred form's first tokens);
 //   - for a pass that will be followed by sampling from cached root logits (root.logits != nullptr), the last ROOT_STATS_PARTS
 //     workgroups leave the softmax statistics of those logits, slice by slice (see SampleArgs in duo_sample.h): work that is off
 //     the critical path here and would otherwise need a launch of its own.

@@ -300,8 +300,9 @@ __device__ __forceinline__ void fill_running_distribution(const SampleArgs& a, c
 // logit and, among equal logits, ascending id, with which the mass reaches top_p * total.
 //
 // Masses are added as whole numbers, p in units of 2^-62: sums of whole numbers do not depend on their order, so LDS
-// atomics give repeatable results, and 128256 roundings of at most 2^-63 leave a sum closer to the exact one than a sum
-// of doubles (1e-17 against 1e-16 as a root mean square).
+// atomics give repeatable results, and the sums add no rounding of their own.  A single mass is what its double was: the
+// error of exp and of the multiplication by 1/Z, a few 2^-53 of it, and 2^-63 for the step to a whole number, which is the larger of
+// the two below p = 2^-10 or so.
 //   1. every id goes into one of NUC_BINS bins of equal width in logit / T below the maximum (a monotone map, so the
 //      bins are in order of decreasing probability; the last bin takes everything from e^-42.6 down), and each bin's
 //      mass is added up: large vocabularies by nucleus_hist_kernel, G slices of a row on as many workgroups (the
