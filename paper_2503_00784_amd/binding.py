@@ -242,16 +242,18 @@ def _wait_for_call(device) -> None:
 
 
 class _Results:
-    """The integer results of a call, one device buffer (one fill, one copy to the host) seen as the tensors of duo_result;
-    `extra` more words behind them."""
+    """The integer results of a call, one device buffer (one fill, one copy to the host) seen as the tensors of duo_result, max_n
+    sequences each; `extra` more words behind them.  The two arrays have room for `room` sequences, so that a call with more than max_n
+    writes into neither the other array nor the commit record."""
 
-    def __init__(self, max_n: int, device, extra: int = 0):
+    def __init__(self, max_n: int, device, extra: int = 0, room: int = 0):
         import torch
         self.max_n = max_n
-        self.buffer = torch.zeros(2 * max_n + 5 + extra, dtype=torch.int32, device=device)
-        self.accept_len, self.next_token = self.buffer[:max_n], self.buffer[max_n:2 * max_n]
-        self.commit, self.status = self.buffer[2 * max_n:2 * max_n + 4], self.buffer[2 * max_n + 4:2 * max_n + 5]
-        self.extra = self.buffer[2 * max_n + 5:]
+        self.room = r = max(max_n, room)
+        self.buffer = torch.zeros(2 * r + 5 + extra, dtype=torch.int32, device=device)
+        self.accept_len, self.next_token = self.buffer[:max_n], self.buffer[r:r + max_n]
+        self.commit, self.status = self.buffer[2 * r:2 * r + 4], self.buffer[2 * r + 4:2 * r + 5]
+        self.extra = self.buffer[2 * r + 5:]
 
     def c(self, logits_out=None) -> Result:
         return Result(self.accept_len.data_ptr(), self.next_token.data_ptr(), self.commit.data_ptr(), self.status.data_ptr(),
@@ -259,10 +261,10 @@ class _Results:
 
     def fetch(self, n: int):
         """(results of the first n sequences, the extra words), by one copy to the host; the caller has waited for the call."""
-        h, m = self.buffer.cpu().numpy(), self.max_n
-        c = h[2 * m:2 * m + 4]
-        return {"accept_len": h[:n].copy(), "next_token": h[m:m + n].copy(), "selected": int(c[0]), "commit_len": int(c[1]),
-                "commit_token": int(c[2]), "new_prefix_len": int(c[3]), "status": int(h[2 * m + 4])}, h[2 * m + 5:]
+        h, r, n = self.buffer.cpu().numpy(), self.room, min(n, self.max_n)
+        c = h[2 * r:2 * r + 4]
+        return {"accept_len": h[:n].copy(), "next_token": h[r:r + n].copy(), "selected": int(c[0]), "commit_len": int(c[1]),
+                "commit_token": int(c[2]), "new_prefix_len": int(c[3]), "status": int(h[2 * r + 4])}, h[2 * r + 5:]
 
 
 _LAYER_KEYS = ("wqkv", "wo", "w_gate_up", "w_down", "g_attn", "g_ffn")
@@ -473,7 +475,7 @@ class NoAllocSampler:
     nothing and takes no workspace.  Inputs are device tensors; `run` enqueues, `fetch` synchronises and reads."""
 
     def __init__(self, max_n: int = DUO_MAX_ROWS, device: str = "cuda:0"):
-        self.outputs = _Results(max_n, device)
+        self.outputs = _Results(max_n, device, room=DUO_MAX_ROWS)
         self.accept_len, self.next_token = self.outputs.accept_len, self.outputs.next_token
         self.commit, self.status = self.outputs.commit, self.outputs.status
 

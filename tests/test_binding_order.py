@@ -81,3 +81,29 @@ def test_noalloc_sampler_waits_for_the_current_device(events):
     assert events == ["call"]  # enqueues only
     sampler.fetch(2)
     assert events == ["call", "wait", "fetch"]
+
+
+class _WritingLibrary(_FakeLibrary):
+    """Writes what the kernels write: n accepted lengths and tokens, the commit record, the status."""
+
+    def duo_spec_sample_noalloc(self, logits, root, vocab, tokens, probs, uniforms, call, out, stream):
+        n, res = call._obj.n, out._obj
+        ints = lambda p: C.cast(p, C.POINTER(C.c_int32))
+        for i in range(4):
+            ints(res.commit)[i] = 100 + i
+        ints(res.status)[0] = 0
+        for i in range(n):
+            ints(res.accept_len)[i] = 10 + i
+            ints(res.next_token)[i] = 20 + i
+        return 0
+
+
+@pytest.mark.parametrize("max_n", [1, 2, 80])
+def test_more_sequences_than_a_sampler_was_made_for_leave_the_commit_alone(events, monkeypatch, max_n):
+    monkeypatch.setattr(binding, "load", lambda dtype="bf16": _WritingLibrary(events))
+    sampler = binding.NoAllocSampler(max_n, device="cpu")
+    assert sampler.accept_len.shape == sampler.next_token.shape == (max_n,)
+    assert sampler.run(*_inputs()) == 0  # two sequences
+    got = sampler.fetch(2)
+    assert (got["selected"], got["commit_len"], got["commit_token"], got["new_prefix_len"], got["status"]) == (100, 101, 102, 103, 0)
+    assert got["accept_len"][0] == 10 and got["next_token"][0] == 20
