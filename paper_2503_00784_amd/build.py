@@ -11,9 +11,11 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libduo_verify.so")
 LIB_PATH_FP16 = os.path.join(HERE, "libduo_verify_fp16.so")
 SOURCES = [os.path.join(HERE, "csrc", "duo_api.hip")]
+KERNEL_ORDER = os.path.join(HERE, "csrc", "kernel_order.txt")  # where the linker places the kernels, and why it matters
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
+         "-Xoffload-linker", "--symbol-ordering-file=" + KERNEL_ORDER]
 
 
 def _compile(extra, out_path: str, verbose: bool) -> str:
