@@ -60,7 +60,7 @@ int block_splits(int M, int N) {
     return S < 1 ? 1 : (S > WIDE_MAX_SPLIT ? WIDE_MAX_SPLIT : S);
 }
 
-// GEMM operand buffers (h, attn, act) hold activations as bf16 pairs: row m = hi, row pair_rows + m = lo,
+// GEMM operand buffers (h, attn, act) hold activations as bf16 pairs: row m = hi, row lo_rows(m) = lo,
 // padded to whole 16-row MFMA tiles; rows that carry no activation are never stored from.
 constexpr int QKV_SPLITS = 4;  // most K splits of the Q/K/V projection at 49..80 rows (QkvFinishArgs::MAX_SPLITS)
 
@@ -123,7 +123,7 @@ Workspace carve(const duo_model_config& c, int max_rows, void* base_v) {
     Workspace ws{};
     char* base = static_cast<char*>(base_v);
     const size_t Mp = align_up((size_t)max_rows, 16);
-    const size_t Ar = (size_t)a_tiles_for(max_rows, true) * 16;
+    const size_t Ar = (size_t)align_up(2 * pair_rows_for(max_rows), 16);  // any number of rows up to max_rows
     const size_t d = c.d_model, qd = (size_t)c.n_q_heads * c.head_dim, F = c.d_ff, V = c.vocab;
     const size_t group = c.n_q_heads / c.n_kv_heads;
     size_t off = 0;
@@ -236,13 +236,7 @@ void launch_projection(int cls, int M, const u16* X, const u16* W, int K, int ti
         return;
     }
     const int quads = pair_rows_for(M) / 4;
-    switch ((M + 15) / 16) {
-        case 1: launch_wide<1, NT>(X, W, K, tiles, quads, rsc, epi, s); break;
-        case 2: launch_wide<2, NT>(X, W, K, tiles, quads, rsc, epi, s); break;
-        case 3: launch_wide<3, NT>(X, W, K, tiles, quads, rsc, epi, s); break;
-        case 4: launch_wide<4, NT>(X, W, K, tiles, quads, rsc, epi, s); break;
-        default: launch_wide<5, NT>(X, W, K, tiles, quads, rsc, epi, s); break;
-    }
+    for_row_tiles(M, [&](auto mh, auto whole) { launch_wide<mh(), NT, whole()>(X, W, K, tiles, quads, rsc, epi, s); });
 }
 
 // x += act W^T (O and down projections, N = d_model columns) followed by the preparation of the next RMSNorm.
@@ -279,7 +273,7 @@ int residual_splits(int M, int K, int N, size_t floats) {
 void launch_residual_projection(int M, const u16* X, const u16* W, int K, int splits, const EpiResidual& er, float* split,
                                 float* ssq_full, int cls, hipStream_t s) {
     const RowScale none{nullptr, 0, 0.f, 0.f, nullptr};
-    const int MH = (M + 15) / 16, d = er.N;
+    const int d = er.N;
     prof(cls, s);
     if (splits == 1) {
         if (M <= DUO_MAX_ROWS) {
@@ -295,15 +289,11 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, int sp
     if (M > DUO_MAX_ROWS) {
         EpiStoreF32 e{d, M, 1, split, d, (size_t)M * d};
         S = launch_block<1>(X, W, K, d / 16, M, splits, none, e, s);
-    } else switch (MH) {
-        case 1: S = launch_wide_split<1>(X, W, K, d, M, split, none, s); break;
-        case 2: S = launch_wide_split<2>(X, W, K, d, M, split, none, s); break;
-        case 3: S = launch_wide_split<3>(X, W, K, d, M, split, none, s); break;
-        case 4: S = launch_wide_split<4>(X, W, K, d, M, split, none, s); break;
-        default: S = launch_wide_split<5>(X, W, K, d, M, split, none, s); break;
+    } else {
+        for_row_tiles(M, [&](auto mh, auto whole) { S = launch_wide_split<mh(), whole()>(X, W, K, d, M, split, none, s); });
     }
     prof(DUO_PROF_RESID_REDUCE, s);
-    launch_residual_reduce(M, split, S, (size_t)M * d, er.X, er.gain, er.h, d, er.pair_rows, er.h_tiles, er.ssq_part, ssq_full, s);
+    launch_residual_reduce(M, split, S, (size_t)M * d, er.X, er.gain, er.h, d, er.lo_rows, er.h_tiles, er.ssq_part, ssq_full, s);
 }
 
 template <int D>
@@ -365,7 +355,8 @@ PromptAttention prompt_attention(int D, int Hkv, int group, int M, int P, int ma
 void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_kv_cache& cache,
                      const int32_t* tokens, int root_token, const RowPlan& plan, const Workspace& ws,
                      float* logits, int32_t* status, hipStream_t s, double temperature = -1.0) {
-    const int M = plan.M, Mp = (M + 15) / 16 * 16, PR = pair_rows_for(M), AT = a_tiles_for(M, true);
+    const int M = plan.M, Mp = (M + 15) / 16 * 16, AT = a_tiles_for(M, true);
+    const LoRows lo_rows = lo_rows_for(M);
     const int d = c.d_model, D = c.head_dim, half = D / 2, Hq = c.n_q_heads, Hkv = c.n_kv_heads;
     const int qd = Hq * D, F = c.d_ff, V = c.vocab, group = Hq / Hkv;
 
@@ -388,7 +379,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     const bool root_stats = stats && plan.R == 0;
     prof(DUO_PROF_SETUP, s);
     DUO_LAUNCH(setup_kernel, dim3(M + (root_stats ? ROOT_STATS_PARTS : 0)), dim3(256), s, w.embed, tokens, root_token, plan, V,
-               cache.prefix_len, status, ws.x, w.g_attn[0], ws.h, d, PR, AT, ws.ssq, ws.ssq_full, D, (double)c.rope_theta, ws.rope_c,
+               cache.prefix_len, status, ws.x, w.g_attn[0], ws.h, d, lo_rows, AT, ws.ssq, ws.ssq_full, D, (double)c.rope_theta, ws.rope_c,
                ws.rope_s, RootStatsArgs{root_stats ? cache.root_logits : nullptr, V, temperature, ws.stats_root});
 
     // Attention launch shape.  Short contexts: one workgroup of 8 waves per (kv head, row group) does
@@ -475,13 +466,11 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
             // (measured on one box: 768 bands, two splits of six-band workgroups 24.2 + 4.2 us against four splits of
             // twelve-band workgroups 26.6 + 5.5 us; 384 bands, four splits of six-band workgroups 15.2 + 4.6 us against
             // two splits of three-band workgroups 16.7 + 4.1 us)
-            if (M <= 64) {
-                if (qkv_bands > 512) launch_wide_cfg<4, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, 2, qkv_norm, ep, s, &S);
-                else launch_wide_cfg<4, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, QKV_SPLITS, qkv_norm, ep, s, &S);
-            } else {
-                if (qkv_bands > 512) launch_wide_cfg<5, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, 2, qkv_norm, ep, s, &S);
-                else launch_wide_cfg<5, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, QKV_SPLITS, qkv_norm, ep, s, &S);
-            }
+            const int want = qkv_bands > 512 ? 2 : QKV_SPLITS;
+            if (M <= 56) launch_wide_cfg<4, 1, 6, 1, EpiStoreF32, false, false>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
+            else if (M <= 64) launch_wide_cfg<4, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
+            else if (M <= 72) launch_wide_cfg<5, 1, 6, 1, EpiStoreF32, false, false>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
+            else launch_wide_cfg<5, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
             QkvFinishArgs fa{ws.split, S, (size_t)M * ncols, ncols, Hq, Hkv, D, ws.q, qd, ws.q_plane, kc, vc, c.max_seq,
                              ws.rope_c, ws.rope_s, plan, cache.prefix_len};
             prof(DUO_PROF_QKV_FINISH, s);
@@ -491,7 +480,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         else launch_projection<2>(DUO_PROF_QKV, M, ws.h, w.wqkv[l], d, qkv_bands / 2, qkv_norm, eq, s);
 
         AttnArgs aa{ws.q, qd, ws.q_plane, kc, vc, c.max_seq, group, plan, Ktot, bpw, nchunks, mq_pad,
-                    1.4426950408889634f / sqrtf((float)D), ws.part, ws.attn, AT, PR};
+                    1.4426950408889634f / sqrtf((float)D), ws.part, ws.attn, AT, lo_rows};
         prof(DUO_PROF_ATTN, s);
         if (shared_kv) {
             const dim3 grid(nchunks, Hkv, sh_zg);
@@ -512,19 +501,19 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         }
 
         // the residual projections leave x, the next norm's operand u = x * gain and its partial sums
-        EpiResidual eo{d, M, ws.x, d, w.g_ffn[l], ws.h, PR, AT, ws.ssq};
+        EpiResidual eo{d, M, ws.x, d, w.g_ffn[l], ws.h, lo_rows, AT, ws.ssq};
         launch_residual_projection(M, ws.attn, w.wo[l], qd, o_splits, eo, split, ws.ssq_full, DUO_PROF_OPROJ, s);
 
-        EpiSwiGLU eg{F, M, ws.act, AT, PR};
+        EpiSwiGLU eg{F, M, ws.act, AT, lo_rows};
         launch_projection<2>(DUO_PROF_GATEUP, M, ws.h, w.w_gate_up[l], d, F / 16, o_full ? norm_full : norm_part, eg, s);
 
         const u16* gnext = l + 1 < c.n_layers ? w.g_attn[l + 1] : w.g_final;
-        EpiResidual ed{d, M, ws.x, d, gnext, ws.h, PR, AT, ws.ssq};
+        EpiResidual ed{d, M, ws.x, d, gnext, ws.h, lo_rows, AT, ws.ssq};
         launch_residual_projection(M, ws.act, w.w_down[l], F, down_splits, ed, split, ws.ssq_full, DUO_PROF_DOWN, s);
     }
     if (many) {
         prof(DUO_PROF_LMHEAD, s);
-        DUO_LAUNCH(last_row_operand_kernel, dim3(d / 32), dim3(64), s, ws.h, M - 1, PR, AT, ws.h_last);
+        DUO_LAUNCH(last_row_operand_kernel, dim3(d / 32), dim3(64), s, ws.h, M - 1, lo_rows, AT, ws.h_last);
         const RowScale last{ws.ssq + (size_t)(M - 1) * NP, NP, 1.0f / (float)d, c.rms_eps, ws.ssq_full + (size_t)(M - 1) * RowScale::FULL_PARTS};
         EpiStoreF32 el{V, 1, 2, logits, V};
         launch_projection<2>(DUO_PROF_LMHEAD, 1, ws.h_last, w.lm_head, d, (V + 31) / 32, last, el, s);

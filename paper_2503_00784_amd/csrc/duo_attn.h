@@ -36,7 +36,8 @@ struct AttnArgs {
     float scale_log2;     // log2(e) / sqrt(D)
     float* part;          // [Hkv][mq_pad][nchunks][D + 4]: O (unnormalised), max, sum
     u16* out;             // attention output, operand layout of the O projection (bf16 pairs)
-    int out_tiles, pair_rows;
+    int out_tiles;
+    LoRows lo_rows;
 };
 
 // 2^x by the hardware instruction alone: results below the normal range come out as zero, which is all a softmax weight
@@ -63,7 +64,7 @@ __device__ __forceinline__ float raise_reference(float bm, float& m_run) {
 }
 
 // Merge the chunk partials (at most 64) of one (row, query head), normalise, store as a bf16 pair
-// (hi = operand row m, lo = operand row m + pair_rows).  Called by one wave.  Lane cb takes chunk cb's
+// (hi = operand row m, lo = operand row lo_rows(m)).  Called by one wave.  Lane cb takes chunk cb's
 // max and sum (one load each instead of a chain of them), the maximum and the weighted sum are formed by
 // fixed butterflies; the outputs are then added in chunk order, lane handling D/64 channels; the first eight
 // chunks' outputs are requested together with the statistics, further ones four at a time.
@@ -122,7 +123,7 @@ __device__ __forceinline__ void attn_merge_row(const AttnArgs& a, int hk, int r,
         split_elem(o, hi, lo);
         const int col = col0 + lane + e * 64;
         a.out[operand_offset(m, col, a.out_tiles)] = hi;
-        a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = lo;
+        a.out[operand_offset(a.lo_rows(m), col, a.out_tiles)] = lo;
     }
 }
 
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(NWV * 64) void attn_partial_kernel(AttnArgs a) {
                     split_elem(o[mt][dt][i] * inv, hi, lo);
                     const int col = col0 + dt * 16 + g * 4 + i;
                     a.out[operand_offset(m, col, a.out_tiles)] = hi;
-                    a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = lo;
+                    a.out[operand_offset(a.lo_rows(m), col, a.out_tiles)] = lo;
                 }
         } else {
             float* pp = a.part + (((size_t)hk * a.mq_pad + r) * a.nchunks + cb) * (D + 4);
@@ -525,7 +526,7 @@ __global__ __launch_bounds__(512) void attn_small_kernel(AttnArgs a) {
         split_elem(acc[i] * inv, hi, lo);
         const int col = col0 + wave * 16 + g * 4 + i;
         a.out[operand_offset(m, col, a.out_tiles)] = hi;
-        a.out[operand_offset(a.pair_rows + m, col, a.out_tiles)] = lo;
+        a.out[operand_offset(a.lo_rows(m), col, a.out_tiles)] = lo;
     }
 }
 
@@ -793,7 +794,7 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
             split_elem4(o[dt] * inv, hi, lo);
             const int col = col0 + dt * 16 + g * 4;
             *reinterpret_cast<u32x2*>(a.out + operand_offset(m, col, a.out_tiles)) = hi;
-            *reinterpret_cast<u32x2*>(a.out + operand_offset(a.pair_rows + m, col, a.out_tiles)) = lo;
+            *reinterpret_cast<u32x2*>(a.out + operand_offset(a.lo_rows(m), col, a.out_tiles)) = lo;
         }
     } else {
         float* pp = a.part + (((size_t)hk * a.mq_pad + r) * a.nchunks + cb) * (D + 4);

@@ -25,12 +25,24 @@
 // precision costs nothing; a single bf16 per activation would leave rounding noise of ~0.1 in the
 // logits of a 32-layer model.
 #pragma once
+#include <type_traits>
+
 #include "duo_common.h"
 
 // element offset of (row r, column k) in an operand buffer of MT row tiles
 __device__ __forceinline__ size_t operand_offset(int r, int k, int MT) {
     return ((size_t)((k >> 5) * MT + (r >> 4)) * 64 + ((k & 31) >> 3) * 16 + (r & 15)) * 8 + (k & 7);
 }
+
+// Where the lo halves of a paired operand's rows lie (hi halves: row m).  Up to eight rows share one 16-row tile with their lo halves.
+// Beyond that hi and lo halves occupy whole tiles, lo tile = hi tile + M/16 rounded up, so that a lane's hi and lo sums have the same position
+// in their tiles; but where the last tile of a verify pass has one to eight rows it holds their lo halves too, eight rows further on (17, 33,
+// 65 rows, a previously emitted token in front of the drafts: 3, 5, 9 tiles instead of 4, 6, 10).  What bounds the projections at
+// 16..80 rows is the bytes that a compute unit takes in, weights and operand alike.
+struct LoRows {
+    int split, base;  // rows below split: base rows further on, the others eight
+    __device__ __forceinline__ int operator()(int m) const { return m < split ? m + base : m + 8; }
+};
 
 // RMSNorm without a kernel of its own.  The producer of the residual stream (embedding gather or a
 // residual projection) stores, next to x, the operand u = x * gain as bf16 pairs and, per row and per
@@ -222,6 +234,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const u16* __restr
 // the main loop are unconditional with clamped indices and invalid steps multiply by zero: no branches, so
 // the counted waits stay exact.
 //
+// Without WHOLE the last row tile holds one to eight rows and their lo halves (see LoRows): one operand tile less, and one product less
+// per band and K step; the halves of its sums are eight lanes apart.
+//
 // With HALF the operand is the single tile of up to eight rows (hi rows 0..7, lo rows 8..15 of the same tile),
 // as the kernel above uses it, activations first (a lane's quad is four rows of one column); the two halves of the
 // sums are then 32 lanes apart.
@@ -234,12 +249,14 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const u16* __restr
 // One barrier per round hands a filled buffer over and takes a drained one back.  Matrices with few bands
 // put NK waves on each band group: they split the K steps of every round (NK * AG steps) between them and
 // add their partial sums through LDS in wave order at the end.
-template <int MH, int NT, int NG, int NK, int PF, int AG, class Epi, bool HALF = false, bool STREAM = true>
+template <int MH, int NT, int NG, int NK, int PF, int AG, class Epi, bool HALF = false, bool WHOLE = true>
 __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16* __restrict__ X, const u16* __restrict__ W,
                                                                       int K, int split_steps, int ntiles, int quads,
                                                                       RowScale rsc, Epi epi) {
     static_assert(!HALF || MH == 1, "the shared-tile layout holds at most eight rows");
-    constexpr int MT = HALF ? 1 : 2 * MH, NC = NG * NK, NTH = (NC + 1) * 64;
+    static_assert(WHOLE || MH > 1, "up to eight rows alone are the HALF form");
+    constexpr int ML = HALF ? 0 : (WHOLE ? MH : MH - 1);  // tiles of lo halves alone
+    constexpr int MT = MH + ML, NC = NG * NK, NTH = (NC + 1) * 64;
     constexpr int RS = NK * AG;        // K steps per round
     constexpr int BUF = RS * MT * 64;  // 16-byte chunks per ring buffer (one round)
     constexpr int NBUF = 3;
@@ -345,7 +362,7 @@ __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16
         int ls = (i / AG) * RS + nk * AG + (i % AG);
         ls = ls < ns ? ls : ns - 1;
 #pragma unroll
-        for (int t = 0; t < NT; ++t) bb[p][t] = STREAM ? load_frag_stream(wp[t] + (size_t)ls * 512) : load_frag(wp[t] + (size_t)ls * 512);
+        for (int t = 0; t < NT; ++t) bb[p][t] = load_frag_stream(wp[t] + (size_t)ls * 512);
     };
     auto a_frags = [&](int slot, int r, int w) {  // this wave's step w of round r
         const u32x4* ab = lds + (r % NBUF) * BUF + (nk * AG + w) * MT * 64 + lane;
@@ -407,7 +424,7 @@ __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16
 #pragma unroll
                         for (int t = 0; t < NT; ++t) acc[mh][t] = mfma16(b[t], af[p & 1][mh], acc[mh][t]);
 #pragma unroll
-                    for (int mh = 0; mh < MH; ++mh)
+                    for (int mh = 0; mh < ML; ++mh)
 #pragma unroll
                         for (int t = 0; t < NT; ++t)
                             acc[SEP ? MH + mh : mh][t] = mfma16(b[t], af[p & 1][MH + mh], acc[SEP ? MH + mh : mh][t]);
@@ -440,6 +457,12 @@ __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16
                 epi.store(tile, qi, lane & 15, v, pre, use_pre);
             }
         } else {
+            if (!WHOLE && mh == MH - 1) {  // rows 0..7 of the last tile hold hi sums, rows 8..15 the same rows' lo sums; all lanes take part
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[t][i] += __shfl_xor(v[t][i], 8, 64);
+            }
             const int m = mh * 16 + (lane & 15);
             if (m < quads * 4) {
                 if (rsc.part) {
@@ -451,13 +474,14 @@ __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16
             }
         }
     };
+    auto sums = [&](int mh, int t) { return SEP && mh < ML ? acc[mh][t] + acc[MA - ML + mh][t] : acc[mh][t]; };
     if (NK == 1) {
         if (live) {  // wave-uniform
 #pragma unroll
             for (int mh = 0; mh < MH; ++mh) {
                 f32x4 v[NT];
 #pragma unroll
-                for (int t = 0; t < NT; ++t) v[t] = SEP ? acc[mh][t] + acc[MA - MH + mh][t] : acc[mh][t];
+                for (int t = 0; t < NT; ++t) v[t] = sums(mh, t);
                 finish(mh, v, mh == 0);
             }
         }
@@ -468,7 +492,7 @@ __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16
         for (int mh = 0; mh < MH; ++mh)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                red[((wave * MH + mh) * NT + t) * 64 + lane] = SEP ? acc[mh][t] + acc[MA - MH + mh][t] : acc[mh][t];
+                red[((wave * MH + mh) * NT + t) * 64 + lane] = sums(mh, t);
         __syncthreads();
         if (live) {
             for (int mh = nk; mh < MH; mh += NK) {  // K parts added in wave order
@@ -666,7 +690,8 @@ struct EpiResidual {
     int ldx;
     const u16* gain;  // gain of the norm that follows
     u16* h;           // operand buffer of the next projection
-    int pair_rows, h_tiles;
+    LoRows lo_rows;
+    int h_tiles;
     float* ssq_part;  // [M][N/16]
     struct Pre {
         float x[4], g;
@@ -698,7 +723,7 @@ struct EpiResidual {
                 u16 hi, lo;
                 split_elem(xn * gn, hi, lo);
                 h[operand_offset(m, n, h_tiles)] = hi;
-                h[operand_offset(pair_rows + m, n, h_tiles)] = lo;
+                h[operand_offset(lo_rows(m), n, h_tiles)] = lo;
             }
         }
 #pragma unroll
@@ -724,7 +749,7 @@ struct EpiResidual {
             u32x2 hi, lo;
             split_elem4(u, hi, lo);
             *reinterpret_cast<u32x2*>(h + operand_offset(m, n, h_tiles)) = hi;
-            *reinterpret_cast<u32x2*>(h + operand_offset(pair_rows + m, n, h_tiles)) = lo;
+            *reinterpret_cast<u32x2*>(h + operand_offset(lo_rows(m), n, h_tiles)) = lo;
         }
         sq += __shfl_xor(sq, 16, 64);  // the tile's sixteen columns: four lanes, 16 apart
         sq += __shfl_xor(sq, 32, 64);
@@ -733,13 +758,14 @@ struct EpiResidual {
 };
 
 // band 0 = gate rows tile*16.., band 1 = up rows tile*16..; act[m][n] = silu(gate) * up, written as a
-// bf16 pair straight into the down projection's operand buffer (row m hi, row pair_rows + m lo)
+// bf16 pair straight into the down projection's operand buffer (row m hi, row lo_rows(m) lo)
 struct EpiSwiGLU {
     static constexpr const char* NAME = "EpiSwiGLU";
     static constexpr bool NORMALISED_INPUT = true;
     int F, M;
     u16* act;
-    int act_tiles, pair_rows;
+    int act_tiles;
+    LoRows lo_rows;
     struct Pre {};
     __device__ __forceinline__ void arm() {}
     __device__ __forceinline__ void prefetch(int, int, int, Pre&) const {}
@@ -754,7 +780,7 @@ struct EpiSwiGLU {
                 u16 hi, lo;
                 split_elem(gate / (1.f + expf(-gate)) * up, hi, lo);
                 act[operand_offset(m, n, act_tiles)] = hi;
-                act[operand_offset(pair_rows + m, n, act_tiles)] = lo;
+                act[operand_offset(lo_rows(m), n, act_tiles)] = lo;
             }
         }
     }
@@ -767,7 +793,7 @@ struct EpiSwiGLU {
         u32x2 hi, lo;
         split_elem4(a, hi, lo);
         *reinterpret_cast<u32x2*>(act + operand_offset(m, n, act_tiles)) = hi;
-        *reinterpret_cast<u32x2*>(act + operand_offset(pair_rows + m, n, act_tiles)) = lo;
+        *reinterpret_cast<u32x2*>(act + operand_offset(lo_rows(m), n, act_tiles)) = lo;
     }
 };
 
@@ -888,11 +914,19 @@ struct EpiQKV {
     }
 };
 
-// Rows of the A operand for M paired activations: hi rows [0, pair_rows), lo rows [pair_rows, 2*pair_rows).
-// Up to eight rows share one 16-row tile with their lo halves; beyond that hi and lo halves occupy whole tiles
-// (lo tile = hi tile + M/16 rounded up), so a lane's hi and lo sums have the same position in their tiles.
+// Rows of the A operand for M paired activations, hi and lo halves in whole tiles beyond eight rows: pair_rows each.
 static inline int pair_rows_for(int M) { return M <= 8 ? 8 : (M + 15) / 16 * 16; }
-static inline int a_tiles_for(int M, bool paired) { return paired ? (2 * pair_rows_for(M) + 15) / 16 : (M + 15) / 16; }
+// The last tile holds its rows' lo halves too (see LoRows): up to sixteen rows the one-band kernels read whole tiles, prompt chunks of more
+// than 80 rows are padded to larger blocks anyway.
+static inline bool half_tail(int M) { return M > 16 && M <= DUO_MAX_ROWS && (M - 1) % 16 < 8; }
+static inline int a_tiles_for(int M, bool paired) {
+    return paired ? (2 * pair_rows_for(M) + 15) / 16 - (half_tail(M) ? 1 : 0) : (M + 15) / 16;
+}
+static inline LoRows lo_rows_for(int M) {
+    const int pr = pair_rows_for(M);
+    if (M <= 8) return LoRows{0, 0};
+    return half_tail(M) ? LoRows{pr - 16, pr} : LoRows{pr, pr};
+}
 
 template <int MT, int NT, int NW, class Epi>
 static inline void launch_gemm_cfg(const u16* X, const u16* W, int K, int tiles, int quads, int pq, const RowScale& rsc,
@@ -913,7 +947,7 @@ static inline void launch_gemm(const u16* X, const u16* W, int K, int tiles, int
     else launch_gemm_cfg<MT, NT, NWK>(X, W, K, tiles, quads, pq, rsc, epi, s);
 }
 
-// M output rows; paired: the activations are bf16 pairs (rows m and pair_rows + m of the operand).
+// M output rows, at most 16 if paired: the activations are bf16 pairs (rows m and pair_rows + m of the operand).
 template <int NT, class Epi>
 static inline void launch_gemm_rows(int M, bool paired, const u16* X, const u16* W, int K, int tiles, const RowScale& rsc,
                                     const Epi& epi, hipStream_t s) {
@@ -940,11 +974,11 @@ static inline void launch_gemm_rows(int M, bool paired, const u16* X, const u16*
 constexpr int WIDE_MAX_SPLIT = 8;
 constexpr int WIDE_PF = 8, WIDE_AG = 4;
 
-template <int MH, int NT, int NG, int NK, class Epi, bool HALF = false, bool STREAM = true, int PFW = WIDE_PF>
+template <int MH, int NT, int NG, int NK, class Epi, bool HALF = false, bool WHOLE = true, int PFW = WIDE_PF>
 static inline void launch_wide_cfg(const u16* X, const u16* W, int K, int tiles, int quads, int splits, const RowScale& rsc,
                                    const Epi& epi, hipStream_t s, int* splits_out) {
-    // rounds of NK * AG K steps; a round's operand tiles (2*MH per step) must fit the producer's counted wait
-    constexpr int AG = (NK * WIDE_AG * (HALF ? 1 : 2 * MH) <= 63) ? WIDE_AG : 2;
+    // rounds of NK * AG K steps; three rounds of operand tiles fit LDS (and one the producer's counted wait)
+    constexpr int AG = (NK * WIDE_AG * (HALF ? 1 : WHOLE ? 2 * MH : 2 * MH - 1) <= 52) ? WIDE_AG : 2;
     constexpr int RS = NK * AG;
     const int steps = K >> 5;
     int split_steps = (steps + splits - 1) / splits;
@@ -952,20 +986,20 @@ static inline void launch_wide_cfg(const u16* X, const u16* W, int K, int tiles,
     const int S = (steps + split_steps - 1) / split_steps;
     if (splits_out) *splits_out = S;
     DUO_KERNEL_NAME("gemm_wide_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s>", MH, NT, NG, NK, PFW, AG, Epi::NAME, HALF ? "true" : "false",
-                    STREAM ? "true" : "false");
-    DUO_LAUNCH((gemm_wide_kernel<MH, NT, NG, NK, PFW, AG, Epi, HALF, STREAM>), dim3((tiles + NG - 1) / NG, S),
+                    WHOLE ? "true" : "false");
+    DUO_LAUNCH((gemm_wide_kernel<MH, NT, NG, NK, PFW, AG, Epi, HALF, WHOLE>), dim3((tiles + NG - 1) / NG, S),
                dim3((NG * NK + 1) * 64), s, X, W, K, split_steps, tiles, quads, rsc, epi);
 }
 
 // Projections with many bands (QKV, gate/up, LM head): no K split, the epilogue finishes the rows.
-template <int MH, int NT, class Epi>
+template <int MH, int NT, bool WHOLE, class Epi>
 static inline void launch_wide(const u16* X, const u16* W, int K, int tiles, int quads, const RowScale& rsc, const Epi& epi,
                                hipStream_t s) {
     // few bands: two waves per band group split K, so that four SIMDs per compute unit issue MFMAs
     const int ng = (tiles + 255) / 256;
-    if (ng <= 1) launch_wide_cfg<MH, NT, 1, 2>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
-    else if (ng == 2) launch_wide_cfg<MH, NT, 2, 2>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
-    else if (ng == 3) launch_wide_cfg<MH, NT, 3, 1>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
+    if (ng <= 1) launch_wide_cfg<MH, NT, 1, 2, Epi, false, WHOLE>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
+    else if (ng == 2) launch_wide_cfg<MH, NT, 2, 2, Epi, false, WHOLE>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
+    else if (ng == 3) launch_wide_cfg<MH, NT, 3, 1, Epi, false, WHOLE>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
     // Many bands: eight waves of four weight slots stage the operand half as often.  What counts are rounds of workgroups, one per
     // compute unit: a full round of eight waves takes 2.03 / 1.98 / 1.96 / 1.84 / 1.65 rounds of four at 16 / 32 / 48 / 64 / 80 rows.
     // An odd number of small rounds leaves the last large one half empty (3072 tiles x 4096 channels: 135 / 144 / 156 / 166 / 178 us
@@ -974,8 +1008,8 @@ static inline void launch_wide(const u16* X, const u16* W, int K, int tiles, int
     // 189 / 196 / 201 / 204 / 194).  Neither is left where two small rounds are full (2048 tiles, 16 and 32 rows: 91 / 93 against
     // 94 / 95; even at 1792: 80 / 84 against 80 / 81) nor, at 16 rows, over many rounds (8192 tiles: 372 against 378).
     else if (const int rounds = (tiles + 1023) / 1024; rounds % 2 == 0 && (MH > 2 || (rounds == 2 ? tiles <= 1792 : (MH == 2 || rounds == 4))))
-        launch_wide_cfg<MH, NT, 8, 1, Epi, false, true, 4>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
-    else launch_wide_cfg<MH, NT, 4, 1>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
+        launch_wide_cfg<MH, NT, 8, 1, Epi, false, WHOLE, 4>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
+    else launch_wide_cfg<MH, NT, 4, 1, Epi, false, WHOLE>(X, W, K, tiles, quads, 1, rsc, epi, s, nullptr);
 }
 
 // Up to eight rows (hi and lo halves in one operand tile): the same kernel pays for matrices of 257..768 workgroup
@@ -992,7 +1026,7 @@ static inline bool launch_wide_half(const u16* X, const u16* W, int K, int tiles
 
 // Projections with few bands (O, down): K is split over the grid's y dimension and the workgroups store
 // partial results [split][M][N]; residual_reduce_kernel adds them in split order.  Returns the number of splits.
-template <int MH>
+template <int MH, bool WHOLE>
 static inline int launch_wide_split(const u16* X, const u16* W, int K, int N, int M, float* part, const RowScale& rsc,
                                     hipStream_t s) {
     EpiStoreF32 e{N, M, 1, part, N, (size_t)M * N};
@@ -1000,6 +1034,24 @@ static inline int launch_wide_split(const u16* X, const u16* W, int K, int N, in
     int S = 1;
     // eight splits of eight-band workgroups, also for the shorter K of the O projection (measured at 64 rows, 4096 x 4096:
     // 11.7 against 12.2 us for four splits of four-band workgroups)
-    launch_wide_cfg<MH, 1, 8, 1>(X, W, K, N / 16, quads, WIDE_MAX_SPLIT, rsc, e, s, &S);
+    launch_wide_cfg<MH, 1, 8, 1, EpiStoreF32, false, WHOLE>(X, W, K, N / 16, quads, WIDE_MAX_SPLIT, rsc, e, s, &S);
     return S;
+}
+
+// f(row tiles, whether hi and lo halves lie in whole tiles) for 9..80 rows
+template <class F>
+static inline void for_row_tiles(int M, F f) {
+    using std::integral_constant;
+    const bool whole = !half_tail(M);
+#define DUO_ROW_TILES(MH)                                                                                   \
+    if (whole) f(integral_constant<int, MH>{}, integral_constant<bool, true>{});                             \
+    else f(integral_constant<int, MH>{}, integral_constant<bool, false>{})
+    switch ((M + 15) / 16) {
+        case 1: f(integral_constant<int, 1>{}, integral_constant<bool, true>{}); break;
+        case 2: DUO_ROW_TILES(2); break;
+        case 3: DUO_ROW_TILES(3); break;
+        case 4: DUO_ROW_TILES(4); break;
+        default: DUO_ROW_TILES(5); break;
+    }
+#undef DUO_ROW_TILES
 }

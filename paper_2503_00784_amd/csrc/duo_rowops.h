@@ -40,7 +40,7 @@ struct RootStatsArgs {
 __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embed, const int32_t* __restrict__ tokens, int root_token,
                                                      RowPlan plan, int vocab, const int32_t* prefix_len, int32_t* status,
                                                      float* __restrict__ x, const u16* __restrict__ gain, u16* __restrict__ h, int d,
-                                                     int pair_rows, int tiles, float* __restrict__ ssq_part, float* __restrict__ ssq_full,
+                                                     LoRows lo_rows, int tiles, float* __restrict__ ssq_part, float* __restrict__ ssq_full,
                                                      int D, double theta, float* __restrict__ rc, float* __restrict__ rs, RootStatsArgs root) {
     __shared__ float wsum[4];
     __shared__ double sm[16];
@@ -87,7 +87,7 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
         *reinterpret_cast<f32x4*>(xr + j8) = xv[0];
         *reinterpret_cast<f32x4*>(xr + j8 + 4) = xv[1];
         *reinterpret_cast<u32x4*>(h + operand_offset(m, j8, tiles)) = hi.q;
-        *reinterpret_cast<u32x4*>(h + operand_offset(pair_rows + m, j8, tiles)) = lo.q;
+        *reinterpret_cast<u32x4*>(h + operand_offset(lo_rows(m), j8, tiles)) = lo.q;
         total += sq;
         sq += __shfl_xor(sq, 1, 64);  // two runs of eight = one 16-column tile
         if (!(threadIdx.x & 1)) ssq_part[(size_t)m * (d >> 4) + (j8 >> 4)] = sq;
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
 template <int NWV, int MAXS>
 __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* __restrict__ part, int S, size_t split_stride,
                                                                    float* __restrict__ x, const u16* __restrict__ gain,
-                                                                   u16* __restrict__ h, int d, int pair_rows, int tiles,
+                                                                   u16* __restrict__ h, int d, LoRows lo_rows, int tiles,
                                                                    float* __restrict__ ssq_part, float* __restrict__ ssq_full) {
     __shared__ float wsum[NWV];
     const int m = blockIdx.x, P = gridDim.y, cols = d / P, c0 = blockIdx.y * cols;
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* 
             split_elem(xv * elem_to_f32(gv.h[j]), hi.h[j], lo.h[j]);
         }
         *reinterpret_cast<u32x4*>(h + operand_offset(m, j8, tiles)) = hi.q;
-        *reinterpret_cast<u32x4*>(h + operand_offset(pair_rows + m, j8, tiles)) = lo.q;
+        *reinterpret_cast<u32x4*>(h + operand_offset(lo_rows(m), j8, tiles)) = lo.q;
         total += sq;
         sq += __shfl_xor(sq, 1, 64);
         if (!(threadIdx.x & 1)) ssq_part[(size_t)m * (d >> 4) + (j8 >> 4)] = sq;
@@ -167,12 +167,12 @@ static inline int reduce_parts(int M, int d) {
     return P;
 }
 static inline void launch_residual_reduce(int M, const float* part, int S, size_t split_stride, float* x, const u16* gain,
-                                          u16* h, int d, int pair_rows, int tiles, float* ssq_part, float* ssq_full,
+                                          u16* h, int d, LoRows lo_rows, int tiles, float* ssq_part, float* ssq_full,
                                           hipStream_t s) {
     const int P = reduce_parts(M, d), cols = d / P;
     const dim3 grid(M, P);
 #define DUO_REDUCE(NWV, MAXS)                                                                                                  \
-    DUO_LAUNCH((residual_reduce_kernel<NWV, MAXS>), grid, dim3(NWV * 64), s, part, S, split_stride, x, gain, h, d, pair_rows, tiles, \
+    DUO_LAUNCH((residual_reduce_kernel<NWV, MAXS>), grid, dim3(NWV * 64), s, part, S, split_stride, x, gain, h, d, lo_rows, tiles, \
                ssq_part, ssq_full)
 #define DUO_REDUCE_COLS(MAXS)                     \
     do {                                          \
@@ -295,15 +295,15 @@ __global__ void status_init_kernel(int32_t* status, const int32_t* prefix_len, i
     if (blockIdx.x == 0 && threadIdx.x == 0) *status = (prefix_len && *prefix_len != host_P) ? 2 : 0;
 }
 
-// Row m of a paired operand buffer (hi at row m, lo at row pair_rows + m; `tiles` row tiles per K step) as an operand
+// Row m of a paired operand buffer (hi at row m, lo at row lo_rows(m); `tiles` row tiles per K step) as an operand
 // of its own for a one-row product: one tile per K step, hi in row 0, lo in row 8, all other rows zero.
 // grid = K/32 workgroups of one wave.
-__global__ __launch_bounds__(64) void last_row_operand_kernel(const u16* __restrict__ src, int m, int pair_rows, int tiles,
+__global__ __launch_bounds__(64) void last_row_operand_kernel(const u16* __restrict__ src, int m, LoRows lo_rows, int tiles,
                                                               u16* __restrict__ dst) {
     const int ks = blockIdx.x, lane = threadIdx.x, r = lane & 15, g = lane >> 4;
     u32x4 v = {0u, 0u, 0u, 0u};
     if (r == 0 || r == 8) {
-        const int row = r == 0 ? m : pair_rows + m;
+        const int row = r == 0 ? m : lo_rows(m);
         v = *reinterpret_cast<const u32x4*>(src + (((size_t)ks * tiles + (row >> 4)) * 64 + g * 16 + (row & 15)) * 8);
     }
     *reinterpret_cast<u32x4*>(dst + ((size_t)ks * 64 + lane) * 8) = v;

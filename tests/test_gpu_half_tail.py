@@ -1,0 +1,50 @@
+"""Operand layout of 17..80 rows whose last row tile holds one to eight rows: that tile holds their lo halves too.  Whole steps against the
+oracle at both edges of every tile count, in the launch shapes of a small model (two waves per band group) and of the 7B layer (three
+band groups per workgroup, split projections, partial results of Q/K/V), and the layout's map by itself."""
+import pytest
+
+from paper_2503_00784_amd import inputs
+from tests.gpu_util import say
+from tests.test_gpu_parity import _check_step, _engine_and_oracle
+
+
+def lo_row(M, m):
+    """The rule of LoRows / lo_rows_for, restated: (tiles, operand row of row m's lo half; its hi half is row m)."""
+    T = 1 if M <= 8 else (M + 15) // 16
+    if M <= 8:
+        return 1, m + 8
+    if 16 < M <= 80 and (M - 1) % 16 < 8:
+        return 2 * T - 1, (m + 16 * T if m < 16 * (T - 1) else m + 8)
+    return 2 * T, m + 16 * T
+
+
+@pytest.mark.parametrize("M", list(range(1, 82)) + [333, 1024])
+def test_every_half_has_a_row_of_its_own(M):
+    tiles = lo_row(M, 0)[0]
+    rows = list(range(M)) + [lo_row(M, m)[1] for m in range(M)]
+    assert len(set(rows)) == 2 * M and max(rows) < 16 * tiles <= 2 * 16 * ((M + 15) // 16)
+    assert tiles == -(-2 * M // 16) or M > 80 or (M - 1) % 16 >= 8  # no tile more than 2 M rows need where the last tile is shared
+
+
+ROWS = [(1, 16, 3), (3, 6, -1), (3, 8, -1), (5, 5, -1), (4, 8, -1), (4, 8, 3), (5, 8, -1), (5, 8, 3), (6, 8, 3), (7, 8, -1), (7, 8, 3), (4, 16, 3), (6, 12, -1), (6, 12, 3)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k,root", ROWS)
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+def test_small_model_at_the_edges_of_the_tiles(n, k, root, dtype):
+    from paper_2503_00784_amd import binding as B
+    if dtype == "fp16" and (n * k) % 8:
+        pytest.skip("the other element type at half of the edges")
+    say(f"MID {dtype} rows={n * k + (root >= 0)}")
+    w, oshape, eng, cache = _engine_and_oracle(B, inputs.MID, 60, 160, seed=n, synthetic_cache=True, dtype=dtype)
+    _check_step(B, inputs.MID, w, oshape, eng, cache, n, k, seed=k, mode=0, root_token=root)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k,root", [(1, 16, 3), (4, 8, 3), (5, 8, -1), (6, 8, 3), (7, 8, -1), (4, 16, 3), (6, 12, -1)])
+def test_layer_of_the_large_model(n, k, root):
+    from paper_2503_00784_amd import binding as B
+    say(f"WIDE7 rows={n * k + (root >= 0)}")
+    w, oshape, eng, cache = _engine_and_oracle(B, inputs.WIDE7, 60, 160, seed=n, synthetic_cache=True)
+    _check_step(B, inputs.WIDE7, w, oshape, eng, cache, n, k, seed=k, mode=0, root_token=root)
