@@ -12,8 +12,7 @@
 //     between the two products;
 //   - queries and softmax weights enter the MFMAs as bf16 pairs (hi + lo), keys and values are the
 //     cache's bf16;
-//   - the softmax is online (reference and sum per row, see REF_SLACK); lane groups exchange maxima by
-//     wavefront shuffles only where the reference moves.
+//   - the softmax is online (running max / sum per row), reduced across the four lane groups by lane swaps.
 // The waves are merged through LDS in a fixed chain, chunk partials (max, sum, unnormalised O)
 // go to scratch and are merged in chunk order: by the same workgroup when a head is one chunk (short
 // prefixes: one kernel per layer), by a small second kernel otherwise.
@@ -44,23 +43,15 @@ struct AttnArgs {
 // that small amounts to; 2^0 is exactly 1 and 2^-inf exactly 0.
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Online softmax against a reference that lags the running maximum: it is raised to the maximum only where a key of the block lies more
-// than 2^REF_SLACK above it.  Sums, weights and outputs are floating point, so they are as accurate relative to any reference within
-// 2^8 of the maximum as relative to the maximum itself (fp16 weights stay below 2^8, and small ones lose less); chunks, waves and teams
-// are merged by their references as they were by their maxima.  What it saves is per block: the exchange of the maximum between the
-// four lane groups (two dependent LDS-crossbar trips in front of the exponentials) and the rescaling of the output, which with the exact
-// maximum of sixteen rows happens in nearly every block of a chunk of twenty.  1024 prompt rows behind 1024 keys on 32 heads 75 -> 65 us, 65 rows
-// of eight groups of four behind 8192 keys 31 -> 26.5, 33 rows of 32 heads behind 2048 11.2 -> 10.6, 64 behind 4096 19.2 -> 18.9.
-constexpr float REF_SLACK = 8.f;
-// bm: this lane's largest scaled score of the block.  Raises m_run (the same in the four lane groups of a row) and returns the factor
-// for what has been added up so far.  All lanes of the wave call it.
-__device__ __forceinline__ float raise_reference(float bm, float& m_run) {
-    bm = fmaxf(bm, __shfl_xor(bm, 16, 64));
-    bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
-    const float m_new = fmaxf(m_run, bm);
-    const float alpha = exp2_raw(m_run - (m_new == -INFINITY ? 0.f : m_new));
-    m_run = m_new;
-    return alpha;
+// The largest of the four lane groups' values (lanes c, c + 16, c + 32, c + 48), in all of them.  Lane swaps within the vector unit: the maximum of
+// a block stands between its scores and its exponentials, and two dependent shuffles through the LDS crossbar, which eight waves keep busy
+// with operand reads, are two trips there (1024 prompt rows behind 1024 keys on 32 heads 75.6 -> 74.0 us, 65 rows of eight groups of four
+// behind 8192 keys 31.4 -> 30.3).
+__device__ __forceinline__ float lane_groups_max(float x) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
 // Merge the chunk partials (at most 64) of one (row, query head), normalise, store as a bf16 pair
@@ -243,13 +234,15 @@ __global__ __launch_bounds__(NWV * 64) void attn_partial_kernel(AttnArgs a) {
             float bm = sc[0];
 #pragma unroll
             for (int j = 1; j < 8; ++j) bm = fmaxf(bm, sc[j]);
-            if (__ballot(bm > m_run[mt] + REF_SLACK) != 0) {  // wave-uniform
-                const float alpha = raise_reference(bm, m_run[mt]);
-                l_run[mt] *= alpha;
+            const float m_new = fmaxf(m_run[mt], lane_groups_max(bm));
+            const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = exp2_raw(m_run[mt] - m_safe);
+            m_run[mt] = m_new;
+            l_run[mt] *= alpha;
+            if (__ballot(alpha != 1.0f) != 0) {
 #pragma unroll
                 for (int dt = 0; dt < DT; ++dt) o[mt][dt] = o[mt][dt] * alpha;
             }
-            const float m_safe = m_run[mt] == -INFINITY ? 0.f : m_run[mt];
             // the weights enter the MFMA as a bf16 pair hi + lo (16 mantissa bits): rounding them to a
             // single bf16 would add as much noise to O as the bf16 rounding of O itself
             Frag8 pf, pl;
@@ -456,8 +449,7 @@ __global__ __launch_bounds__(512) void attn_small_kernel(AttnArgs a) {
     for (int b = 0; b < BATCH; ++b)
 #pragma unroll
         for (int j = 0; j < 8; ++j) mx = fmaxf(mx, sc[b][j]);
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = lane_groups_max(mx);
     const float m_safe = mx == -INFINITY ? 0.f : mx;
     float m_run = mx, l_run = 0.f;
     f32x4 o[DT];
@@ -715,14 +707,10 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
         float bm = sc[0];
 #pragma unroll
         for (int j = 1; j < 8; ++j) bm = fmaxf(bm, sc[j]);
-        bm *= a.scale_log2;  // the reference is kept in scaled units
-        if (__ballot(bm > m_run + REF_SLACK) != 0) {  // wave-uniform
-            const float alpha = raise_reference(bm, m_run);
-            l_run *= alpha;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) o[dt] = o[dt] * alpha;
-        }
-        const float m_safe = m_run == -INFINITY ? 0.f : m_run;
+        const float m_new = fmaxf(m_run, lane_groups_max(bm) * a.scale_log2);  // the running maximum is kept in scaled units
+        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+        const float alpha = exp2_raw(m_run - m_safe);
+        m_run = m_new;
         float pw[8], ps = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -730,7 +718,12 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
             ps += pw[j];
         }
         split_elem8(pw, pf.q, pl.q);  // softmax weights as bf16 pairs (hi + lo)
-        l_run += ps;
+        l_run = l_run * alpha + ps;
+        // the running maximum rarely moves after the first blocks: rescale only when some row's did
+        if (__ballot(alpha != 1.0f) != 0) {
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) o[dt] = o[dt] * alpha;
+        }
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt) {
             Frag8 vf = frag(KT + dt);

@@ -1,6 +1,5 @@
-"""Online softmax against a reference that lags the running maximum by up to 2^8: prefixes whose scores climb, fall and jump by more
-and by less than that from one block of 32 keys to the next, for every attention kernel that loops over blocks.  Whole steps against
-the oracle."""
+"""The online softmax's running maximum, its exchange between lane groups and the rescaling of what has been added up: prefixes whose
+scores climb, fall and jump from one block of 32 keys to the next, in every attention launch shape.  Whole steps against the oracle."""
 import numpy as np
 import pytest
 
@@ -23,8 +22,7 @@ def _key_scales(pattern, P):
     return np.random.default_rng(P).choice([0.1, 1.0, 4.0, 30.0], (P + 31) // 32).repeat(32)[:P]
 
 
-# query tiles (rows x group / 16) and contexts: the per-wave kernel (one tile, two tiles on a short context), the shared one in teams of
-# two, four and five waves and as one team of eight
+# query tiles (rows x group / 16) and contexts: one and two tiles, teams of two, four and five waves and one team of eight
 @pytest.mark.parametrize("pattern", ["climb", "fall", "jump"])
 @pytest.mark.parametrize("shape,P,n,k,root", [(G64, 1500, 1, 4, -1), (H128, 1500, 1, 8, -1), (H128, 1500, 2, 8, -1), (G64, 500, 1, 8, -1), (H128, 500, 2, 16, -1),
                                               (H128, 1500, 2, 16, -1), (G64, 1500, 1, 12, 3), (H128, 1500, 4, 12, 3), (H128, 2200, 4, 16, 5),
