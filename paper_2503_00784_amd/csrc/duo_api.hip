@@ -208,17 +208,6 @@ inline void prof(int cls, hipStream_t) {
     ++g_prof.used;
 }
 
-template <int D>
-void launch_attention(int mtw, int nwv, dim3 grid, const AttnArgs& a, hipStream_t s) {
-    if (nwv == 8) {
-        if (mtw == 1) DUO_LAUNCH((attn_partial_kernel<D, 1, 8>), grid, dim3(512), s, a);
-        else if (D == 64) DUO_LAUNCH((attn_partial_kernel<64, 2, 8>), grid, dim3(512), s, a);
-    } else {
-        if (mtw == 1) DUO_LAUNCH((attn_partial_kernel<D, 1, 4>), grid, dim3(256), s, a);
-        else DUO_LAUNCH((attn_partial_kernel<D, 2, 4>), grid, dim3(256), s, a);
-    }
-}
-
 // A projection whose epilogue finishes the rows (QKV, gate/up, LM head).  Up to eight rows every wave streams
 // its own bands and reads the activations itself; beyond that the waves of a workgroup share the activation
 // operand through LDS.
@@ -382,22 +371,19 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
                cache.prefix_len, status, ws.x, w.g_attn[0], ws.h, d, lo_rows, AT, ws.ssq, ws.ssq_full, D, (double)c.rope_theta, ws.rope_c,
                ws.rope_s, RootStatsArgs{root_stats ? cache.root_logits : nullptr, V, temperature, ws.stats_root});
 
-    // Attention launch shape.  Short contexts: one workgroup of 8 waves per (kv head, row group) does
-    // the whole head and writes the output itself.  Long contexts: the keys are cut into chunks for
-    // more workgroups, and a second small kernel merges the chunk partials.
+    // Attention launch shape.  One query tile per kv head on a short context: one workgroup of 8 waves per kv head does the whole head
+    // without a loop.  Otherwise the kernel that stages K/V blocks in LDS for all query tiles, one query tile per wave: with the keys cut into
+    // chunks for more workgroups and a second small kernel that merges the chunk partials, or in one chunk without one.
     const int Ktot = plan.P + M;
     const int NB = (Ktot + 31) / 32;
     const int MQ = M * group, MqT = (MQ + 15) / 16;
-    const int mtw = MqT >= 2 ? 2 : 1;
-    const int MG = (MqT + mtw - 1) / mtw;
     const int mq_pad = Mp * group;
-    // Two or more query tiles per kv head: the kernel that stages K/V blocks in LDS for all query tiles
-    // (two tiles on a short context stay with the per-wave kernel, which then needs no chunk merge).
-    const bool shared_kv = MqT > 2 || (MqT == 2 && NB > 32);
-    int sh_nwv = 4, sh_zg = 1, sh_ksplit = 1;
-    int nwv, bpw, nchunks;
+    // One tile: the no-loop kernel against chunks and merge, 32 heads of 128: 400 keys 8.8 against 10.6 us, 700 11.6 against 10.8, 980 14.2
+    // against 11.6; 8 heads 9.5 / 10.0, 12.5 / 9.8, 14.8 / 10.2; heads of 64 8.8 against 9.6 at 980, the most it holds.
+    const bool shared_kv = MqT > 1 || NB > 32 || (D == 128 && NB > 20);
+    int sh_nwv = 4, sh_zg = 1, sh_ksplit = 1, bpw = 0, nchunks = 1;
     if (shared_kv) {
-        // one query tile per wave, about 256 workgroups (one per compute unit): measured best for 4 tiles x 32 heads and 16 tiles x 8 heads
+        // about 256 workgroups (one per compute unit): measured best for 4 tiles x 32 heads and 16 tiles x 8 heads
         // Up to four tiles: two teams of waves share the blocks (two waves per SIMD: 20.7 against 23.2 us at 4 tiles,
         // 11.8 against 14.4 us at 2 tiles, measured on 32 heads x 4160 / 2080 keys).
         // 9..16 tiles (64 rows x a GQA group of 4): 27.3 against 28.2 us at 8192 keys; 17..20 tiles (65..80 rows) in the same shape
@@ -420,24 +406,15 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         // heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us)
         int target = 256 / (Hkv * sh_zg);
         target = target < 1 ? 1 : (target > max_chunks ? max_chunks : target);
+        // A short context is one chunk, the merge costs 4.3 us and its launch.  One chunk against chunks and merge, 32 heads of 128: two tiles
+        // 250 / 400 / 700 keys 9.0 / 9.6 / 13.4 against 10.9 / 11.4 / 11.7 us, three 10.3 / 11.7 / 15.9 against 11.4 / 11.6 / 12.5, four 10.8 /
+        // 12.9 against 12.1 / 12.6; one team of eight: five tiles 120 / 250 keys 10.3 / 13.6 against 12.0 / 12.2; 17 tiles on eight heads 250 / 400
+        // keys 12.0 / 14.5 against 13.4 / 13.9.
+        if (NB <= (MqT <= 2 ? 16 : sh_ksplit == 2 ? 10 : 5)) target = 1;
         if (many) target = prompt.chunks;
         bpw = (NB + target - 1) / target;  // blocks per chunk
         bpw = bpw < 2 ? 2 : bpw;
         nchunks = (NB + bpw - 1) / bpw;
-        nwv = sh_nwv;
-    } else if (NB <= 32) {
-        nwv = (mtw == 2 && D == 128) ? 4 : 8;  // register budget of the two-tile, 128-channel variant
-        bpw = (NB + nwv - 1) / nwv;
-        nchunks = 1;
-    } else {
-        // about 224 workgroups, at least two blocks per wave (measured on 32 heads x 2080 keys: 192 workgroups
-        // of 3 blocks per wave take 14 us, 544 of one block 24 us)
-        nwv = 4;
-        int target = (224 + Hkv * MG - 1) / (Hkv * MG);
-        target = target < 1 ? 1 : (target > max_chunks ? max_chunks : target);
-        bpw = (NB + 4 * target - 1) / (4 * target);
-        bpw = bpw < 2 ? 2 : bpw;
-        nchunks = (NB + 4 * bpw - 1) / (4 * bpw);
     }
 
     // The bands of the Q/K/V matrix are independent of each other, so a wave may take one or two.  One band per wave
@@ -486,13 +463,10 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
             const dim3 grid(nchunks, Hkv, sh_zg);
             if (D == 128) launch_attention_shared<128>(sh_nwv, sh_ksplit, grid, aa, s);
             else launch_attention_shared<64>(sh_nwv, sh_ksplit, grid, aa, s);
-        } else if (NB <= 32 && MqT == 1) {  // short context, one query tile: the no-loop kernel
-            if (D == 128) DUO_LAUNCH((attn_small_kernel<128, 4>), dim3(1, Hkv), dim3(512), s, aa);
-            else DUO_LAUNCH((attn_small_kernel<64, 4>), dim3(1, Hkv), dim3(512), s, aa);
         } else if (D == 128) {
-            launch_attention<128>(mtw, nwv, dim3(nchunks, Hkv, MG), aa, s);
+            DUO_LAUNCH((attn_small_kernel<128, 4>), dim3(1, Hkv), dim3(512), s, aa);
         } else {
-            launch_attention<64>(mtw, nwv, dim3(nchunks, Hkv, MG), aa, s);
+            DUO_LAUNCH((attn_small_kernel<64, 4>), dim3(1, Hkv), dim3(512), s, aa);
         }
         if (nchunks > 1) {
             prof(DUO_PROF_ATTN_COMB, s);

@@ -118,237 +118,6 @@ __device__ __forceinline__ void attn_merge_row(const AttnArgs& a, int hk, int r,
     }
 }
 
-template <int D, int MTW, int NWV>
-__global__ __launch_bounds__(NWV * 64) void attn_partial_kernel(AttnArgs a) {
-    constexpr int KS = D / 32;  // MFMA K steps of the QK^T product
-    constexpr int DT = D / 16;  // 16-channel tiles of the PV product
-    constexpr int NBUF = NWV / 2;
-    __shared__ f32x4 lds_o[NBUF][MTW * DT * 64];
-    __shared__ float lds_ml[NBUF][MTW][2][16];
-
-    const int cb = blockIdx.x, hk = blockIdx.y, mg = blockIdx.z;
-    // scalar wave index: MFMA ignores the EXEC mask, so all control flow around it must be wave-uniform
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int c = lane & 15, g = lane >> 4;
-    const int MQ = a.plan.M * a.group;
-
-    // Visibility of draft slots, branch-free: with mk = key - P, row m sees mk < R (prefix and root)
-    // and vis_lo <= mk <= vis_hi (its own sequence up to itself).
-    elem8 qf[MTW][KS], ql[MTW][KS];
-    int vis_lo[MTW], vis_hi[MTW];
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        // query operand (B of S^T = K Q^T): column c of tile mt is pair r = (row m, head gq of the group)
-        const int r = (mg * MTW + mt) * 16 + c;
-        const bool ok = r < MQ;
-        const int m = ok ? r / a.group : 0, gq = ok ? r % a.group : 0;
-        const int R = a.plan.R;
-        vis_lo[mt] = !ok ? 0x7fffffff : (m < R ? 0 : R + ((m - R) / a.plan.k) * a.plan.k);
-        vis_hi[mt] = ok ? m : -1;
-        const u16* qp = a.q + (size_t)m * a.ldq + (hk * a.group + gq) * D + g * 8;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            Frag8 f;
-            f.q = ok ? *reinterpret_cast<const u32x4*>(qp + ks * 32) : u32x4{0u, 0u, 0u, 0u};
-            qf[mt][ks] = f.v;
-            f.q = ok ? *reinterpret_cast<const u32x4*>(qp + a.q_plane + ks * 32) : u32x4{0u, 0u, 0u, 0u};
-            ql[mt][ks] = f.v;
-        }
-    }
-
-    f32x4 o[MTW][DT];
-    float m_run[MTW], l_run[MTW];
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        m_run[mt] = -INFINITY;
-        l_run[mt] = 0.f;
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) o[mt][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    const u16* kbase = a.kc + (size_t)hk * a.max_seq * D + lane * 8;  // tiles are contiguous: lane l reads bytes 16*l ..
-    const u16* vbase = a.vc + (size_t)hk * a.max_seq * D + lane * 8;
-    const int b0 = (cb * NWV + wave) * a.blocks_per_wave;
-    int nb = (a.Ktot + 31) / 32 - b0;  // this wave's blocks
-    nb = nb < 0 ? 0 : (nb > a.blocks_per_wave ? a.blocks_per_wave : nb);
-
-    // K and V^T tiles of one 32-key block, stored in MFMA operand layout.  S^T tile t, MFMA row 4g'+i' is
-    // key kb + 8g' + 4t + i'; V^T operand dt is (channel dt*16 + c, keys kb + 8g .. +8).  Slots of the block at or
-    // beyond Ktot may hold anything: their scores are replaced by -inf (a select), their values zeroed.
-    elem8 kf[2][2][KS], vf[2][DT];  // double buffered: the next block is loaded while this one is used
-    auto load_k = [&](int buf, int kb) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                kf[buf][t][ks] = load_frag_stream(kbase + ((size_t)((kb >> 5) * 2 + t) * KS + ks) * 512);
-    };
-    auto load_v = [&](int buf, int kb) {
-#pragma unroll
-        for (int dt = 0; dt < DT; ++dt) vf[buf][dt] = load_frag_stream(vbase + ((size_t)(kb >> 5) * DT + dt) * 512);
-    };
-    // scores of block kb (buffer buf), then request the next block's values (kb_next < 0: none), then
-    // softmax and P V; the next block's keys were requested before the call
-    auto use_block = [&](int buf, int kb, int kb_next) {
-        const bool tail = kb + 32 > a.Ktot;      // slots at or beyond Ktot may hold anything: zero their V
-        const bool masked = kb + 32 > a.plan.P;  // block touches draft slots or the end
-        if (tail) {
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                Frag8 f;
-                f.v = vf[buf][dt];
-#pragma unroll
-                for (int j = 0; j < 8; ++j)
-                    if (kb + g * 8 + j >= a.Ktot) f.h[j] = 0;
-                vf[buf][dt] = f.v;
-            }
-        }
-        float scs[MTW][8];
-#pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = mfma16(kf[buf][t][ks], ql[mt][ks], acc);
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) acc = mfma16(kf[buf][t][ks], qf[mt][ks], acc);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) scs[mt][t * 4 + i] = acc[i] * a.scale_log2;
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        if (kb_next >= 0) load_v(buf ^ 1, kb_next);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-            float* sc = scs[mt];
-            if (masked) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int mk = kb + g * 8 + j - a.plan.P;
-                    const bool vis = (mk < a.plan.R) | ((mk >= vis_lo[mt]) & (mk <= vis_hi[mt]));
-                    sc[j] = vis ? sc[j] : -INFINITY;
-                }
-            }
-            float bm = sc[0];
-#pragma unroll
-            for (int j = 1; j < 8; ++j) bm = fmaxf(bm, sc[j]);
-            const float m_new = fmaxf(m_run[mt], lane_groups_max(bm));
-            const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-            const float alpha = exp2_raw(m_run[mt] - m_safe);
-            m_run[mt] = m_new;
-            l_run[mt] *= alpha;
-            if (__ballot(alpha != 1.0f) != 0) {
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) o[mt][dt] = o[mt][dt] * alpha;
-            }
-            // the weights enter the MFMA as a bf16 pair hi + lo (16 mantissa bits): rounding them to a
-            // single bf16 would add as much noise to O as the bf16 rounding of O itself
-            Frag8 pf, pl;
-            float pw[8], ps = 0.f;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                pw[j] = exp2_raw(sc[j] - m_safe);
-                ps += pw[j];
-            }
-            split_elem8(pw, pf.q, pl.q);
-            l_run[mt] += ps;
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                o[mt][dt] = mfma16(vf[buf][dt], pl.v, o[mt][dt]);
-                o[mt][dt] = mfma16(vf[buf][dt], pf.v, o[mt][dt]);
-            }
-        }
-    };
-    if (nb > 0) {
-        load_k(0, b0 * 32);
-        load_v(0, b0 * 32);
-    }
-    for (int ib = 0; ib < nb; ib += 2) {  // two blocks per trip so that the buffer index is static
-        const int kb0 = (b0 + ib) * 32;
-        const bool more1 = ib + 1 < nb, more2 = ib + 2 < nb;
-        if (more1) load_k(1, kb0 + 32);
-        __builtin_amdgcn_sched_barrier(0);
-        use_block(0, kb0, more1 ? kb0 + 32 : -1);
-        if (more1) {
-            if (more2) load_k(0, kb0 + 64);
-            __builtin_amdgcn_sched_barrier(0);
-            use_block(1, kb0 + 32, more2 ? kb0 + 64 : -1);
-        }
-    }
-    // lane-group partial sums -> row sums (max is already uniform across lane groups)
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        l_run[mt] += __shfl_xor(l_run[mt], 16, 64);
-        l_run[mt] += __shfl_xor(l_run[mt], 32, 64);
-    }
-
-    // ---- merge the waves through LDS in a fixed binary tree: wave w + s -> wave w for s = NWV/2 .. 1
-#pragma unroll
-    for (int s = NWV / 2; s >= 1; s >>= 1) {
-        if (wave >= s && wave < 2 * s) {
-            const int buf = wave - s;
-#pragma unroll
-            for (int mt = 0; mt < MTW; ++mt) {
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt) lds_o[buf][(mt * DT + dt) * 64 + lane] = o[mt][dt];
-                if (g == 0) {
-                    lds_ml[buf][mt][0][c] = m_run[mt];
-                    lds_ml[buf][mt][1][c] = l_run[mt];
-                }
-            }
-        }
-        __syncthreads();
-        if (wave < s) {
-#pragma unroll
-            for (int mt = 0; mt < MTW; ++mt) {
-                const float mo = lds_ml[wave][mt][0][c], lo = lds_ml[wave][mt][1][c];
-                const float mn = fmaxf(m_run[mt], mo);
-                const float ms = mn == -INFINITY ? 0.f : mn;
-                const float sa = exp2f(m_run[mt] - ms), sb = exp2f(mo - ms);
-                m_run[mt] = mn;
-                l_run[mt] = l_run[mt] * sa + lo * sb;
-#pragma unroll
-                for (int dt = 0; dt < DT; ++dt)
-                    o[mt][dt] = o[mt][dt] * sa + lds_o[wave][(mt * DT + dt) * 64 + lane] * sb;
-            }
-        }
-        __syncthreads();
-    }
-    if (wave != 0) return;
-    // wave 0 holds the chunk's result: lane (c, g) has O[r = c][dt*16 + 4g .. +4].  A head that is one
-    // chunk is normalised and stored right away (bf16 pairs into the O projection's operand buffer);
-    // otherwise the chunk partial goes to scratch for attn_combine_kernel.
-#pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        const int r = (mg * MTW + mt) * 16 + c;
-        if (r >= MQ) continue;
-        if (a.nchunks == 1) {
-            const int m = r / a.group, col0 = (hk * a.group + r % a.group) * D;
-            const float inv = 1.0f / l_run[mt];
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    u16 hi, lo;
-                    split_elem(o[mt][dt][i] * inv, hi, lo);
-                    const int col = col0 + dt * 16 + g * 4 + i;
-                    a.out[operand_offset(m, col, a.out_tiles)] = hi;
-                    a.out[operand_offset(a.lo_rows(m), col, a.out_tiles)] = lo;
-                }
-        } else {
-            float* pp = a.part + (((size_t)hk * a.mq_pad + r) * a.nchunks + cb) * (D + 4);
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(pp + dt * 16 + g * 4) = o[mt][dt];
-            if (g == 0) {
-                pp[D] = m_run[mt];
-                pp[D + 1] = l_run[mt];
-            }
-        }
-    }
-}
-
 // Short contexts (at most 8 * BATCH blocks of 32 keys, up to 16 query rows per kv head): the whole head
 // in one workgroup of eight waves, no loop.  A wave requests the keys of ALL its blocks and the values
 // of the first one at once, forms every score, requests the remaining values into the registers the
@@ -740,8 +509,9 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     // No row of this wave sees a key behind the slot of the wave's last query row: such blocks are masked for all of its
     // rows, so the wave leaves out their products and softmax (a prompt chunk's early rows against the chunk's late
     // keys: causal attention per query tile, not only per workgroup) and only keeps the ring's pace.
+    // A wave without a query tile (the last of 3, 5 or 17 tiles) leaves out all of them.
     const int r_wave_last = min(MQ, (tile + 1) * 16) - 1;
-    const int kb_last = r_wave_last >= 0 ? a.plan.P + r_wave_last / a.group : -1;  // key slot of that row
+    const int kb_last = tile * 16 < MQ ? a.plan.P + r_wave_last / a.group : -1;  // key slot of that row
     __syncthreads();  // block 0 is in LDS
     for (int st = 0; st < nst; ++st) {
         const int ib = st * KSPLIT + team;  // this team's block of the stage
