@@ -221,7 +221,7 @@ void launch_projection(int cls, int M, const u16* X, const u16* W, int K, int ti
         return;
     }
     if (M <= 8) {
-        if (!launch_wide_half<NT>(X, W, K, tiles, rsc, epi, s)) launch_gemm_rows<NT>(M, true, X, W, K, tiles, rsc, epi, s);
+        if (!launch_wide_half<NT>(X, W, K, tiles, rsc, epi, s)) launch_gemm_pairs<NT>(M, X, W, K, tiles, rsc, epi, s);
         return;
     }
     const int quads = pair_rows_for(M) / 4;
@@ -266,7 +266,7 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, int sp
     prof(cls, s);
     if (splits == 1) {
         if (M <= DUO_MAX_ROWS) {
-            launch_gemm_rows<1>(M, true, X, W, K, d / 16, none, er, s);
+            launch_gemm_pairs<1>(M, X, W, K, d / 16, none, er, s);
             return;
         }
         launch_block<1>(X, W, K, d / 16, M, 1, none, er, s);
@@ -367,7 +367,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     const bool stats = temperature >= 0.0;
     const bool root_stats = stats && plan.R == 0;
     prof(DUO_PROF_SETUP, s);
-    DUO_LAUNCH(setup_kernel, dim3(M + (root_stats ? ROOT_STATS_PARTS : 0)), dim3(256), s, w.embed, tokens, root_token, plan, V,
+    DUO_LAUNCH(setup_kernel, dim3(RowUnits{M, 1}.blocks() + (root_stats ? ROOT_STATS_PARTS : 0)), dim3(256), s, w.embed, tokens, root_token, plan, V,
                cache.prefix_len, status, ws.x, w.g_attn[0], ws.h, d, lo_rows, AT, ws.ssq, ws.ssq_full, D, (double)c.rope_theta, ws.rope_c,
                ws.rope_s, RootStatsArgs{root_stats ? cache.root_logits : nullptr, V, temperature, ws.stats_root});
 
@@ -915,7 +915,7 @@ int duo_skinny_gemm(const uint16_t* x, const uint16_t* w, float* y, int rows, in
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     (void)hipGetLastError();
     EpiStoreF32 e{N, rows, 2, y, N};
-    launch_gemm_rows<2>(rows, false, x, w, K, (N + 31) / 32, RowScale{nullptr, 0, 0.f, 0.f, nullptr}, e, s);
+    launch_gemm_rows<2>(rows, x, w, K, (N + 31) / 32, RowScale{nullptr, 0, 0.f, 0.f, nullptr}, e, s);
     return hip_ok(hipGetLastError(), "duo_skinny_gemm launch");
 }
 

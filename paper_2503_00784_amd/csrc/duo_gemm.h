@@ -942,29 +942,28 @@ static inline void launch_gemm_cfg(const u16* X, const u16* W, int K, int tiles,
 template <int MT, int NT, class Epi>
 static inline void launch_gemm(const u16* X, const u16* W, int K, int tiles, int quads, int pq, const RowScale& rsc,
                                const Epi& epi, hipStream_t s) {
-    constexpr int NWK = MT <= 6 ? 4 : 2;  // keeps the partial-sum buffer within 64 KiB of LDS
+    constexpr int NWK = 4;
     if (tiles >= 320) launch_gemm_cfg<MT, NT, 1>(X, W, K, tiles, quads, pq, rsc, epi, s);
     else launch_gemm_cfg<MT, NT, NWK>(X, W, K, tiles, quads, pq, rsc, epi, s);
 }
 
-// M output rows, at most 16 if paired: the activations are bf16 pairs (rows m and pair_rows + m of the operand).
+// M output rows.  Paired (at most 16): the activations are bf16 pairs, rows m and pair_rows + m of the operand.
 template <int NT, class Epi>
-static inline void launch_gemm_rows(int M, bool paired, const u16* X, const u16* W, int K, int tiles, const RowScale& rsc,
-                                    const Epi& epi, hipStream_t s) {
-    const int mt = a_tiles_for(M, paired);
-    const int quads = paired ? pair_rows_for(M) / 4 : (M + 3) / 4;
-    const int pq = paired ? pair_rows_for(M) / 4 : 0;
-    switch (mt) {
-        case 1: launch_gemm<1, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 2: launch_gemm<2, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 3: launch_gemm<3, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 4: launch_gemm<4, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 5: launch_gemm<5, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 6: launch_gemm<6, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 7: launch_gemm<7, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 8: launch_gemm<8, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        case 9: launch_gemm<9, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
-        default: launch_gemm<10, NT>(X, W, K, tiles, quads, pq, rsc, epi, s); break;
+static inline void launch_gemm_pairs(int M, const u16* X, const u16* W, int K, int tiles, const RowScale& rsc, const Epi& epi, hipStream_t s) {
+    const int quads = pair_rows_for(M) / 4;
+    if (M <= 8) launch_gemm<1, NT>(X, W, K, tiles, quads, quads, rsc, epi, s);
+    else launch_gemm<2, NT>(X, W, K, tiles, quads, quads, rsc, epi, s);
+}
+// Not paired: up to 80 rows.
+template <int NT, class Epi>
+static inline void launch_gemm_rows(int M, const u16* X, const u16* W, int K, int tiles, const RowScale& rsc, const Epi& epi, hipStream_t s) {
+    const int quads = (M + 3) / 4;
+    switch ((M + 15) / 16) {
+        case 1: launch_gemm<1, NT>(X, W, K, tiles, quads, 0, rsc, epi, s); break;
+        case 2: launch_gemm<2, NT>(X, W, K, tiles, quads, 0, rsc, epi, s); break;
+        case 3: launch_gemm<3, NT>(X, W, K, tiles, quads, 0, rsc, epi, s); break;
+        case 4: launch_gemm<4, NT>(X, W, K, tiles, quads, 0, rsc, epi, s); break;
+        default: launch_gemm<5, NT>(X, W, K, tiles, quads, 0, rsc, epi, s); break;
     }
 }
 

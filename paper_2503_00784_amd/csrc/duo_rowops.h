@@ -20,6 +20,21 @@ __device__ __forceinline__ void block_row_sum(float v, float* wsum, float* out) 
     }
 }
 
+// Which row of an operand a workgroup prepares.  An operand buffer keeps 16 bytes of eight rows together in a 128-byte line, and workgroups go to
+// the eight dies in turn, each with an L2 of its own: with one row after the other every line was written by eight dies, 16 bytes each.  So
+// the eight workgroups of eight rows (times one of `parts` column ranges) are eight places apart, on one die.  us, one
+// row after the other against this: set-up of 1024 rows 29.2 -> 18.5, the reduce kernel at 300 / 520 / 900 rows of the 8B shape 11.0 / 17.1 / 14.1 ->
+// 8.1 / 11.9 / 10.9, at 64 rows 4.6 -> 4.35, and the whole step of 64 rows 1219 -> 1204 (the end of a kernel writes its lines back).
+struct RowUnits {
+    int M, parts;
+    __host__ __device__ __forceinline__ int blocks() const { return ((M + 7) / 8 * parts + 7) / 8 * 64; }
+    __device__ __forceinline__ int row(int b, int& part) const {  // M or more: none
+        const int unit = b % 8 + b / 64 * 8, group = unit / parts;
+        part = unit - group * parts;
+        return group * 8 + (b >> 3) % 8;
+    }
+};
+
 // The first kernel of a pass, one workgroup (256 threads) per row and more for the root statistics:
 //   - x[m] = E[token_m], plus what the first RMSNorm needs (see RowScale in duo_gemm.h): u = x * gain as bf16 pairs in the QKV
 //     projection's operand buffer, the per-tile partial sums of x^2 and the whole row's; runs of eight channels per thread;
@@ -44,10 +59,10 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
                                                      int D, double theta, float* __restrict__ rc, float* __restrict__ rs, RootStatsArgs root) {
     __shared__ float wsum[4];
     __shared__ double sm[16];
-    const int m = blockIdx.x;
-    if (m >= plan.M) {  // statistics of one slice of the root logits
+    const RowUnits units{plan.M, 1};
+    if ((int)blockIdx.x >= units.blocks()) {  // statistics of one slice of the root logits
         if (!root.logits) return;
-        const int sl = m - plan.M, len = (root.V + ROOT_STATS_PARTS - 1) / ROOT_STATS_PARTS;
+        const int sl = blockIdx.x - units.blocks(), len = (root.V + ROOT_STATS_PARTS - 1) / ROOT_STATS_PARTS;
         const int v0 = sl * len, v1 = min(root.V, v0 + len);
         double zmax, Z;
         slice_stats(root.logits, v0, v1, root.T, sm, zmax, Z);
@@ -57,6 +72,9 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
         }
         return;
     }
+    int part;
+    const int m = units.row(blockIdx.x, part);
+    if (m >= plan.M) return;
     if (m == 0 && status) {
         int bad = 0;
         for (int i = threadIdx.x; i < plan.M; i += 256) {
@@ -107,16 +125,19 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
 // EpiResidual, instead of S), then what EpiResidual does for the next RMSNorm: u = x * gain
 // as bf16 pairs in operand layout and the partial sums of x^2 per 16-column tile, plus the sum of squares over this
 // workgroup's whole column range (RowScale::full), which the consumer reads instead of 256 partials per row.
-// grid = (rows, P): workgroup (m, pt) takes columns pt * d/P .. of row m (d/P a multiple of 64; P <= FULL_PARTS),
+// grid = units.blocks(): workgroup (m, pt) takes columns pt * d/P .. of row m (d/P a multiple of 64; P <= FULL_PARTS),
 // NWV waves, eight consecutive channels per thread and turn; the loads of all
 // splits are issued together (S <= MAXS <= 8, indices beyond S re-read the last split and are not added).
 template <int NWV, int MAXS>
-__global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* __restrict__ part, int S, size_t split_stride,
+__global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(RowUnits units, const float* __restrict__ part, int S, size_t split_stride,
                                                                    float* __restrict__ x, const u16* __restrict__ gain,
                                                                    u16* __restrict__ h, int d, LoRows lo_rows, int tiles,
                                                                    float* __restrict__ ssq_part, float* __restrict__ ssq_full) {
     __shared__ float wsum[NWV];
-    const int m = blockIdx.x, P = gridDim.y, cols = d / P, c0 = blockIdx.y * cols;
+    const int P = units.parts, cols = d / P;
+    int pt;
+    const int m = units.row(blockIdx.x, pt), c0 = pt * cols;
+    if (m >= units.M) return;
     float total = 0.f;
     for (int j8 = c0 + threadIdx.x * 8; j8 < c0 + cols; j8 += NWV * 64 * 8) {  // lanes leave in pairs
         float* xr = x + (size_t)m * d + j8;
@@ -155,14 +176,15 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(const float* 
         sq += __shfl_xor(sq, 1, 64);
         if (!(threadIdx.x & 1)) ssq_part[(size_t)m * (d >> 4) + (j8 >> 4)] = sq;
     }
-    block_row_sum<NWV>(total, wsum, ssq_full + (size_t)m * RowScale::FULL_PARTS + blockIdx.y);
-    if (blockIdx.y == 0 && (int)threadIdx.x >= P && threadIdx.x < RowScale::FULL_PARTS)
+    block_row_sum<NWV>(total, wsum, ssq_full + (size_t)m * RowScale::FULL_PARTS + pt);
+    if (pt == 0 && (int)threadIdx.x >= P && threadIdx.x < RowScale::FULL_PARTS)
         ssq_full[(size_t)m * RowScale::FULL_PARTS + threadIdx.x] = 0.f;  // unused ranges
 }
 
 // Column ranges per row for residual_reduce_kernel: enough workgroups to fill the chip when there are few rows.
+// (520 rows of the 8B shape: 4 ranges 11.9 us, 1 range 13.1; 400: 9.8 / 10.0.)
 static inline int reduce_parts(int M, int d) {
-    int P = M <= 32 ? 8 : (M <= 80 ? 4 : (M < 256 ? 2 : 1));
+    int P = M <= 32 ? 8 : 4;
     while (P > 1 && d % (P * 64) != 0) P >>= 1;
     return P;
 }
@@ -170,9 +192,10 @@ static inline void launch_residual_reduce(int M, const float* part, int S, size_
                                           u16* h, int d, LoRows lo_rows, int tiles, float* ssq_part, float* ssq_full,
                                           hipStream_t s) {
     const int P = reduce_parts(M, d), cols = d / P;
-    const dim3 grid(M, P);
+    const RowUnits units{M, P};
+    const dim3 grid(units.blocks());
 #define DUO_REDUCE(NWV, MAXS)                                                                                                  \
-    DUO_LAUNCH((residual_reduce_kernel<NWV, MAXS>), grid, dim3(NWV * 64), s, part, S, split_stride, x, gain, h, d, lo_rows, tiles, \
+    DUO_LAUNCH((residual_reduce_kernel<NWV, MAXS>), grid, dim3(NWV * 64), s, units, part, S, split_stride, x, gain, h, d, lo_rows, tiles, \
                ssq_part, ssq_full)
 #define DUO_REDUCE_COLS(MAXS)                     \
     do {                                          \
