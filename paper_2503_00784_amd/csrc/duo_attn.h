@@ -570,10 +570,10 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     }
 }
 
-// Merge of the chunk partials when a head was split over several workgroups: one wave per (row, head).
+// Merge of the chunk partials when a head was split over several workgroups: one wave per (row, head), eight rows of one head per
+// workgroup: they share the 128-byte lines of the operand that the merge writes.
 template <int D>
-__global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs a) {
-    const int r = blockIdx.x * 4 + (threadIdx.x >> 6);  // four waves, four rows
-    if (r < a.plan.M * a.group) attn_merge_row<D>(a, blockIdx.y, r, threadIdx.x & 63);
+__global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
+    const int groups = (a.plan.M + 7) >> 3, gq = blockIdx.x / groups, m = (blockIdx.x - gq * groups) * 8 + (threadIdx.x >> 6);
+    if (m < a.plan.M) attn_merge_row<D>(a, blockIdx.y, m * a.group + gq, threadIdx.x & 63);
 }
-

@@ -101,7 +101,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const u16* __restr
                                                                int quads, int pair_quads, RowScale rsc, Epi epi) {
     __shared__ f32x4 red[NW * MT * NT * 64];
     __shared__ float row_scale[MT * 16];
-    const int tile = blockIdx.x;
+    const int tile = die_contiguous(blockIdx.x, gridDim.x);
     // the wave index must live in a scalar register: MFMA ignores the EXEC mask, so every branch
     // around an MFMA has to be a scalar (wave-uniform) branch, never lane predication
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -345,7 +345,8 @@ __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16
 
     // ---- consumers: wave (ng, nk) takes band group ng and, of every round, the K steps nk * AG .. + AG
     const int ng = wave % NG, nk = wave / NG;
-    const int tile_raw = blockIdx.x * NG + ng;
+    // (a split launch's workgroups write whole lines of partial results: as they come)
+    const int tile_raw = (gridDim.y == 1 ? die_contiguous(blockIdx.x, gridDim.x) : (int)blockIdx.x) * NG + ng;
     const bool live = tile_raw < ntiles;
     const int tile = live ? tile_raw : ntiles - 1;
     const u16* wp[NT];
