@@ -2,20 +2,17 @@
 // token and the earlier tokens of its own draft sequence (independent sequences, Sec. 3.2).
 //
 // The prefix keys/values of one KV head are read ONCE for all rows and all query heads of the
-// group: a workgroup takes one (kv head, key chunk), each of its waves a share of the
-// chunk's 32-key blocks.  Per block a wave computes S^T = K Q^T and O^T += V^T P^T with MFMA:
-//   - K rows and V^T rows (values are cached transposed) are loaded straight from HBM in MFMA
-//     operand layout, 16 bytes per lane, no LDS staging -- each byte is consumed by one wave
-//     (loads with the non-temporal hint: nothing of the prefix is read twice in a pass);
+// group: a workgroup takes one (kv head, key chunk).  Per 32-key block a wave computes S^T = K Q^T and O^T += V^T P^T with MFMA:
+//   - K and V^T tiles lie in the cache as MFMA operands; attn_small_kernel loads them straight into registers, attn_shared_kernel
+//     puts them in LDS once for all query tiles (both with the non-temporal hint: nothing of the prefix is read twice in a pass);
 //   - the key permutation inside a block is chosen so that the S^T accumulator of a lane
 //     already holds the eight consecutive keys its P^T operand needs: no cross-lane traffic
 //     between the two products;
 //   - queries and softmax weights enter the MFMAs as bf16 pairs (hi + lo), keys and values are the
 //     cache's bf16;
 //   - the softmax is online (running max / sum per row), reduced across the four lane groups by lane swaps.
-// The waves are merged through LDS in a fixed chain, chunk partials (max, sum, unnormalised O)
-// go to scratch and are merged in chunk order: by the same workgroup when a head is one chunk (short
-// prefixes: one kernel per layer), by a small second kernel otherwise.
+// Chunk partials (max, sum, unnormalised O) go to scratch and are merged in chunk order by a small second kernel; where a head is one
+// chunk (short prefixes) the same workgroup finishes it: one kernel per layer.
 #pragma once
 #include "duo_common.h"
 #include "duo_gemm.h"
@@ -29,7 +26,7 @@ struct AttnArgs {
     int max_seq, group;
     RowPlan plan;
     int Ktot;             // P + M keys in play
-    int blocks_per_wave;  // 32-key blocks per wave; a chunk is (waves per workgroup) * blocks_per_wave blocks
+    int chunk_blocks;     // 32-key blocks per chunk (attn_shared_kernel)
     int nchunks;
     int mq_pad;           // padded number of (row, query-head-in-group) pairs
     float scale_log2;     // log2(e) / sqrt(D)
@@ -291,12 +288,10 @@ __global__ __launch_bounds__(512) void attn_small_kernel(AttnArgs a) {
     }
 }
 
-// Many query rows per kv head (more than two 16-row query tiles: many draft rows and/or a large GQA
-// group).  The kernels above give every wave its own keys and ALL query tiles, which does not fit the
-// registers beyond two tiles, so more tiles meant more workgroups re-reading the same keys.  Here it is
-// the other way round: a workgroup takes one (kv head, key chunk); each 32-key block of K and V^T is put
-// in LDS once, in MFMA operand layout (the same 1 KiB tiles the other kernels load straight into
-// registers), and each of the NWV consumer waves owns one query tile and runs over all blocks of the
+// Two or more 16-row query tiles per kv head, or one on a long context.  (A kernel whose waves read their own keys for all query tiles was
+// slower at every size: two tiles on 40 / 980 keys 9.0 / 20.4 us against 5.8 / 7.0 + 4.3 with the merge, one tile of 32 heads on 1400
+// 8.4 against 7.2.)  A workgroup takes one (kv head, key chunk); each 32-key block of K and V^T is put
+// in LDS once, in MFMA operand layout, and each of the NWV consumer waves owns one query tile and runs over all blocks of the
 // chunk, so nothing is merged between waves.  One extra wave does nothing but move the blocks: 16-byte
 // global -> LDS loads (no registers, no LDS store instructions) into a ring of three buffers, two blocks
 // ahead of the MFMAs; its barriers are bare s_barrier instructions behind a counted wait.  One barrier per
@@ -331,9 +326,9 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;  // scalar: MFMA ignores EXEC
     const int c = lane & 15, g = lane >> 4;
     const int NB = (a.Ktot + 31) / 32;
-    const int b0 = cb * a.blocks_per_wave;  // here: blocks per chunk
+    const int b0 = cb * a.chunk_blocks;
     int nb = NB - b0;
-    nb = nb < 0 ? 0 : (nb > a.blocks_per_wave ? a.blocks_per_wave : nb);
+    nb = nb < 0 ? 0 : (nb > a.chunk_blocks ? a.chunk_blocks : nb);
     // Row groups in reverse launch order: workgroups start in index order, and the late rows of a prompt chunk see the
     // most keys, so the longest-running groups go first.
     const int zg = (int)(gridDim.z - 1 - blockIdx.z);

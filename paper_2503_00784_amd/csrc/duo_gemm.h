@@ -20,7 +20,7 @@
 //
 // Activation precision: an activation a is carried as a bf16 pair (hi, lo) with hi = bf16(a),
 // lo = bf16(a - hi), i.e. 16 mantissa bits.  The pair occupies two ROWS of the MFMA A operand:
-// row m holds hi, row m + pair_rows holds lo, and the epilogue adds the two output rows.  For the
+// row m holds hi, another (see LoRows) holds lo, and the epilogue adds the two output rows.  For the
 // common M <= 8 case both halves fit the one 16-row tile an MFMA needs anyway, so the extra
 // precision costs nothing; a single bf16 per activation would leave rounding noise of ~0.1 in the
 // logits of a 32-layer model.
