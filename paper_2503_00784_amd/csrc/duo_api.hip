@@ -15,6 +15,7 @@
 #include "duo_common.h"
 #include "duo_gemm.h"
 #include "duo_gemm_block.h"
+#include "duo_launch.h"
 #include "duo_pack.h"
 #include "duo_rowops.h"
 #include "duo_sample.h"
@@ -286,54 +287,13 @@ void launch_residual_projection(int M, const u16* X, const u16* W, int K, int sp
 }
 
 template <int D>
-void launch_attention_shared(int nwv, int ksplit, dim3 grid, const AttnArgs& a, hipStream_t s) {
-    if (ksplit == 2 && nwv == 10) DUO_LAUNCH((attn_shared_kernel<D, 10, 2>), grid, dim3(704), s, a);
-    else if (ksplit == 2 && nwv == 8) DUO_LAUNCH((attn_shared_kernel<D, 8, 2>), grid, dim3(576), s, a);
-    else if (ksplit == 2) DUO_LAUNCH((attn_shared_kernel<D, 4, 2>), grid, dim3(320), s, a);
+void launch_attention(const AttnLaunch& at, int Hkv, const AttnArgs& a, hipStream_t s) {
+    const dim3 grid(at.chunks, Hkv, at.row_groups);
+    if (at.small) DUO_LAUNCH((attn_small_kernel<D, 4>), grid, dim3(512), s, a);
+    else if (at.ksplit == 2 && at.nwv == 10) DUO_LAUNCH((attn_shared_kernel<D, 10, 2>), grid, dim3(704), s, a);
+    else if (at.ksplit == 2 && at.nwv == 8) DUO_LAUNCH((attn_shared_kernel<D, 8, 2>), grid, dim3(576), s, a);
+    else if (at.ksplit == 2) DUO_LAUNCH((attn_shared_kernel<D, 4, 2>), grid, dim3(320), s, a);
     else DUO_LAUNCH((attn_shared_kernel<D, 8, 1>), grid, dim3(576), s, a);
-}
-
-// Attention of a prompt chunk: query tiles of attn_shared_kernel's workgroups (a tile per wave of a team) and chunks of keys.  A
-// workgroup has a compute unit to itself and takes 6 us and, per ring stage of a block for each team, 1.02 us with two teams of four
-// waves, 1.27 with two of five, 1.06 as one team of eight (heads of 128; of 64: 0.68 of it), about the same per tile and block: what
-// decides is how evenly the groups of 4, 5 or 8 tiles fill the chip.  The late rows see the most keys and go first, so the launch takes its
-// mean load or, where the last workgroups come as an odd few, (rounds + 1) times the length of those.  More than one chunk: the merge, 4 us
-// and 1.5 us per million values.  In us with the merge, groups of four tiles
-// alone against this choice: 32 heads, 640 rows behind 4000 keys 139 -> 108, behind 16000 420 -> 371; 40 heads, 200 rows behind 8000
-// 110 -> 98; 8 heads x 8, 800 rows behind 8000 533 -> 478.  1024 rows behind 1024 keys on 32 heads keep them: 69, against 93 + 14 with two
-// tiles per wave.
-struct PromptAttention {
-    int nwv, ksplit, chunks;
-};
-PromptAttention prompt_attention(int D, int Hkv, int group, int M, int P, int max_chunks) {
-    constexpr int CUS = 256;
-    static const struct {
-        int nwv, ksplit;
-        float stage;
-    } shapes[] = {{8, 2, 1.02f}, {10, 2, 1.27f}, {8, 1, 1.06f}};
-    const int NB = (P + M + 31) / 32, MQ = M * group;
-    PromptAttention best{8, 2, 1};
-    float best_cost = 1e30f;
-    for (const auto& s : shapes) {
-        const int rows = s.nwv / s.ksplit * 16, groups = (MQ + rows - 1) / rows;  // query rows of a workgroup, row groups
-        const auto blocks_seen = [&](int z) { return std::min(NB, (P + (std::min(MQ, (z + 1) * rows) - 1) / group) / 32 + 1); };
-        for (int t = 1; t <= max_chunks; ++t) {
-            const int bl = std::max(2, (NB + t - 1) / t), n = (NB + bl - 1) / bl;  // blocks per chunk, chunks
-            const float mean_stages = 0.5f * (float)(blocks_seen(0) + blocks_seen(groups - 1)) / (float)s.ksplit;  // all chunks of a row group
-            float cost = (float)(Hkv * groups) * (6.f * (float)n + s.stage * mean_stages) / (float)CUS;
-            for (int r = 0; r * CUS < Hkv * groups * n; ++r) {  // 256 r workgroups came first: the next one is the longest that is left
-                const int seen = std::min(bl, blocks_seen(groups - 1 - r * CUS / (n * Hkv)));
-                cost = std::max(cost, (float)(r + 1) * (6.f + s.stage * (float)((seen + s.ksplit - 1) / s.ksplit)));
-            }
-            if (D == 64) cost *= 0.68f;
-            if (n > 1) cost += 4.f + 1.5e-6f * (float)n * (float)MQ * (float)Hkv * (float)D;
-            if (cost < best_cost) {
-                best_cost = cost;
-                best = PromptAttention{s.nwv, s.ksplit, t};
-            }
-        }
-    }
-    return best;
 }
 
 // The target pass over the rows of `plan`: fills the cache slots P .. P+M-1 and writes fp32
@@ -363,7 +323,6 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     const size_t split_floats = std::max(ws.split_floats, idle_floats);
     const int o_splits = residual_splits(M, qd, d, split_floats), down_splits = residual_splits(M, F, d, split_floats);
     const bool o_full = many || o_splits > 1, down_full = many || down_splits > 1;  // whole-row sums of squares behind it
-    const int max_chunks = many ? MAX_CHUNKS_MANY_ROWS : MAX_CHUNKS;
     const bool stats = temperature >= 0.0;
     const bool root_stats = stats && plan.R == 0;
     prof(DUO_PROF_SETUP, s);
@@ -371,51 +330,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
                cache.prefix_len, status, ws.x, w.g_attn[0], ws.h, d, lo_rows, AT, ws.ssq, ws.ssq_full, D, (double)c.rope_theta, ws.rope_c,
                ws.rope_s, RootStatsArgs{root_stats ? cache.root_logits : nullptr, V, temperature, ws.stats_root});
 
-    // Attention launch shape.  One query tile per kv head on a short context: one workgroup of 8 waves per kv head does the whole head
-    // without a loop.  Otherwise the kernel that stages K/V blocks in LDS for all query tiles, one query tile per wave: with the keys cut into
-    // chunks for more workgroups and a second small kernel that merges the chunk partials, or in one chunk without one.
-    const int Ktot = plan.P + M;
-    const int NB = (Ktot + 31) / 32;
-    const int MQ = M * group, MqT = (MQ + 15) / 16;
-    const int mq_pad = Mp * group;
-    // One tile: the no-loop kernel against chunks and merge, 32 heads of 128: 400 keys 8.8 against 10.6 us, 700 11.6 against 10.8, 980 14.2
-    // against 11.6; 8 heads 9.5 / 10.0, 12.5 / 9.8, 14.8 / 10.2; heads of 64 8.8 against 9.6 at 980, the most it holds.
-    const bool shared_kv = MqT > 1 || NB > 32 || (D == 128 && NB > 20);
-    int sh_nwv = 4, sh_zg = 1, sh_ksplit = 1, bpw = 0, nchunks = 1;
-    if (shared_kv) {
-        // about 256 workgroups (one per compute unit): measured best for 4 tiles x 32 heads and 16 tiles x 8 heads
-        // Up to four tiles: two teams of waves share the blocks (two waves per SIMD: 20.7 against 23.2 us at 4 tiles,
-        // 11.8 against 14.4 us at 2 tiles, measured on 32 heads x 4160 / 2080 keys).
-        // 9..16 tiles (64 rows x a GQA group of 4): 27.3 against 28.2 us at 8192 keys; 17..20 tiles (65..80 rows) in the same shape
-        // against two tiles per wave: 33.8 against 43.4 us at 8192 keys, 14.1 against 18.6 at 2048, 10.9 against 13.4 at 700.
-        sh_ksplit = (MqT <= 4 || MqT > 8) ? 2 : 1;
-        sh_nwv = MqT > 2 ? 8 : 4;
-        PromptAttention prompt{0, 0, 0};
-        if (many) {
-            prompt = prompt_attention(D, Hkv, group, M, plan.P, max_chunks);
-            sh_ksplit = prompt.ksplit;
-            sh_nwv = prompt.nwv;
-        } else if (MqT == 5 && NB >= 64) {
-            // five tiles (65..80 rows of a head without a group) on a long context: two teams of five against eight waves of which
-            // five have a tile, 25.9 -> 22.3 us on 32 heads x 4161 keys, 17.9 -> 17.3 at 2127 (at 577 keys 9.1 -> 10.3: not there)
-            sh_ksplit = 2;
-            sh_nwv = 10;
-        }
-        sh_zg = (MqT + sh_nwv / sh_ksplit - 1) / (sh_nwv / sh_ksplit);
-        // LDS (teams) or registers (nine waves) leave room for one workgroup per compute unit, so no more than 256 of them (40
-        // heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us)
-        int target = 256 / (Hkv * sh_zg);
-        target = target < 1 ? 1 : (target > max_chunks ? max_chunks : target);
-        // A short context is one chunk, the merge costs 4.3 us and its launch.  One chunk against chunks and merge, 32 heads of 128: two tiles
-        // 250 / 400 / 700 keys 9.0 / 9.6 / 13.4 against 10.9 / 11.4 / 11.7 us, three 10.3 / 11.7 / 15.9 against 11.4 / 11.6 / 12.5, four 10.8 /
-        // 12.9 against 12.1 / 12.6; one team of eight: five tiles 120 / 250 keys 10.3 / 13.6 against 12.0 / 12.2; 17 tiles on eight heads 250 / 400
-        // keys 12.0 / 14.5 against 13.4 / 13.9.
-        if (NB <= (MqT <= 2 ? 16 : sh_ksplit == 2 ? 10 : 5)) target = 1;
-        if (many) target = prompt.chunks;
-        bpw = (NB + target - 1) / target;  // blocks per chunk
-        bpw = bpw < 2 ? 2 : bpw;
-        nchunks = (NB + bpw - 1) / bpw;
-    }
+    const AttnLaunch at = attention_launch(D, Hkv, group, M, plan.P, many, many ? MAX_CHUNKS_MANY_ROWS : MAX_CHUNKS);
 
     // The bands of the Q/K/V matrix are independent of each other, so a wave may take one or two.  One band per wave
     // where that makes a single, nearly full round of workgroups (measured at 768 bands of 4096 input channels:
@@ -456,19 +371,12 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         } else if (qkv_nt == 1) launch_projection<1>(DUO_PROF_QKV, M, ws.h, w.wqkv[l], d, qkv_bands, qkv_norm, eq, s);
         else launch_projection<2>(DUO_PROF_QKV, M, ws.h, w.wqkv[l], d, qkv_bands / 2, qkv_norm, eq, s);
 
-        AttnArgs aa{ws.q, qd, ws.q_plane, kc, vc, c.max_seq, group, plan, Ktot, bpw, nchunks, mq_pad,
+        AttnArgs aa{ws.q, qd, ws.q_plane, kc, vc, c.max_seq, group, plan, plan.P + M, at.chunk_blocks, at.chunks, Mp * group,
                     1.4426950408889634f / sqrtf((float)D), ws.part, ws.attn, AT, lo_rows};
         prof(DUO_PROF_ATTN, s);
-        if (shared_kv) {
-            const dim3 grid(nchunks, Hkv, sh_zg);
-            if (D == 128) launch_attention_shared<128>(sh_nwv, sh_ksplit, grid, aa, s);
-            else launch_attention_shared<64>(sh_nwv, sh_ksplit, grid, aa, s);
-        } else if (D == 128) {
-            DUO_LAUNCH((attn_small_kernel<128, 4>), dim3(1, Hkv), dim3(512), s, aa);
-        } else {
-            DUO_LAUNCH((attn_small_kernel<64, 4>), dim3(1, Hkv), dim3(512), s, aa);
-        }
-        if (nchunks > 1) {
+        if (D == 128) launch_attention<128>(at, Hkv, aa, s);
+        else launch_attention<64>(at, Hkv, aa, s);
+        if (at.chunks > 1) {
             prof(DUO_PROF_ATTN_COMB, s);
             if (D == 128) DUO_LAUNCH((attn_combine_kernel<128>), dim3((M + 7) / 8 * group, Hkv), dim3(512), s, aa);
             else DUO_LAUNCH((attn_combine_kernel<64>), dim3((M + 7) / 8 * group, Hkv), dim3(512), s, aa);

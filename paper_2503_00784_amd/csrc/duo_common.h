@@ -132,16 +132,6 @@ __device__ __forceinline__ double wave_max(double v) {
     return v;
 }
 
-// Workgroups go to the eight dies in turn, each with an L2 of its own.  This turns workgroup b of n into a place such that every die gets a
-// contiguous range of places: neighbours that write parts of the same 128-byte lines (channels of a query row, columns of the residual
-// stream, partial sums of squares) then do so through one L2 instead of through eight.  Only speed depends on it.
-// us, before and after: LM head of 33 rows x 32000 53.5 -> 49.5, x 128256 200 -> 191; O projection of 8 rows 9.0 -> 8.7; the whole 7B step of
-// 8 rows 2829 -> 2806.  Not for the block kernel of prompt chunks (Q/K/V of 1024 rows 165 -> 175).
-__device__ __forceinline__ int die_contiguous(int b, int n) {
-    const int die = b & 7, q = n >> 3, r = n & 7;
-    return die * q + min(die, r) + (b >> 3);
-}
-
 // KV-cache layout inside one (layer, kv head) plane of max_seq * D elements.  Both caches are stored as the
 // 1 KiB MFMA operand tiles the attention kernels consume, 32 slots (one key block) at a time, so that a wave
 // fetches a tile with one fully coalesced load (lane l reads bytes 16*l .. 16*l+15) instead of sixteen half

@@ -28,21 +28,12 @@
 #include <type_traits>
 
 #include "duo_common.h"
+#include "duo_launch.h"
 
 // element offset of (row r, column k) in an operand buffer of MT row tiles
 __device__ __forceinline__ size_t operand_offset(int r, int k, int MT) {
     return ((size_t)((k >> 5) * MT + (r >> 4)) * 64 + ((k & 31) >> 3) * 16 + (r & 15)) * 8 + (k & 7);
 }
-
-// Where the lo halves of a paired operand's rows lie (hi halves: row m).  Up to eight rows share one 16-row tile with their lo halves.
-// Beyond that hi and lo halves occupy whole tiles, lo tile = hi tile + M/16 rounded up, so that a lane's hi and lo sums have the same position
-// in their tiles; but where the last tile of a verify pass has one to eight rows it holds their lo halves too, eight rows further on (17, 33,
-// 65 rows, a previously emitted token in front of the drafts: 3, 5, 9 tiles instead of 4, 6, 10).  What bounds the projections at
-// 16..80 rows is the bytes that a compute unit takes in, weights and operand alike.
-struct LoRows {
-    int split, base;  // rows below split: base rows further on, the others eight
-    __device__ __forceinline__ int operator()(int m) const { return m < split ? m + base : m + 8; }
-};
 
 // RMSNorm without a kernel of its own.  The producer of the residual stream (embedding gather or a
 // residual projection) stores, next to x, the operand u = x * gain as bf16 pairs and, per row and per
@@ -914,20 +905,6 @@ struct EpiQKV {
         }
     }
 };
-
-// Rows of the A operand for M paired activations, hi and lo halves in whole tiles beyond eight rows: pair_rows each.
-static inline int pair_rows_for(int M) { return M <= 8 ? 8 : (M + 15) / 16 * 16; }
-// The last tile holds its rows' lo halves too (see LoRows): up to sixteen rows the one-band kernels read whole tiles, prompt chunks of more
-// than 80 rows are padded to larger blocks anyway.
-static inline bool half_tail(int M) { return M > 16 && M <= DUO_MAX_ROWS && (M - 1) % 16 < 8; }
-static inline int a_tiles_for(int M, bool paired) {
-    return paired ? (2 * pair_rows_for(M) + 15) / 16 - (half_tail(M) ? 1 : 0) : (M + 15) / 16;
-}
-static inline LoRows lo_rows_for(int M) {
-    const int pr = pair_rows_for(M);
-    if (M <= 8) return LoRows{0, 0};
-    return half_tail(M) ? LoRows{pr - 16, pr} : LoRows{pr, pr};
-}
 
 template <int MT, int NT, int NW, class Epi>
 static inline void launch_gemm_cfg(const u16* X, const u16* W, int K, int tiles, int quads, int pq, const RowScale& rsc,

@@ -1,0 +1,153 @@
+// Launch rules and index maps: plain arithmetic from sizes to launch shapes and places, without a word of HIP but for the qualifiers of what a
+// kernel calls too, so that a program without a GPU can evaluate them.
+#pragma once
+#include <algorithm>
+
+#include "../../include/duo_verify.h"
+
+// Workgroups go to the eight dies in turn, each with an L2 of its own.  This turns workgroup b of n into a place such that every die gets a
+// contiguous range of places: neighbours that write parts of the same 128-byte lines (channels of a query row, columns of the residual
+// stream, partial sums of squares) then do so through one L2 instead of through eight.  Only speed depends on it.
+// us, before and after: LM head of 33 rows x 32000 53.5 -> 49.5, x 128256 200 -> 191; O projection of 8 rows 9.0 -> 8.7; the whole 7B step of
+// 8 rows 2829 -> 2806.  Not for the block kernel of prompt chunks (Q/K/V of 1024 rows 165 -> 175).
+__host__ __device__ __forceinline__ int die_contiguous(int b, int n) {
+    const int die = b & 7, q = n >> 3, r = n & 7;
+    return die * q + (die < r ? die : r) + (b >> 3);
+}
+
+// Where the lo halves of a paired operand's rows lie (hi halves: row m).  Up to eight rows share one 16-row tile with their lo halves.
+// Beyond that hi and lo halves occupy whole tiles, lo tile = hi tile + M/16 rounded up, so that a lane's hi and lo sums have the same position
+// in their tiles; but where the last tile of a verify pass has one to eight rows it holds their lo halves too, eight rows further on (17, 33,
+// 65 rows, a previously emitted token in front of the drafts: 3, 5, 9 tiles instead of 4, 6, 10).  What bounds the projections at
+// 16..80 rows is the bytes that a compute unit takes in, weights and operand alike.
+struct LoRows {
+    int split, base;  // rows below split: base rows further on, the others eight
+    __host__ __device__ __forceinline__ int operator()(int m) const { return m < split ? m + base : m + 8; }
+};
+
+// Rows of the A operand for M paired activations, hi and lo halves in whole tiles beyond eight rows: pair_rows each.
+inline int pair_rows_for(int M) { return M <= 8 ? 8 : (M + 15) / 16 * 16; }
+// The last tile holds its rows' lo halves too (see LoRows): up to sixteen rows the one-band kernels read whole tiles, prompt chunks of more
+// than 80 rows are padded to larger blocks anyway.
+inline bool half_tail(int M) { return M > 16 && M <= DUO_MAX_ROWS && (M - 1) % 16 < 8; }
+inline int a_tiles_for(int M, bool paired) {
+    return paired ? (2 * pair_rows_for(M) + 15) / 16 - (half_tail(M) ? 1 : 0) : (M + 15) / 16;
+}
+inline LoRows lo_rows_for(int M) {
+    const int pr = pair_rows_for(M);
+    if (M <= 8) return LoRows{0, 0};
+    return half_tail(M) ? LoRows{pr - 16, pr} : LoRows{pr, pr};
+}
+
+// Which row of an operand a workgroup prepares.  An operand buffer keeps 16 bytes of eight rows together in a 128-byte line, and workgroups go to
+// the eight dies in turn, each with an L2 of its own: with one row after the other every line was written by eight dies, 16 bytes each.  So
+// the eight workgroups of eight rows (times one of `parts` column ranges) are eight places apart, on one die.  us, one
+// row after the other against this: set-up of 1024 rows 29.2 -> 18.5, the reduce kernel at 300 / 520 / 900 rows of the 8B shape 11.0 / 17.1 / 14.1 ->
+// 8.1 / 11.9 / 10.9, at 64 rows 4.6 -> 4.35, and the whole step of 64 rows 1219 -> 1204 (the end of a kernel writes its lines back).
+struct RowUnits {
+    int M, parts;
+    __host__ __device__ __forceinline__ int blocks() const { return ((M + 7) / 8 * parts + 7) / 8 * 64; }
+    __device__ __forceinline__ int row(int b, int& part) const {  // M or more: none
+        const int unit = b % 8 + b / 64 * 8, group = unit / parts;
+        part = unit - group * parts;
+        return group * 8 + (b >> 3) % 8;
+    }
+};
+
+// Column ranges per row for residual_reduce_kernel: enough workgroups to fill the chip when there are few rows.
+// (520 rows of the 8B shape: 4 ranges 11.9 us, 1 range 13.1; 400: 9.8 / 10.0.)
+inline int reduce_parts(int M, int d) {
+    int P = M <= 32 ? 8 : 4;
+    while (P > 1 && d % (P * 64) != 0) P >>= 1;
+    return P;
+}
+// Attention of a prompt chunk: query tiles of attn_shared_kernel's workgroups (a tile per wave of a team) and chunks of keys.  A
+// workgroup has a compute unit to itself and takes 6 us and, per ring stage of a block for each team, 1.02 us with two teams of four
+// waves, 1.27 with two of five, 1.06 as one team of eight (heads of 128; of 64: 0.68 of it), about the same per tile and block: what
+// decides is how evenly the groups of 4, 5 or 8 tiles fill the chip.  The late rows see the most keys and go first, so the launch takes its
+// mean load or, where the last workgroups come as an odd few, (rounds + 1) times the length of those.  More than one chunk: the merge, 4 us
+// and 1.5 us per million values.  In us with the merge, groups of four tiles
+// alone against this choice: 32 heads, 640 rows behind 4000 keys 139 -> 108, behind 16000 420 -> 371; 40 heads, 200 rows behind 8000
+// 110 -> 98; 8 heads x 8, 800 rows behind 8000 533 -> 478.  1024 rows behind 1024 keys on 32 heads keep them: 69, against 93 + 14 with two
+// tiles per wave.
+struct PromptAttention {
+    int nwv, ksplit, chunks;
+};
+inline PromptAttention prompt_attention(int D, int Hkv, int group, int M, int P, int max_chunks) {
+    constexpr int CUS = 256;
+    static const struct {
+        int nwv, ksplit;
+        float stage;
+    } shapes[] = {{8, 2, 1.02f}, {10, 2, 1.27f}, {8, 1, 1.06f}};
+    const int NB = (P + M + 31) / 32, MQ = M * group;
+    PromptAttention best{8, 2, 1};
+    float best_cost = 1e30f;
+    for (const auto& s : shapes) {
+        const int rows = s.nwv / s.ksplit * 16, groups = (MQ + rows - 1) / rows;  // query rows of a workgroup, row groups
+        const auto blocks_seen = [&](int z) { return std::min(NB, (P + (std::min(MQ, (z + 1) * rows) - 1) / group) / 32 + 1); };
+        for (int t = 1; t <= max_chunks; ++t) {
+            const int bl = std::max(2, (NB + t - 1) / t), n = (NB + bl - 1) / bl;  // blocks per chunk, chunks
+            const float mean_stages = 0.5f * (float)(blocks_seen(0) + blocks_seen(groups - 1)) / (float)s.ksplit;  // all chunks of a row group
+            float cost = (float)(Hkv * groups) * (6.f * (float)n + s.stage * mean_stages) / (float)CUS;
+            for (int r = 0; r * CUS < Hkv * groups * n; ++r) {  // 256 r workgroups came first: the next one is the longest that is left
+                const int seen = std::min(bl, blocks_seen(groups - 1 - r * CUS / (n * Hkv)));
+                cost = std::max(cost, (float)(r + 1) * (6.f + s.stage * (float)((seen + s.ksplit - 1) / s.ksplit)));
+            }
+            if (D == 64) cost *= 0.68f;
+            if (n > 1) cost += 4.f + 1.5e-6f * (float)n * (float)MQ * (float)Hkv * (float)D;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = PromptAttention{s.nwv, s.ksplit, t};
+            }
+        }
+    }
+    return best;
+}
+
+// Attention of one pass: M rows behind P keys, `group` query heads for each of Hkv kv heads of D channels; `many`: a prompt chunk of more
+// rows than a verify pass has.
+struct AttnLaunch {
+    bool small;                   // attn_small_kernel, otherwise attn_shared_kernel
+    int nwv, ksplit, row_groups;  // attn_shared_kernel: consumer waves, teams; row groups (grid z)
+    int chunk_blocks, chunks;     // 32-key blocks of a chunk; chunks (more than one: a second kernel merges them)
+};
+
+inline AttnLaunch attention_launch(int D, int Hkv, int group, int M, int P, bool many, int max_chunks) {
+    const int NB = (P + M + 31) / 32, MqT = (M * group + 15) / 16;  // blocks of keys, query tiles per kv head
+    // One query tile per kv head on a short context: one workgroup of eight waves per kv head does the whole head without a loop, at most
+    // 32 blocks.  Against chunks and merge, 32 heads of 128: 400 keys 8.8 against 10.6 us, 700 11.6 against 10.8, 980 14.2
+    // against 11.6; 8 heads 9.5 / 10.0, 12.5 / 9.8, 14.8 / 10.2; heads of 64 8.8 against 9.6 at 980.
+    if (MqT == 1 && NB <= (D == 64 ? 32 : 20)) return {true, 8, 1, 1, NB, 1};
+    // Otherwise the kernel that stages K/V blocks in LDS for all query tiles, one query tile per wave.
+    // Up to four tiles: two teams of waves share the blocks (two waves per SIMD: 20.7 against 23.2 us at 4 tiles,
+    // 11.8 against 14.4 us at 2 tiles, measured on 32 heads x 4160 / 2080 keys).
+    // 9..16 tiles (64 rows x a GQA group of 4): 27.3 against 28.2 us at 8192 keys; 17..20 tiles (65..80 rows) in the same shape
+    // against two tiles per wave: 33.8 against 43.4 us at 8192 keys, 14.1 against 18.6 at 2048, 10.9 against 13.4 at 700.
+    AttnLaunch at{false, MqT > 2 ? 8 : 4, (MqT <= 4 || MqT > 8) ? 2 : 1, 1, 0, 1};
+    if (many) {
+        const PromptAttention p = prompt_attention(D, Hkv, group, M, P, max_chunks);
+        at.nwv = p.nwv;
+        at.ksplit = p.ksplit;
+        at.chunks = p.chunks;
+    } else if (MqT == 5 && NB >= 64) {
+        // five tiles (65..80 rows of a head without a group) on a long context: two teams of five against eight waves of which
+        // five have a tile, 25.9 -> 22.3 us on 32 heads x 4161 keys, 17.9 -> 17.3 at 2127 (at 577 keys 9.1 -> 10.3: not there)
+        at.nwv = 10;
+        at.ksplit = 2;
+    }
+    const int tiles = at.nwv / at.ksplit;
+    at.row_groups = (MqT + tiles - 1) / tiles;
+    if (!many) {
+        // LDS (teams) or registers (nine waves) leave room for one workgroup per compute unit, so no more than 256 of them: measured best
+        // for 4 tiles x 32 heads and 16 tiles x 8 heads (40 heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us).
+        at.chunks = std::min(std::max(256 / (Hkv * at.row_groups), 1), max_chunks);
+        // A short context is one chunk, the merge costs 4.3 us and its launch.  One chunk against chunks and merge, 32 heads of 128: two tiles
+        // 250 / 400 / 700 keys 9.0 / 9.6 / 13.4 against 10.9 / 11.4 / 11.7 us, three 10.3 / 11.7 / 15.9 against 11.4 / 11.6 / 12.5, four 10.8 /
+        // 12.9 against 12.1 / 12.6; one team of eight: five tiles 120 / 250 keys 10.3 / 13.6 against 12.0 / 12.2; 17 tiles on eight heads 250 / 400
+        // keys 12.0 / 14.5 against 13.4 / 13.9.
+        if (NB <= (MqT <= 2 ? 16 : at.ksplit == 2 ? 10 : 5)) at.chunks = 1;
+    }
+    at.chunk_blocks = std::max(2, (NB + at.chunks - 1) / at.chunks);
+    at.chunks = (NB + at.chunk_blocks - 1) / at.chunk_blocks;
+    return at;
+}

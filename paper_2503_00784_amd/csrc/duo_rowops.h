@@ -20,21 +20,6 @@ __device__ __forceinline__ void block_row_sum(float v, float* wsum, float* out) 
     }
 }
 
-// Which row of an operand a workgroup prepares.  An operand buffer keeps 16 bytes of eight rows together in a 128-byte line, and workgroups go to
-// the eight dies in turn, each with an L2 of its own: with one row after the other every line was written by eight dies, 16 bytes each.  So
-// the eight workgroups of eight rows (times one of `parts` column ranges) are eight places apart, on one die.  us, one
-// row after the other against this: set-up of 1024 rows 29.2 -> 18.5, the reduce kernel at 300 / 520 / 900 rows of the 8B shape 11.0 / 17.1 / 14.1 ->
-// 8.1 / 11.9 / 10.9, at 64 rows 4.6 -> 4.35, and the whole step of 64 rows 1219 -> 1204 (the end of a kernel writes its lines back).
-struct RowUnits {
-    int M, parts;
-    __host__ __device__ __forceinline__ int blocks() const { return ((M + 7) / 8 * parts + 7) / 8 * 64; }
-    __device__ __forceinline__ int row(int b, int& part) const {  // M or more: none
-        const int unit = b % 8 + b / 64 * 8, group = unit / parts;
-        part = unit - group * parts;
-        return group * 8 + (b >> 3) % 8;
-    }
-};
-
 // The first kernel of a pass, one workgroup (256 threads) per row and more for the root statistics:
 //   - x[m] = E[token_m], plus what the first RMSNorm needs (see RowScale in duo_gemm.h): u = x * gain as bf16 pairs in the QKV
 //     projection's operand buffer, the per-tile partial sums of x^2 and the whole row's; runs of eight channels per thread;
@@ -181,13 +166,6 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(RowUnits unit
         ssq_full[(size_t)m * RowScale::FULL_PARTS + threadIdx.x] = 0.f;  // unused ranges
 }
 
-// Column ranges per row for residual_reduce_kernel: enough workgroups to fill the chip when there are few rows.
-// (520 rows of the 8B shape: 4 ranges 11.9 us, 1 range 13.1; 400: 9.8 / 10.0.)
-static inline int reduce_parts(int M, int d) {
-    int P = M <= 32 ? 8 : 4;
-    while (P > 1 && d % (P * 64) != 0) P >>= 1;
-    return P;
-}
 static inline void launch_residual_reduce(int M, const float* part, int S, size_t split_stride, float* x, const u16* gain,
                                           u16* h, int d, LoRows lo_rows, int tiles, float* ssq_part, float* ssq_full,
                                           hipStream_t s) {

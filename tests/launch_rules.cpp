@@ -1,0 +1,24 @@
+// The library's own launch rules and index maps (plain arithmetic) for the tests to call.
+#define __host__
+#define __device__
+#define __forceinline__ inline
+#include "../paper_2503_00784_amd/csrc/duo_launch.h"
+
+extern "C" {
+
+int place(int b, int n) { return die_contiguous(b, n); }
+
+int row_blocks(int M, int parts) { return RowUnits{M, parts}.blocks(); }
+int row_of(int M, int parts, int b, int* part) { return RowUnits{M, parts}.row(b, *part); }
+int parts_of(int M, int d) { return reduce_parts(M, d); }
+
+int operand_tiles(int M) { return a_tiles_for(M, true); }
+int shared_last_tile(int M) { return half_tail(M); }
+int lo_row(int M, int m) { return lo_rows_for(M)(m); }
+
+void attention(int D, int Hkv, int group, int M, int P, int many, int max_chunks, int* out) {
+    const AttnLaunch a = attention_launch(D, Hkv, group, M, P, many != 0, max_chunks);
+    const int v[] = {a.small, a.nwv, a.ksplit, a.row_groups, a.chunk_blocks, a.chunks};
+    for (int i = 0; i < 6; ++i) out[i] = v[i];
+}
+}

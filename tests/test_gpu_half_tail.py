@@ -1,29 +1,23 @@
 """Operand layout of 17..80 rows whose last row tile holds one to eight rows: that tile holds their lo halves too.  Whole steps against the
 oracle at both edges of every tile count, in the launch shapes of a small model (two waves per band group) and of the 7B layer (three
-band groups per workgroup, split projections, partial results of Q/K/V), and the layout's map by itself."""
+band groups per workgroup, split projections, partial results of Q/K/V), and the layout's map by itself (the library's own,
+compiled for the host)."""
 import pytest
 
 from paper_2503_00784_amd import inputs
 from tests.gpu_util import say
+from tests.launch_rules import rules
 from tests.test_gpu_parity import _check_step, _engine_and_oracle
-
-
-def lo_row(M, m):
-    """The rule of LoRows / lo_rows_for, restated: (tiles, operand row of row m's lo half; its hi half is row m)."""
-    T = 1 if M <= 8 else (M + 15) // 16
-    if M <= 8:
-        return 1, m + 8
-    if 16 < M <= 80 and (M - 1) % 16 < 8:
-        return 2 * T - 1, (m + 16 * T if m < 16 * (T - 1) else m + 8)
-    return 2 * T, m + 16 * T
 
 
 @pytest.mark.parametrize("M", list(range(1, 82)) + [333, 1024])
 def test_every_half_has_a_row_of_its_own(M):
-    tiles = lo_row(M, 0)[0]
-    rows = list(range(M)) + [lo_row(M, m)[1] for m in range(M)]
-    assert len(set(rows)) == 2 * M and max(rows) < 16 * tiles <= 2 * 16 * ((M + 15) // 16)
+    tiles, lo = rules().operand_tiles(M), [rules().lo_row(M, m) for m in range(M)]
+    assert len(set(lo) | set(range(M))) == 2 * M and max(lo) < 16 * tiles <= 2 * 16 * ((M + 15) // 16)
     assert tiles == -(-2 * M // 16) or M > 80 or (M - 1) % 16 >= 8  # no tile more than 2 M rows need where the last tile is shared
+    if M > 16:  # a lane's hi and lo sums have the same position in their tiles, or are eight rows apart in the last one
+        shared = bool(rules().shared_last_tile(M))
+        assert all(r - m == 8 if shared and m // 16 == (M - 1) // 16 else (r - m) % 16 == 0 for m, r in enumerate(lo))
 
 
 ROWS = [(1, 16, 3), (3, 6, -1), (3, 8, -1), (5, 5, -1), (4, 8, -1), (4, 8, 3), (5, 8, -1), (5, 8, 3), (6, 8, 3), (7, 8, -1), (7, 8, 3), (4, 16, 3), (6, 12, -1), (6, 12, 3)]

@@ -1,17 +1,19 @@
-"""The maps from workgroups to rows and tiles that put writers of one cache line on one die, restated: every row (times column range) and
-every tile has exactly one workgroup, whatever the counts, and the rows of a line share a die."""
+"""The maps from workgroups to rows and tiles that put writers of one cache line on one die, the library's own, compiled for the host: every
+row (times column range) and every tile has exactly one workgroup, whatever the counts, and the rows of a line share a die."""
+import ctypes as C
+
 import pytest
+
+from tests.launch_rules import rules
 
 
 def row_units(M, parts):
     """RowUnits: {workgroup: (row, part)} of the workgroups that have one."""
-    blocks = ((M + 7) // 8 * parts + 7) // 8 * 64
-    out = {}
-    for b in range(blocks):
-        unit = b % 8 + b // 64 * 8
-        m = unit // parts * 8 + (b >> 3) % 8
+    part, out = C.c_int(), {}
+    for b in range(rules().row_blocks(M, parts)):
+        m = rules().row_of(M, parts, b, C.byref(part))
         if m < M:
-            out[b] = (m, unit % parts)
+            out[b] = (m, part.value)
     return out
 
 
@@ -25,12 +27,16 @@ def test_rows(M, parts):
         assert die.setdefault((m // 8, p), b % 8) == b % 8
 
 
+@pytest.mark.parametrize("d", [64, 320, 512, 768, 4096, 5120, 8192])
+@pytest.mark.parametrize("M", [1, 32, 33, 80, 81, 1024])
+def test_column_ranges(M, d):
+    parts = rules().parts_of(M, d)
+    assert parts in (1, 2, 4, 8) and d % (64 * parts) == 0
+
+
 @pytest.mark.parametrize("n", [1, 3, 7, 8, 9, 48, 72, 192, 230, 255, 256, 257, 501, 1000, 4096])
 def test_tiles(n):
-    def place(b):
-        die, q, r = b & 7, n >> 3, n & 7
-        return die * q + min(die, r) + (b >> 3)
-    places = [place(b) for b in range(n)]
+    places = [rules().place(b, n) for b in range(n)]
     assert sorted(places) == list(range(n))
     for die in range(8):
         mine = places[die::8]
