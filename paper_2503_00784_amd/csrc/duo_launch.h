@@ -1,6 +1,8 @@
 // Launch rules and index maps: plain arithmetic from sizes to launch shapes and places, without a word of HIP but for the qualifiers of what a
 // kernel calls too, so that a program without a GPU can evaluate them.
 #pragma once
+#include <math.h>
+
 #include <algorithm>
 
 #include "../../include/duo_verify.h"
@@ -112,12 +114,35 @@ struct AttnLaunch {
     int chunk_blocks, chunks;     // 32-key blocks of a chunk; chunks (more than one: a second kernel merges them)
 };
 
+// Whether a short context of three or more query tiles is one chunk.  Against chunks and the merge, which adds about 3 us to a step (4.2 us by
+// itself, of which one overlaps with its neighbours: whole layers with the one against the other): the more workgroups one chunk makes, the
+// longer the context up to which it wins, and the blocks behind the prefix count less, since the early rows leave them out.  us, one chunk
+// against the two kernels less 1 us, heads of 128, at 100 / 200 / 250 keys.  Three and four tiles: 64 rows on 1 head 9.5 / 10.6 / 10.8 against
+// 10.2 / 9.4 / 9.7, on 32 9.9 / 10.9 / 11.1 against 11.7 / 11.6 / 11.8; 16 rows of four on 8 heads 9.6 / 11.6 / 12.8 against 9.5 / 9.7 / 9.8.
+// More than eight: 64 rows of four on 1 head 10.5 / 12.1 / 12.2 against 9.8 / 9.7 / 9.8 (20 keys 9.4, 9.5), on 8 10.6 / 12.3 / 12.6 against 11.0 /
+// 11.6 / 12.1, on 32 11.9 / 13.8 / 14.0 against 15.0 / 16.0 / 16.2.  Five to eight, one team of eight waves, at 60 / 90 keys: 32 rows of four on
+// 8 heads 12.2 / 13.0 against 10.3 / 11.1, on 32 12.6 / 13.5 against 11.9 / 12.6, 16 rows of eight on 64 13.3 / 14.3 against 15.8 / 16.3.
+// Heads of 64 take two thirds as long and so stay one chunk further: 64 rows of four on 1 head 6.9 at 100 and 8.4 at 200 against 7.2 and 7.3, 16
+// rows of four on 8 heads 7.5 at 200 and 8.3 at 250 against 7.5 and 7.6.
+inline bool attention_one_chunk(int D, int MqT, int ksplit, int wgs, int M, int P, int NB) {
+    const int x = P / 32;  // blocks of the prefix alone
+    if (ksplit == 1) return NB <= 5 && (D == 64 || wgs >= 40 || x <= (wgs >= 32 ? 1 : 0));
+    if (NB > 10) return false;
+    if (D == 64) return wgs >= 16 || NB <= 8;
+    if (wgs >= 40) return true;
+    if (MqT > 8) return wgs >= 12 && x <= 3;
+    return x <= (wgs >= 32 ? 4 + M / 16 : 3);
+}
+
 inline AttnLaunch attention_launch(int D, int Hkv, int group, int M, int P, bool many, int max_chunks) {
     const int NB = (P + M + 31) / 32, MqT = (M * group + 15) / 16;  // blocks of keys, query tiles per kv head
-    // One query tile per kv head on a short context: one workgroup of eight waves per kv head does the whole head without a loop, at most
-    // 32 blocks.  Against chunks and merge, 32 heads of 128: 400 keys 8.8 against 10.6 us, 700 11.6 against 10.8, 980 14.2
-    // against 11.6; 8 heads 9.5 / 10.0, 12.5 / 9.8, 14.8 / 10.2; heads of 64 8.8 against 9.6 at 980.
-    if (MqT == 1 && NB <= (D == 64 ? 32 : 20)) return {true, 8, 1, 1, NB, 1};
+    // One query tile per kv head on a short context: one workgroup of eight waves per kv head does the whole head without a loop, at
+    // most 32 blocks.  Against chunks and their merge (less the 1 us of it that overlaps), heads of 128, 660 / 800 / 990 keys: 8 heads 10.5 / 11.6 /
+    // 14.0 against 8.7 / 8.6 / 9.0 us, 32 10.8 / 11.8 / 14.4 against 9.5 / 9.3 / 10.1, 64 11.3 / 12.3 / 15.1 against 10.9 / 11.7 / 12.7, 96 12.0 /
+    // 13.2 / 16.1 against 12.4 / 13.7 / 14.8; from there on the chunks are too few: 128 12.4 / 14.0 / 17.0 against 14.2 / 15.9 / 17.4, 256 17.9 / 20.2 /
+    // 24.6 against 18.3 / 21.2 / 24.4 without a merge.  Up to 640 keys the smaller number of blocks per wave decides (400 keys on 32 heads 8.7
+    // against 9.6), with heads of 64 all the way (990 keys 8.5 against 9.6).
+    if (MqT == 1 && NB <= (D == 64 || Hkv > 96 ? 32 : Hkv > 64 ? 24 : 20)) return {true, 8, 1, 1, NB, 1};
     // Otherwise the kernel that stages K/V blocks in LDS for all query tiles, one query tile per wave.
     // Up to four tiles: two teams of waves share the blocks (two waves per SIMD: 20.7 against 23.2 us at 4 tiles,
     // 11.8 against 14.4 us at 2 tiles, measured on 32 heads x 4160 / 2080 keys).
@@ -140,12 +165,14 @@ inline AttnLaunch attention_launch(int D, int Hkv, int group, int M, int P, bool
     if (!many) {
         // LDS (teams) or registers (nine waves) leave room for one workgroup per compute unit, so no more than 256 of them: measured best
         // for 4 tiles x 32 heads and 16 tiles x 8 heads (40 heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us).
-        at.chunks = std::min(std::max(256 / (Hkv * at.row_groups), 1), max_chunks);
-        // A short context is one chunk, the merge costs 4.3 us and its launch.  One chunk against chunks and merge, 32 heads of 128: two tiles
-        // 250 / 400 / 700 keys 9.0 / 9.6 / 13.4 against 10.9 / 11.4 / 11.7 us, three 10.3 / 11.7 / 15.9 against 11.4 / 11.6 / 12.5, four 10.8 /
-        // 12.9 against 12.1 / 12.6; one team of eight: five tiles 120 / 250 keys 10.3 / 13.6 against 12.0 / 12.2; 17 tiles on eight heads 250 / 400
-        // keys 12.0 / 14.5 against 13.4 / 13.9.
-        if (NB <= (MqT <= 2 ? 16 : at.ksplit == 2 ? 10 : 5)) at.chunks = 1;
+        const int wgs = Hkv * at.row_groups;
+        at.chunks = std::min(std::max(256 / wgs, 1), max_chunks);
+        // One tile on few heads: what a chunk more saves the kernel, the merge takes longer (4.1 us up to sixteen, 4.7 at 24, 5.4 at 32, 8.8 at 64
+        // chunks).  One head x 3000 / 5000 / 8200 keys in 47 / 53 / 52 chunks 11.9 / 12.9 / 13.2 us, in 24 / 23 / 29 10.2 / 11.1 / 11.8.
+        if (MqT == 1) at.chunks = std::min(at.chunks, std::max(24, (int)((D == 64 ? 1.4f : 2.f) * sqrtf((float)NB))));
+        // Two tiles on up to 512 keys, us, one chunk against chunks and merge, 32 heads of 128: 250 / 400 / 700 keys 9.0 / 9.6 / 13.4 against 9.9 /
+        // 10.4 / 10.7.
+        if (MqT == 2 ? NB <= 16 : MqT > 2 && attention_one_chunk(D, MqT, at.ksplit, wgs, M, P, NB)) at.chunks = 1;
     }
     at.chunk_blocks = std::max(2, (NB + at.chunks - 1) / at.chunks);
     at.chunks = (NB + at.chunk_blocks - 1) / at.chunk_blocks;

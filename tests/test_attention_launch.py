@@ -30,3 +30,28 @@ def test_every_launch_holds_its_work(D, Hkv, group):
         assert (a.row_groups - 1) * (a.nwv // a.ksplit) < tiles <= a.row_groups * (a.nwv // a.ksplit)
         # four waves: the first two stages are requested without a look at the row group's own number of blocks
         assert a.nwv != 4 or a.row_groups == 1
+
+
+# The sides of the rule's lines where one form was measured against the other, whole layers (kernel and merge, us, on either side in the rule's comments)
+@pytest.mark.parametrize("Hkv,group,M,P,small", [(32, 1, 8, 632, True), (32, 1, 8, 633, False), (64, 1, 8, 700, False), (96, 1, 8, 760, True), (96, 1, 8, 761, False), (97, 1, 8, 800, True), (128, 1, 8, 1016, True),
+                                                 (128, 1, 8, 1017, False), (256, 1, 16, 900, True), (8, 4, 4, 636, True), (8, 4, 4, 637, False)])
+def test_one_tile_without_a_loop(Hkv, group, M, P, small):
+    assert launch(128, Hkv, group, M, P).small == small
+    assert launch(64, Hkv, group, M, P).small == (P + M <= 1024)
+
+
+@pytest.mark.parametrize("Hkv", [1, 2, 4])
+@pytest.mark.parametrize("P,most", [(660, 24), (1400, 24), (2000, 24), (3000, 24), (5000, 25), (8200, 32), (16300, 45)])
+def test_one_tile_on_few_heads_leaves_the_merge_few_chunks(Hkv, P, most):
+    assert 8 <= launch(128, Hkv, 1, 8, P).chunks <= most
+    assert P + 8 <= 1024 or 8 <= launch(64, Hkv, 1, 8, P).chunks <= max(24, most * 3 // 4)
+
+
+@pytest.mark.parametrize("D,Hkv,group,M,P,one", [
+    (128, 8, 4, 16, 100, True), (128, 8, 4, 16, 200, False), (128, 8, 4, 16, 250, False), (128, 32, 4, 16, 180, True), (128, 32, 4, 16, 200, False),
+    (128, 1, 1, 64, 100, True), (128, 1, 1, 64, 200, False), (128, 32, 1, 64, 250, True), (128, 40, 1, 64, 250, True), (128, 40, 1, 64, 260, False),
+    (128, 1, 4, 64, 20, False), (128, 8, 4, 64, 100, True), (128, 8, 4, 64, 200, False), (128, 32, 4, 64, 230, True),
+    (128, 8, 4, 32, 60, False), (128, 8, 4, 32, 20, True), (128, 64, 8, 16, 90, True), (128, 32, 1, 80, 60, True), (128, 1, 1, 80, 60, False),
+    (64, 8, 4, 16, 200, True), (64, 8, 4, 16, 250, False), (64, 1, 4, 64, 100, True), (64, 1, 4, 64, 200, False), (64, 8, 4, 32, 90, True)])
+def test_short_context_in_one_chunk_or_more(D, Hkv, group, M, P, one):
+    assert (launch(D, Hkv, group, M, P).chunks == 1) == one
