@@ -36,8 +36,9 @@ struct AttnArgs {
     LoRows lo_rows;
 };
 
-// 2^x by the hardware instruction alone: results below the normal range come out as zero, which is all a softmax weight
-// that small amounts to; 2^0 is exactly 1 and 2^-inf exactly 0.
+// 2^x by the hardware instruction alone: results below the normal range come out as zero; 2^0 is exactly 1 and 2^-inf exactly 0.
+// Three and more query tiles take their softmax weights so: such a weight shows only next to values of 2^100 and more.  One and two tiles
+// keep them (exp2f), as do the merges.
 __device__ __forceinline__ float exp2_raw(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // The largest of the four lane groups' values (lanes c, c + 16, c + 32, c + 48), in all of them.  Lane swaps within the vector unit: the maximum of
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(512) void attn_small_kernel(AttnArgs a) {
             float pw[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                pw[j] = exp2_raw(sc[b][j] - m_safe);
+                pw[j] = exp2f(sc[b][j] - m_safe);
                 l_run += pw[j];
             }
             split_elem8(pw, pf.q, pl.q);
@@ -436,6 +437,7 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto weight = [](float x) { return NWV == 4 ? exp2f(x) : exp2_raw(x); };  // four waves: up to two query tiles
     auto use_block = [&](const u32x4* buf, int kb) {
         const bool masked = kb + 32 > a.plan.P;  // block touches draft slots or the end
         const bool tail = kb + 32 > a.Ktot;      // slots at or beyond Ktot may hold anything: zero their V
@@ -473,12 +475,12 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
         for (int j = 1; j < 8; ++j) bm = fmaxf(bm, sc[j]);
         const float m_new = fmaxf(m_run, lane_groups_max(bm) * a.scale_log2);  // the running maximum is kept in scaled units
         const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = exp2_raw(m_run - m_safe);
+        const float alpha = weight(m_run - m_safe);
         m_run = m_new;
         float pw[8], ps = 0.f;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            pw[j] = exp2_raw(fmaf(sc[j], a.scale_log2, -m_safe));
+            pw[j] = weight(fmaf(sc[j], a.scale_log2, -m_safe));
             ps += pw[j];
         }
         split_elem8(pw, pf.q, pl.q);  // softmax weights as bf16 pairs (hi + lo)
