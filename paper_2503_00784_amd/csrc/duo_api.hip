@@ -359,10 +359,10 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
             // twelve-band workgroups 26.6 + 5.5 us; 384 bands, four splits of six-band workgroups 15.2 + 4.6 us against
             // two splits of three-band workgroups 16.7 + 4.1 us)
             const int want = qkv_bands > 512 ? 2 : QKV_SPLITS;
-            if (M <= 56) launch_wide_cfg<4, 1, 6, 1, EpiStoreF32, false, false>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
-            else if (M <= 64) launch_wide_cfg<4, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
-            else if (M <= 72) launch_wide_cfg<5, 1, 6, 1, EpiStoreF32, false, false>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
-            else launch_wide_cfg<5, 1, 6, 1>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
+            for_row_tiles(M, [&](auto mh, auto whole) {
+                if constexpr (mh() >= 4)  // 49..80 rows
+                    launch_wide_cfg<mh(), 1, 6, 1, EpiStoreF32, false, whole()>(ws.h, w.wqkv[l], d, qkv_bands, quads, want, qkv_norm, ep, s, &S);
+            });
             QkvFinishArgs fa{ws.split, S, (size_t)M * ncols, ncols, Hq, Hkv, D, ws.q, qd, ws.q_plane, kc, vc, c.max_seq,
                              ws.rope_c, ws.rope_s, plan, cache.prefix_len};
             prof(DUO_PROF_QKV_FINISH, s);
