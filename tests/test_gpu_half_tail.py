@@ -2,6 +2,8 @@
 oracle at both edges of every tile count, in the launch shapes of a small model (two waves per band group) and of the 7B layer (three
 band groups per workgroup, split projections, partial results of Q/K/V), and the layout's map by itself (the library's own,
 compiled for the host)."""
+import dataclasses
+
 import pytest
 
 from paper_2503_00784_amd import inputs
@@ -42,3 +44,33 @@ def test_layer_of_the_large_model(n, k, root):
     say(f"WIDE7 rows={n * k + (root >= 0)}")
     w, oshape, eng, cache = _engine_and_oracle(B, inputs.WIDE7, 60, 160, seed=n, synthetic_cache=True)
     _check_step(B, inputs.WIDE7, w, oshape, eng, cache, n, k, seed=k, mode=0, root_token=root)
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2503_00784_amd import binding
+    binding.load()
+    return binding
+
+
+def _step(B, s, n, k, root):
+    w, oshape, eng, cache = _engine_and_oracle(B, s, 40, 160, seed=n, synthetic_cache=True)
+    _check_step(B, s, w, oshape, eng, cache, n, k, seed=k, mode=0, root_token=root)
+
+
+# The eight-wave kernel at four and five row tiles, both edges of either: an LM head of 4008 tiles, a gate/up projection of 1026
+@pytest.mark.gpu
+@pytest.mark.parametrize("vocab,d_ff", [(128256, 512), (1000, 16416)])
+@pytest.mark.parametrize("n,k,root", [(6, 8, 3), (7, 8, -1), (4, 16, 3), (6, 12, -1)])
+def test_eight_waves(B, vocab, d_ff, n, k, root):
+    say(f"vocab={vocab} d_ff={d_ff} rows={n * k + (root >= 0)}")
+    _step(B, dataclasses.replace(inputs.MID, n_layers=1, vocab=vocab, d_ff=d_ff), n, k, root)
+
+
+# Two band groups of two waves each, whose partial sums are added before the halves: gate/up of 258 tiles at every number of row
+# tiles, Q/K/V of 384 bands at two and three (beyond that its partial results take another kernel)
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k,root", [(1, 16, 3), (3, 8, -1), (4, 8, 3), (5, 8, -1), (6, 8, 3), (7, 8, -1), (4, 16, 3), (6, 12, -1)])
+def test_two_groups_of_two_waves(B, n, k, root):
+    say(f"Q/K/V of 384 bands, d_ff=4128, rows={n * k + (root >= 0)}")
+    _step(B, inputs.ModelShape(1, 256, 64, 16, 64, 4128, 1000), n, k, root)
