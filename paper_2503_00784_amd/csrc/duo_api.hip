@@ -304,7 +304,7 @@ void launch_attention(const AttnLaunch& at, int Hkv, const AttnArgs& a, hipStrea
 void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_kv_cache& cache,
                      const int32_t* tokens, int root_token, const RowPlan& plan, const Workspace& ws,
                      float* logits, int32_t* status, hipStream_t s, double temperature = -1.0) {
-    const int M = plan.M, Mp = (M + 15) / 16 * 16, AT = a_tiles_for(M, true);
+    const int M = plan.M, Mp = (M + 15) / 16 * 16, AT = a_tiles_for(M);
     const LoRows lo_rows = lo_rows_for(M);
     const int d = c.d_model, D = c.head_dim, half = D / 2, Hq = c.n_q_heads, Hkv = c.n_kv_heads;
     const int qd = Hq * D, F = c.d_ff, V = c.vocab, group = Hq / Hkv;

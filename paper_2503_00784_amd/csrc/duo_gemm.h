@@ -87,7 +87,7 @@ struct RowScale {
     }
 };
 
-template <int MT, int NT, int NW, int PF, int GRP, class Epi, bool STREAM = true>
+template <int MT, int NT, int NW, int PF, int GRP, class Epi>
 __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const u16* __restrict__ X, const u16* __restrict__ W, int K,
                                                                int quads, int pair_quads, RowScale rsc, Epi epi) {
     __shared__ f32x4 red[NW * MT * NT * 64];
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const u16* __restr
     auto load_slot = [&](int p, int i) {
         const int st = step_of(i);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) bb[p][t] = STREAM ? load_frag_stream(wp[t] + (size_t)st * 512) : load_frag(wp[t] + (size_t)st * 512);
+        for (int t = 0; t < NT; ++t) bb[p][t] = load_frag_stream(wp[t] + (size_t)st * 512);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) aa[p][mt] = load_frag(xp + ((size_t)st * MT + mt) * 512);
     };
@@ -213,9 +213,9 @@ __global__ __launch_bounds__(NW * 64) void gemm_skinny_kernel(const u16* __restr
     }
 }
 
-// Variant for more than eight rows (M = 9..80, i.e. MH = 1..5 tiles of hi rows plus as many of lo rows).
-// With that many rows the activation operand is no longer negligible next to the weights: every wave of the
-// kernel above re-reads all 2*MH tiles of it per K step.  Here the NG consumer waves of a workgroup share it
+// Variant for more than eight rows (M = 9..80, i.e. MH = 1..5 tiles of hi rows plus as many of lo rows, or one fewer
+// without WHOLE).  With that many rows the activation operand is no longer negligible next to the weights: every wave of the
+// kernel above re-reads all of its tiles per K step.  Here the NG consumer waves of a workgroup share it
 // through LDS, each taking its own group of NT weight bands (every weight byte still goes from HBM straight
 // into one wave's registers, PF steps ahead); hi and lo products accumulate into the same registers (for few
 // tiles into separate ones, so that dependent MFMAs on one accumulator have others in between), and the
@@ -911,7 +911,7 @@ static inline void launch_gemm_cfg(const u16* X, const u16* W, int K, int tiles,
                                    const Epi& epi, hipStream_t s) {
     constexpr int PF = (NT + MT) <= 4 ? 8 : ((NT + MT) <= 8 ? 4 : 2);
     constexpr int GRP = 2;
-    DUO_KERNEL_NAME("gemm_skinny_kernel<%d, %d, %d, %d, %d, %s, true>", MT, NT, NW, PF, GRP, Epi::NAME);
+    DUO_KERNEL_NAME("gemm_skinny_kernel<%d, %d, %d, %d, %d, %s>", MT, NT, NW, PF, GRP, Epi::NAME);
     DUO_LAUNCH((gemm_skinny_kernel<MT, NT, NW, PF, GRP, Epi>), dim3(tiles), dim3(NW * 64), s, X, W, K, quads, pq, rsc, epi);
 }
 
@@ -920,9 +920,8 @@ static inline void launch_gemm_cfg(const u16* X, const u16* W, int K, int tiles,
 template <int MT, int NT, class Epi>
 static inline void launch_gemm(const u16* X, const u16* W, int K, int tiles, int quads, int pq, const RowScale& rsc,
                                const Epi& epi, hipStream_t s) {
-    constexpr int NWK = 4;
     if (tiles >= 320) launch_gemm_cfg<MT, NT, 1>(X, W, K, tiles, quads, pq, rsc, epi, s);
-    else launch_gemm_cfg<MT, NT, NWK>(X, W, K, tiles, quads, pq, rsc, epi, s);
+    else launch_gemm_cfg<MT, NT, 4>(X, W, K, tiles, quads, pq, rsc, epi, s);
 }
 
 // M output rows.  Paired (at most 16): the activations are bf16 pairs, rows m and pair_rows + m of the operand.

@@ -32,9 +32,7 @@ inline int pair_rows_for(int M) { return M <= 8 ? 8 : (M + 15) / 16 * 16; }
 // The last tile holds its rows' lo halves too (see LoRows): up to sixteen rows the one-band kernels read whole tiles, prompt chunks of more
 // than 80 rows are padded to larger blocks anyway.
 inline bool half_tail(int M) { return M > 16 && M <= DUO_MAX_ROWS && (M - 1) % 16 < 8; }
-inline int a_tiles_for(int M, bool paired) {
-    return paired ? (2 * pair_rows_for(M) + 15) / 16 - (half_tail(M) ? 1 : 0) : (M + 15) / 16;
-}
+inline int a_tiles_for(int M) { return (2 * pair_rows_for(M) + 15) / 16 - (half_tail(M) ? 1 : 0); }
 inline LoRows lo_rows_for(int M) {
     const int pr = pair_rows_for(M);
     if (M <= 8) return LoRows{0, 0};

@@ -12,7 +12,7 @@ int row_blocks(int M, int parts) { return RowUnits{M, parts}.blocks(); }
 int row_of(int M, int parts, int b, int* part) { return RowUnits{M, parts}.row(b, *part); }
 int parts_of(int M, int d) { return reduce_parts(M, d); }
 
-int operand_tiles(int M) { return a_tiles_for(M, true); }
+int operand_tiles(int M) { return a_tiles_for(M); }
 int shared_last_tile(int M) { return half_tail(M); }
 int lo_row(int M, int m) { return lo_rows_for(M)(m); }
 

@@ -313,9 +313,8 @@ def test_mid_config_gqa_ragged(B, n, k, mode, root):
 def test_mid_config_long_prefix(B, n, k, root, P):
     """The MID shape (GQA group of 4, heads of 64) on a long synthetic prefix, so that a head's keys are cut into
     several chunks: 32, 64, 16, 52 and 20 (row, query head) pairs per KV head = 2, 4, 1, 4 and 2 query tiles, i.e. the
-    attention kernel whose waves form two teams over the key blocks (two and four tiles per workgroup, chunks of an even
-    and an odd number of blocks, a last block that is partly draft slots) and, for one tile, the per-wave kernel; the
-    chunk merge in all of them.  The cases of 64, 50, 80 and 64 rows add the K-split Q/K/V projection with its finish
+    attention kernel whose waves form two teams over the key blocks (one, two and four tiles per workgroup, chunks of an even
+    and an odd number of blocks, a last block that is partly draft slots), and the chunk merge in all of them.  The cases of 64, 50, 80 and 64 rows add the K-split Q/K/V projection with its finish
     kernel and 16 to 20 query tiles per KV head: prefixes that end inside a 32-key block and on a block boundary, with
     and without a root row, sequences of 7, 8 and 16 tokens."""
     shape = inputs.MID
