@@ -326,7 +326,7 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
     const bool stats = temperature >= 0.0;
     const bool root_stats = stats && plan.R == 0;
     prof(DUO_PROF_SETUP, s);
-    DUO_LAUNCH(setup_kernel, dim3(RowUnits{M, 1}.blocks() + (root_stats ? ROOT_STATS_PARTS : 0)), dim3(256), s, w.embed, tokens, root_token, plan, V,
+    DUO_LAUNCH(setup_kernel, dim3(RowUnits{M, 0}.blocks() + (root_stats ? ROOT_STATS_PARTS : 0)), dim3(256), s, w.embed, tokens, root_token, plan, V,
                cache.prefix_len, status, ws.x, w.g_attn[0], ws.h, d, lo_rows, AT, ws.ssq, ws.ssq_full, D, (double)c.rope_theta, ws.rope_c,
                ws.rope_s, RootStatsArgs{root_stats ? cache.root_logits : nullptr, V, temperature, ws.stats_root});
 

@@ -41,25 +41,31 @@ inline LoRows lo_rows_for(int M) {
 
 // Which row of an operand a workgroup prepares.  An operand buffer keeps 16 bytes of eight rows together in a 128-byte line, and workgroups go to
 // the eight dies in turn, each with an L2 of its own: with one row after the other every line was written by eight dies, 16 bytes each.  So
-// the eight workgroups of eight rows (times one of `parts` column ranges) are eight places apart, on one die.  us, one
+// the eight workgroups of eight rows (a unit: the rows times one of several column ranges) are eight places apart, on one die.  us, one
 // row after the other against this: set-up of 1024 rows 29.2 -> 18.5, the reduce kernel at 300 / 520 / 900 rows of the 8B shape 11.0 / 17.1 / 14.1 ->
 // 8.1 / 11.9 / 10.9, at 64 rows 4.6 -> 4.35, and the whole step of 64 rows 1219 -> 1204 (the end of a kernel writes its lines back).
+__host__ __device__ __forceinline__ int unit_of(int b) { return b % 8 + b / 64 * 8; }
+__host__ __device__ __forceinline__ int row_of_unit(int b) { return (b >> 3) % 8; }
+__host__ __device__ __forceinline__ int unit_blocks(int units) { return (units + 7) / 8 * 64; }
+
+// Rows times 2^parts_log2 column ranges.  A power of two: a division in front of the first load is a tenth of the reduce kernel's time
+// where rows are short (3.45 against 3.75 us, 49 rows of 512 channels).
 struct RowUnits {
-    int M, parts;
-    __host__ __device__ __forceinline__ int blocks() const { return ((M + 7) / 8 * parts + 7) / 8 * 64; }
-    __device__ __forceinline__ int row(int b, int& part) const {  // M or more: none
-        const int unit = b % 8 + b / 64 * 8, group = unit / parts;
-        part = unit - group * parts;
-        return group * 8 + (b >> 3) % 8;
+    int M, parts_log2;
+    __host__ __device__ __forceinline__ int blocks() const { return unit_blocks((M + 7) / 8 << parts_log2); }
+    __host__ __device__ __forceinline__ int row(int b, int& part) const {  // M or more: none
+        const int unit = unit_of(b);
+        part = unit & ((1 << parts_log2) - 1);
+        return (unit >> parts_log2) * 8 + row_of_unit(b);
     }
 };
 
-// Column ranges per row for residual_reduce_kernel: enough workgroups to fill the chip when there are few rows.
+// Column ranges per row for residual_reduce_kernel, as a power of two: enough workgroups to fill the chip when there are few rows.
 // (520 rows of the 8B shape: 4 ranges 11.9 us, 1 range 13.1; 400: 9.8 / 10.0.)
-inline int reduce_parts(int M, int d) {
-    int P = M <= 32 ? 8 : 4;
-    while (P > 1 && d % (P * 64) != 0) P >>= 1;
-    return P;
+inline int reduce_parts_log2(int M, int d) {
+    int p = M <= 32 ? 3 : 2;
+    while (p > 0 && d % (64 << p) != 0) --p;
+    return p;
 }
 // Attention of a prompt chunk: query tiles of attn_shared_kernel's workgroups (a tile per wave of a team) and chunks of keys.  A
 // workgroup has a compute unit to itself and takes 6 us and, per ring stage of a block for each team, 1.02 us with two teams of four

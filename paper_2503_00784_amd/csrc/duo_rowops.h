@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void setup_kernel(const u16* __restrict__ embe
                                                      int D, double theta, float* __restrict__ rc, float* __restrict__ rs, RootStatsArgs root) {
     __shared__ float wsum[4];
     __shared__ double sm[16];
-    const RowUnits units{plan.M, 1};
+    const RowUnits units{plan.M, 0};
     if ((int)blockIdx.x >= units.blocks()) {  // statistics of one slice of the root logits
         if (!root.logits) return;
         const int sl = blockIdx.x - units.blocks(), len = (root.V + ROOT_STATS_PARTS - 1) / ROOT_STATS_PARTS;
@@ -119,7 +119,7 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(RowUnits unit
                                                                    u16* __restrict__ h, int d, LoRows lo_rows, int tiles,
                                                                    float* __restrict__ ssq_part, float* __restrict__ ssq_full) {
     __shared__ float wsum[NWV];
-    const int P = units.parts, cols = d / P;
+    const int P = 1 << units.parts_log2, cols = d >> units.parts_log2;
     int pt;
     const int m = units.row(blockIdx.x, pt), c0 = pt * cols;
     if (m >= units.M) return;
@@ -169,8 +169,8 @@ __global__ __launch_bounds__(NWV * 64) void residual_reduce_kernel(RowUnits unit
 static inline void launch_residual_reduce(int M, const float* part, int S, size_t split_stride, float* x, const u16* gain,
                                           u16* h, int d, LoRows lo_rows, int tiles, float* ssq_part, float* ssq_full,
                                           hipStream_t s) {
-    const int P = reduce_parts(M, d), cols = d / P;
-    const RowUnits units{M, P};
+    const RowUnits units{M, reduce_parts_log2(M, d)};
+    const int cols = d >> units.parts_log2;
     const dim3 grid(units.blocks());
 #define DUO_REDUCE(NWV, MAXS)                                                                                                  \
     DUO_LAUNCH((residual_reduce_kernel<NWV, MAXS>), grid, dim3(NWV * 64), s, units, part, S, split_stride, x, gain, h, d, lo_rows, tiles, \

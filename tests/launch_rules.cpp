@@ -8,9 +8,9 @@ extern "C" {
 
 int place(int b, int n) { return die_contiguous(b, n); }
 
-int row_blocks(int M, int parts) { return RowUnits{M, parts}.blocks(); }
-int row_of(int M, int parts, int b, int* part) { return RowUnits{M, parts}.row(b, *part); }
-int parts_of(int M, int d) { return reduce_parts(M, d); }
+int row_blocks(int M, int parts_log2) { return RowUnits{M, parts_log2}.blocks(); }
+int row_of(int M, int parts_log2, int b, int* part) { return RowUnits{M, parts_log2}.row(b, *part); }
+int parts_of(int M, int d) { return 1 << reduce_parts_log2(M, d); }
 
 int operand_tiles(int M) { return a_tiles_for(M); }
 int shared_last_tile(int M) { return half_tail(M); }

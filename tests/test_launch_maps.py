@@ -9,9 +9,9 @@ from tests.launch_rules import rules
 
 def row_units(M, parts):
     """RowUnits: {workgroup: (row, part)} of the workgroups that have one."""
-    part, out = C.c_int(), {}
-    for b in range(rules().row_blocks(M, parts)):
-        m = rules().row_of(M, parts, b, C.byref(part))
+    part, out, log2 = C.c_int(), {}, parts.bit_length() - 1
+    for b in range(rules().row_blocks(M, log2)):
+        m = rules().row_of(M, log2, b, C.byref(part))
         if m < M:
             out[b] = (m, part.value)
     return out
