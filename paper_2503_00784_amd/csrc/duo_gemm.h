@@ -336,8 +336,11 @@ __global__ __launch_bounds__((NG * NK + 1) * 64) void gemm_wide_kernel(const u16
 
     // ---- consumers: wave (ng, nk) takes band group ng and, of every round, the K steps nk * AG .. + AG
     const int ng = wave % NG, nk = wave / NG;
-    // (a split launch's workgroups write whole lines of partial results: as they come)
-    const int tile_raw = (gridDim.y == 1 ? die_contiguous(blockIdx.x, gridDim.x) : (int)blockIdx.x) * NG + ng;
+    // A split launch's workgroups write whole lines of partial results and take their tiles as they come; so do eight waves at five row tiles
+    // (LM head of 128256 entries behind one layer, 65 / 80 rows 387.5 / 396.7 us against 395.0 / 406.1 with neighbours on one die; of 100003
+    // 366.1 / 374.3 against 362.9 / 375.0; at four row tiles equal, below 2 to 6 % in favour of the die).
+    constexpr bool BY_DIE = MH < 5 || NG < 8;
+    const int tile_raw = (BY_DIE && gridDim.y == 1 ? die_contiguous(blockIdx.x, gridDim.x) : (int)blockIdx.x) * NG + ng;
     const bool live = tile_raw < ntiles;
     const int tile = live ? tile_raw : ntiles - 1;
     const u16* wp[NT];
