@@ -296,6 +296,13 @@ void launch_attention(const AttnLaunch& at, int Hkv, const AttnArgs& a, hipStrea
     else DUO_LAUNCH((attn_shared_kernel<D, 8, 1>), grid, dim3(576), s, a);
 }
 
+template <int D>
+void launch_attention_combine(int heads, const AttnArgs& a, hipStream_t s) {
+    const HeadUnits units{a.plan.M, heads};
+    if (merge_spread(a.plan.M, heads)) DUO_LAUNCH((attn_combine_kernel<D, true>), dim3(units.blocks()), dim3(64), s, a, units);
+    else DUO_LAUNCH((attn_combine_kernel<D, false>), dim3((a.plan.M + 7) / 8 * heads), dim3(512), s, a, units);
+}
+
 // The target pass over the rows of `plan`: fills the cache slots P .. P+M-1 and writes fp32
 // logits [M][V] (row stride V) to `logits`.
 // `temperature` >= 0: the pass is followed by sampling at that temperature, so the LM head also leaves the softmax
@@ -378,8 +385,8 @@ void enqueue_forward(const duo_model_config& c, const duo_weights& w, const duo_
         else launch_attention<64>(at, Hkv, aa, s);
         if (at.chunks > 1) {
             prof(DUO_PROF_ATTN_COMB, s);
-            if (D == 128) DUO_LAUNCH((attn_combine_kernel<128>), dim3((M + 7) / 8 * group, Hkv), dim3(512), s, aa);
-            else DUO_LAUNCH((attn_combine_kernel<64>), dim3((M + 7) / 8 * group, Hkv), dim3(512), s, aa);
+            if (D == 128) launch_attention_combine<128>(Hq, aa, s);
+            else launch_attention_combine<64>(Hq, aa, s);
         }
 
         // the residual projections leave x, the next norm's operand u = x * gain and its partial sums

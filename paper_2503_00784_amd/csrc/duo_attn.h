@@ -571,10 +571,18 @@ __global__ __launch_bounds__((NWV + 1) * 64) void attn_shared_kernel(AttnArgs a)
     }
 }
 
-// Merge of the chunk partials when a head was split over several workgroups: one wave per (row, head), eight rows of one head per
-// workgroup: they share the 128-byte lines of the operand that the merge writes.
-template <int D>
-__global__ __launch_bounds__(512) void attn_combine_kernel(AttnArgs a) {
-    const int groups = (a.plan.M + 7) >> 3, gq = blockIdx.x / groups, m = (blockIdx.x - gq * groups) * 8 + (threadIdx.x >> 6);
-    if (m < a.plan.M) attn_merge_row<D>(a, blockIdx.y, m * a.group + gq, threadIdx.x & 63);
+// Merge of the chunk partials when a head was split over several workgroups: one wave per (row, head).  Eight rows of one head share the
+// 128-byte lines of the operand that the merge writes, so their waves are one workgroup or, with SPREAD, eight workgroups on one die.
+template <int D, bool SPREAD>
+__global__ __launch_bounds__(SPREAD ? 64 : 512) void attn_combine_kernel(AttnArgs a, HeadUnits units) {
+    int head, m;
+    if (SPREAD) {
+        m = units.row(blockIdx.x, head);
+    } else {
+        const int groups = (a.plan.M + 7) >> 3;
+        head = blockIdx.x / groups;
+        m = (blockIdx.x - head * groups) * 8 + (threadIdx.x >> 6);
+    }
+    const int hk = head / a.group;
+    if (head < units.heads && m < a.plan.M) attn_merge_row<D>(a, hk, m * a.group + head - hk * a.group, threadIdx.x & 63);
 }

@@ -41,7 +41,7 @@ inline LoRows lo_rows_for(int M) {
 
 // Which row of an operand a workgroup prepares.  An operand buffer keeps 16 bytes of eight rows together in a 128-byte line, and workgroups go to
 // the eight dies in turn, each with an L2 of its own: with one row after the other every line was written by eight dies, 16 bytes each.  So
-// the eight workgroups of eight rows (a unit: the rows times one of several column ranges) are eight places apart, on one die.  us, one
+// the eight workgroups of eight rows (a unit: the rows times one of several column ranges or heads) are eight places apart, on one die.  us, one
 // row after the other against this: set-up of 1024 rows 29.2 -> 18.5, the reduce kernel at 300 / 520 / 900 rows of the 8B shape 11.0 / 17.1 / 14.1 ->
 // 8.1 / 11.9 / 10.9, at 64 rows 4.6 -> 4.35, and the whole step of 64 rows 1219 -> 1204 (the end of a kernel writes its lines back).
 __host__ __device__ __forceinline__ int unit_of(int b) { return b % 8 + b / 64 * 8; }
@@ -57,6 +57,17 @@ struct RowUnits {
         const int unit = unit_of(b);
         part = unit & ((1 << parts_log2) - 1);
         return (unit >> parts_log2) * 8 + row_of_unit(b);
+    }
+};
+
+// Rows times heads, for the merge of attention chunks.
+struct HeadUnits {
+    int M, heads;
+    __host__ __device__ __forceinline__ int blocks() const { return unit_blocks((M + 7) / 8 * heads); }
+    __host__ __device__ __forceinline__ int row(int b, int& head) const {  // M or more, or heads or more: none
+        const int unit = unit_of(b), groups = (M + 7) / 8;
+        head = unit / groups;
+        return (unit - head * groups) * 8 + row_of_unit(b);
     }
 };
 
@@ -164,6 +175,7 @@ inline AttnLaunch attention_launch(int D, int Hkv, int group, int M, int P, bool
         at.nwv = 10;
         at.ksplit = 2;
     }
+    bool few_heads = false;
     const int tiles = at.nwv / at.ksplit;
     at.row_groups = (MqT + tiles - 1) / tiles;
     if (!many) {
@@ -171,14 +183,30 @@ inline AttnLaunch attention_launch(int D, int Hkv, int group, int M, int P, bool
         // for 4 tiles x 32 heads and 16 tiles x 8 heads (40 heads x 1032 keys: 240 against 280 workgroups 8.4 against 13.4 us).
         const int wgs = Hkv * at.row_groups;
         at.chunks = std::min(std::max(256 / wgs, 1), max_chunks);
-        // One tile on few heads: what a chunk more saves the kernel, the merge takes longer (4.1 us up to sixteen, 4.7 at 24, 5.4 at 32, 8.8 at 64
-        // chunks).  One head x 3000 / 5000 / 8200 keys in 47 / 53 / 52 chunks 11.9 / 12.9 / 13.2 us, in 24 / 23 / 29 10.2 / 11.1 / 11.8.
-        if (MqT == 1) at.chunks = std::min(at.chunks, std::max(24, (int)((D == 64 ? 1.4f : 2.f) * sqrtf((float)NB))));
+        // On few heads a chunk more costs the merge what it saves the kernel: no more than about 1.5 sqrt(blocks).  Steps in us, as
+        // many chunks as there are compute units (at most 64) against this.  Two kv heads of four, three layers, behind 4000 keys: 8 rows 122.2 ->
+        // 112.2, 32 rows 147.1 -> 139.3, 64 rows 169.1 -> 162.5; behind 2000: 112.4 -> 108.4, 133.0 -> 131.2, 161.4 -> 158.3.  Twelve heads of 64, two
+        // layers, behind 2000 / 6000 keys: 8 rows 103.5 -> 100.2, 106.3 -> 105.3.  Eight kv heads of 128 of four, two layers, behind 2000 / 6000
+        // keys: 1 row 377.1 -> 375.5, 382.4 -> 379.5, 8 rows 403.4 -> 398.5, 407.4 -> 403.8.  One team (five to eight tiles) takes twice as long for a block:
+        // 2 sqrt(blocks) and at least 16, 24 rows of those eight heads behind 1400 keys 442.0 -> 442.3 with 13, 445.3 with 10.  At least 12 for two teams: a
+        // stage each up to 24 blocks (the kernel alone, 16 rows of two kv heads of four behind 700 keys, 5.3 us in 12 chunks, 6.3 in 6).
+        const float root = sqrtf((float)NB);
+        const int most = at.ksplit == 1 ? std::max(16, (int)(2.f * root)) : std::max(12, (int)(1.5f * root));
+        few_heads = most < at.chunks;
+        if (few_heads) at.chunks = most;
         // Two tiles on up to 512 keys, us, one chunk against chunks and merge, 32 heads of 128: 250 / 400 / 700 keys 9.0 / 9.6 / 13.4 against 9.9 /
         // 10.4 / 10.7.
         if (MqT == 2 ? NB <= 16 : MqT > 2 && attention_one_chunk(D, MqT, at.ksplit, wgs, M, P, NB)) at.chunks = 1;
     }
     at.chunk_blocks = std::max(2, (NB + at.chunks - 1) / at.chunks);
+    // two teams take two blocks at a time: an odd one more costs them nothing and may save a chunk
+    if (few_heads && at.ksplit == 2 && at.chunks > 1) at.chunk_blocks = (at.chunk_blocks + 1) / 2 * 2;
     at.chunks = (NB + at.chunk_blocks - 1) / at.chunk_blocks;
     return at;
 }
+
+// Whether the merge of attention chunks puts eight rows of a head into eight workgroups of a wave each or into one of eight waves.  Where the rows
+// are few, one compute unit per wave: steps of 12 / 24 / 32 rows of three layers of two kv heads of four behind 6000 keys (64 chunks) 128.8 /
+// 151.3 / 156.0 us with eight waves, 123.3 / 145.6 / 151.8 with one; twelve heads behind 1400 keys, 12 rows, 103.2 against 101.5.  From 64 rows of
+// 32 heads on they are equal.
+inline bool merge_spread(int M, int heads) { return (M + 7) / 8 * heads < 128; }

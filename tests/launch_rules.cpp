@@ -10,6 +10,8 @@ int place(int b, int n) { return die_contiguous(b, n); }
 
 int row_blocks(int M, int parts_log2) { return RowUnits{M, parts_log2}.blocks(); }
 int row_of(int M, int parts_log2, int b, int* part) { return RowUnits{M, parts_log2}.row(b, *part); }
+int head_blocks(int M, int heads) { return HeadUnits{M, heads}.blocks(); }
+int head_row_of(int M, int heads, int b, int* head) { return HeadUnits{M, heads}.row(b, *head); }
 int parts_of(int M, int d) { return 1 << reduce_parts_log2(M, d); }
 
 int operand_tiles(int M) { return a_tiles_for(M); }

@@ -40,11 +40,16 @@ def test_one_tile_without_a_loop(Hkv, group, M, P, small):
     assert launch(64, Hkv, group, M, P).small == (P + M <= 1024)
 
 
-@pytest.mark.parametrize("Hkv", [1, 2, 4])
-@pytest.mark.parametrize("P,most", [(660, 24), (1400, 24), (2000, 24), (3000, 24), (5000, 25), (8200, 32), (16300, 45)])
-def test_one_tile_on_few_heads_leaves_the_merge_few_chunks(Hkv, P, most):
-    assert 8 <= launch(128, Hkv, 1, 8, P).chunks <= most
-    assert P + 8 <= 1024 or 8 <= launch(64, Hkv, 1, 8, P).chunks <= max(24, most * 3 // 4)
+@pytest.mark.parametrize("Hkv,group,M", [(1, 1, 8), (2, 4, 4), (2, 4, 16), (4, 1, 8), (2, 4, 64), (12, 1, 8), (8, 4, 16)])
+@pytest.mark.parametrize("P,most", [(1100, 12), (1400, 12), (2000, 12), (3000, 15), (5000, 19), (8200, 24), (16300, 34)])
+def test_few_heads_leave_the_merge_few_chunks(Hkv, group, M, P, most):
+    for D in (64, 128):
+        assert min(6, 256 // Hkv) <= launch(D, Hkv, group, M, P).chunks <= most
+
+
+@pytest.mark.parametrize("P,most", [(900, 16), (1400, 16), (4000, 23), (8200, 33)])
+def test_few_heads_of_one_team(P, most):
+    assert 8 <= launch(64, 2, 4, 24, P).chunks <= most and 8 <= launch(128, 8, 4, 32, P).chunks <= most
 
 
 @pytest.mark.parametrize("D,Hkv,group,M,P,one", [

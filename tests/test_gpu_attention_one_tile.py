@@ -21,3 +21,14 @@ def test_both_sides_of_the_lines(heads, kv, D, keys, k, root):
     say(f"heads {heads}/{kv} x {D} keys={keys} rows={k + (root >= 0)}")
     w, oshape, eng, cache = _engine_and_oracle(B, s, P, (keys + 31) // 32 * 32, seed=keys, synthetic_cache=True)
     _check_step(B, s, w, oshape, eng, cache, 1, k, seed=k, mode=0, root_token=root)
+
+
+# The merge of chunks, eight rows of a head in one workgroup (129 and 160 such groups) or in eight (126 and fewer), rows that do not fill the last
+@pytest.mark.parametrize("heads,kv,D,P,n,k,root", [(43, 43, 128, 1100, 2, 8, 3), (42, 42, 128, 1100, 2, 8, 3), (32, 8, 64, 1400, 3, 11, -1), (12, 4, 128, 1400, 1, 9, -1),
+                                                   (6, 2, 64, 6000, 1, 5, -1)])
+def test_merge_of_chunks(heads, kv, D, P, n, k, root):
+    from paper_2503_00784_amd import binding as B
+    s = inputs.ModelShape(1, 256, heads, kv, D, 512, 1000)
+    say(f"merge: heads {heads}/{kv} x {D} P={P} rows={n * k + (root >= 0)}")
+    w, oshape, eng, cache = _engine_and_oracle(B, s, P, (P + 80 + 31) // 32 * 32, seed=P, synthetic_cache=True)
+    _check_step(B, s, w, oshape, eng, cache, n, k, seed=k, mode=0, root_token=root)

@@ -27,6 +27,18 @@ def test_rows(M, parts):
         assert die.setdefault((m // 8, p), b % 8) == b % 8
 
 
+@pytest.mark.parametrize("heads", [1, 2, 3, 12, 32, 97])
+@pytest.mark.parametrize("M", [1, 5, 8, 9, 17, 64, 80, 81, 1024])
+def test_rows_of_heads(M, heads):
+    head, got, die = C.c_int(), [], {}
+    for b in range(rules().head_blocks(M, heads)):
+        m = rules().head_row_of(M, heads, b, C.byref(head))
+        if m < M and head.value < heads:
+            got.append((m, head.value))
+            assert die.setdefault((m // 8, head.value), b % 8) == b % 8
+    assert sorted(got) == [(m, h) for m in range(M) for h in range(heads)]
+
+
 @pytest.mark.parametrize("d", [64, 320, 512, 768, 4096, 5120, 8192])
 @pytest.mark.parametrize("M", [1, 32, 33, 80, 81, 1024])
 def test_column_ranges(M, d):
